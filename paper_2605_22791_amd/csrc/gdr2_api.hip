@@ -847,7 +847,8 @@ gdr2_status chunk_bwd(const gdr2_problem* p, const int32_t* cu, int nseq, const 
     });
     return hip_status(e, stream);
   }
-  hipError_t e = build_table(&pv, G, stream);
+  // a saving forward left its chunk table in ws with the other intermediates
+  hipError_t e = saved ? hipSuccess : build_table(&pv, G, stream);
   if (e != hipSuccess) return GDR2_EHIP;
   if (p->dtype == GDR2_BF16)
     e = dispatch<BwdRun, bf16_t>(p->Dk, p->Dv, &pv, q, k, v, log_alpha, b, w, S0, dout, dS_T, dq,

@@ -191,3 +191,31 @@ def test_chunk_table_in_workspace():
     counts = [exp_off[s + 1] - exp_off[s] for s in range(N)]
     assert sorted(order) == list(range(N))
     assert all(counts[order[i]] >= counts[order[i + 1]] for i in range(N - 1))
+
+
+@pytest.mark.parametrize("lengths", [[1], [0, 0, 65], [64] * 1024, [0] * 1023 + [3, 200], [1, 0, 70] * 700],
+                         ids=["one", "empty first", "1024", "1025", "2100"])
+def test_chunk_table_passes(lengths):
+    """The table at the edges of its passes of 1024 sequences, empty sequences among them."""
+    import torch
+    import paper_2605_22791_amd as g2
+    d = make_packed(lengths, 1, 64, 64, seed=130, dtype="bf16")
+    x = dev_inputs(d)
+    cu = torch.from_numpy(d["cu_seqlens"]).cuda()
+    T, N = sum(lengths), len(lengths)
+    lay, total, _ = ws_layout_bf16(1, T, 1, 64, 64, bwd=False, nseq=N)
+    ws = torch.zeros(total, dtype=torch.uint8, device="cuda")
+    _case(f"varlen chunk table, {N} sequences, T = {T}")
+    g2.gdr2_chunk_fwd_varlen(*[x[n] for n in ("q", "k", "v", "log_alpha", "b", "w")], cu, None, scale=d["scale"],
+                             ws=ws)
+    raw = ws.cpu().numpy()
+    region = lambda n: raw[lay[n][0]: lay[n][0] + lay[n][1]].view(np.int32)
+    L = np.array(lengths)
+    n = -(-L // 64)
+    off = np.concatenate([[0], np.cumsum(n)])
+    first = np.arange(off[-1]) - np.repeat(off[:-1], n)     # chunk number within its sequence
+    assert np.array_equal(region("coff")[:N + 1], off)
+    assert np.array_equal(region("ct0")[:off[-1]], np.repeat(d["cu_seqlens"][:-1], n) + 64 * first)
+    assert np.array_equal(region("clen")[:off[-1]], np.minimum(64, np.repeat(L, n) - 64 * first))
+    order = region("sorder")[:N]
+    assert np.array_equal(np.sort(order), np.arange(N)) and np.all(np.diff(n[order]) <= 0)
