@@ -18,11 +18,18 @@
 // Precision: every product is fp32-accurate (split hi/lo operands: T, the
 // solve, A in Y and U, A_qk, Q_g, Ktail, Ebar, Z); Y is stored in bf16.
 //
-// Decay factors are 2^(G2_r - G2_s) for r >= s, formed relative to the first
-// row p = 16 i of the row block i of r: 2^(G2_r - G2_p) * 2^(G2_p - G2_s); the
-// first factor is <= 1, the second <= 1 outside the diagonal block and bounded
-// by one block's decay inside it.  A diagonal block whose internal decay
-// exceeds e^60 is formed element by element.
+// Decay factors are 2^(G2_r - G2_s) for r >= s, split at a row p:
+// 2^(G2_r - G2_p) * 2^(G2_p - G2_s).  Off the diagonal p is the first row of r's
+// 16-row block and both factors are <= 1.  In a diagonal block p is its middle
+// row (8 of 16), so that each factor is bounded by half a block's decay; entries
+// above the diagonal may overflow there and are masked.  A diagonal block with
+// a half whose decay exceeds e^60 takes four 4-row sub-blocks: products split at
+// each sub-block's first row (both factors <= 1) and its own 4 x 4 pairs element
+// by element.  Split at the block's first row, blocks of the layer's own decay
+// distribution (exp(a) up to 16) exceeded the bound for 3 to 6 in 10^4
+// (block, head) pairs, and the element-by-element tile they took then (16 x 16 x
+// Dk serial steps, some 90 us) set the kernel's time: 8192 tokens x 16 heads
+// from raw projections took 212 us, 146 now.
 //
 // T and A_qk are computed transposed (rows = keys) so that each lane's four
 // outputs are consecutive keys of one query row: T goes to LDS as float4 rows
@@ -55,9 +62,9 @@ struct IntraCfg {
   static constexpr int OFF_K = SZ_X;
   static constexpr int OFF_TA = OFF_K + 64 * LKB * 2;
   static constexpr int OFF_MISC = OFF_TA + 64 * LTA * 4;
-  static constexpr int OFF_RQ = OFF_MISC + 16;  // fused stage: inverse norms of the q rows [64]
   // A split hi / lo, bf16 [64][LA]: hi over the k tile (dead by then), lo after the rest
   static constexpr int LA = 64 + 8;
+  static constexpr int OFF_RQ = OFF_MISC + 16;  // fused stage: inverse norms of the q rows [64]
   static constexpr int OFF_AL = OFF_RQ + 64 * 4;
   static constexpr int LDS = OFF_AL + 64 * LA * 2;
   static_assert(64 * LA * 2 <= 64 * LKB * 2, "A hi plane fits the k tile");
@@ -228,7 +235,8 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
   }
   for (int e = tid; e < 4 * DK; e += 256) {
     const int i = e / DK, c = e % DK;
-    if (sG[(16 * i) * LG + c] - sG[(16 * i + 15) * LG + c] > kDiagLimit2) unsafe[i] = 1;
+    const float gm = sG[(16 * i + 8) * LG + c];
+    if (sG[(16 * i) * LG + c] - gm > kDiagLimit2 || gm - sG[(16 * i + 15) * LG + c] > kDiagLimit2) unsafe[i] = 1;
   }
   for (int c = tid; c < DK; c += 256) a.GC[ch * (WsBf16::gc(DK) / 4) + c] = ex2(sG[(CH - 1) * LG + c]);
   if constexpr (FUSED) {
@@ -307,66 +315,9 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
   // ---- T^T and A_qk^T tiles: D[s][r] = sum_c RK_s[c] * {LE, LQ}_r[c]
   {
     unsigned char* Ao = a.Aqk + ch * WsBf16::aqk();
-#pragma unroll 1
-    for (int t = 0; t < 3; ++t) {
-      const int code = tile_of(wave, t);
-      if (code < 0) continue;
-      const int i = code >> 2, j = code & 3;
-      const int r = 16 * i + r16;  // query row of this lane's outputs
-      f4 accT = f4zero(), accA = f4zero();
-      if (unsafe[i] && i == j) {
-        // element by element: every factor 2^(G2_r - G2_s) with r >= s is <= 1
-#pragma unroll 1
-        for (int u = 0; u < 4; ++u) {
-          const int s = 16 * j + 4 * g + u;
-          float tt = 0.f, ta = 0.f;
-          if (r >= s) {
-#pragma unroll 1
-            for (int c = 0; c < DK; ++c) {
-              const float e = ex2(sG[r * LG + c] - sG[s * LG + c]) * (float)sK[s * LKB + c];
-              tt += (float)Bg[kofs(r) + c] * (float)sK[r * LKB + c] * e;
-              if constexpr (FUSED)
-                ta += (float)(__bf16)((float)Q[kofs(r) + c] * sRQ[r]) * e;
-              else
-                ta += (float)Q[kofs(r) + c] * e;
-            }
-          }
-#pragma unroll
-          for (int uu = 0; uu < 4; ++uu)
-            if (uu == u) {
-              accT[uu] = tt;
-              accA[uu] = ta;
-            }
-        }
-      } else {
-        const int s = 16 * j + r16;  // key row supplied by this lane (A operand)
-        const bool sec = i == 1;        // wave 0's second row block
-#pragma unroll
-        for (int p = 0; p < KS; ++p) {
-          const int c0 = 32 * p + 8 * g;
-          float Gs[8], Gr[8], Gp[8], ks[8], kr[8], br[8], qr[8];
-          ldf8(sG + s * LG + c0, Gs);
-          ldf8(sG + r * LG + c0, Gr);
-          ldf8(sG + (16 * i) * LG + c0, Gp);
-          unpack8(ld8(sK + s * LKB + c0), ks);
-          unpack8(ld8(sK + r * LKB + c0), kr);
-          unpack8(sec ? breg[1][p] : breg[0][p], br);
-          unpack8(sec ? qreg[1][p] : qreg[0][p], qr);
-          float rk[8], le[8], lq[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            rk[e] = ks[e] * ex2(Gp[e] - Gs[e]);
-            const float f = ex2(Gr[e] - Gp[e]);
-            le[e] = br[e] * kr[e] * f;
-            lq[e] = qr[e] * f;
-          }
-          const Fr rkf = split8(rk);
-          accT = mma3(rkf, split8(le), accT);
-          accA = mma3(rkf, split8(lq), accA);
-        }
-      }
-      // lane holds T[r][s0 + u] and A_qk[r][s0 + u], s0 = 16 j + 4 g
-      const int s0 = 16 * j + 4 * g;
+    // the lane's T[r][s0 + u] and A_qk[r][s0 + u], r = 16 i + r16, s0 = 16 j + 4 g
+    const auto emit = [&](int i, int j, const f4& accT, const f4& accA) {
+      const int r = 16 * i + r16, s0 = 16 * j + 4 * g;
       float4 tv;
       tv.x = (r > s0 + 0) ? accT[0] : 0.f;
       tv.y = (r > s0 + 1) ? accT[1] : 0.f;
@@ -378,6 +329,103 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
       for (int u = 0; u < 4; ++u) av[u] = (r >= s0 + u) ? accA[u] : 0.f;
       const size_t off = (size_t)(i * 2 + (j >> 1)) * 2048 + 16 * lane + 8 * (j & 1);
       st4split(reinterpret_cast<__bf16*>(Ao + off), reinterpret_cast<__bf16*>(Ao + off + 1024), av);
+    };
+#pragma unroll 1
+    for (int t = 0; t < 3; ++t) {
+      const int code = tile_of(wave, t);
+      if (code < 0) continue;
+      const int i = code >> 2, j = code & 3;
+      const int r = 16 * i + r16;  // query row of this lane's outputs
+      const int s = 16 * j + r16;  // key row supplied by this lane (A operand)
+      const int ref = 16 * i + (i == j ? 8 : 0);
+      const bool sec = i == 1;  // wave 0's second row block
+      f4 accT = f4zero(), accA = f4zero();
+#pragma unroll
+      for (int p = 0; p < KS; ++p) {
+        const int c0 = 32 * p + 8 * g;
+        float Gs[8], Gr[8], Gp[8], ks[8], kr[8], br[8], qr[8];
+        ldf8(sG + s * LG + c0, Gs);
+        ldf8(sG + r * LG + c0, Gr);
+        ldf8(sG + ref * LG + c0, Gp);
+        unpack8(ld8(sK + s * LKB + c0), ks);
+        unpack8(ld8(sK + r * LKB + c0), kr);
+        unpack8(sec ? breg[1][p] : breg[0][p], br);
+        unpack8(sec ? qreg[1][p] : qreg[0][p], qr);
+        float rk[8], le[8], lq[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          rk[e] = ks[e] * ex2(Gp[e] - Gs[e]);
+          const float f = ex2(Gr[e] - Gp[e]);
+          le[e] = br[e] * kr[e] * f;
+          lq[e] = qr[e] * f;
+        }
+        const Fr rkf = split8(rk);
+        accT = mma3(rkf, split8(le), accT);
+        accA = mma3(rkf, split8(lq), accA);
+      }
+      emit(i, j, accT, accA);
+    }
+    // An unsafe diagonal block again, over what the loop left there: sub-blocks
+    // sa of four rows against the keys before each as products split at the
+    // sub-block's first row, both factors <= 1 (a product's other rows and keys
+    // are clamped and not used), then its own 4 x 4 pairs element by element.
+    // q and b are re-read: rare, and it must not cost the loop registers.
+    // Wave 0 forms diagonal blocks 0 and 1, waves 1 and 3 blocks 2 and 3.
+    const int d0 = wave == 0 ? 0 : (wave == 1 ? 2 : 3), d1 = wave == 0 ? 2 : (wave == 2 ? 3 : d0 + 1);
+#pragma unroll 1
+    for (int i = d0; i < d1; ++i) {
+      if (unsafe[i] == 0) continue;
+      const int r = 16 * i + r16;
+      const __bf16 *Qr = Q + kofs(r), *Br = Bg + kofs(r);
+      const auto qn = [&](float x) { return FUSED ? (float)(__bf16)(x * sRQ[r]) : x; };
+      f4 accT = f4zero(), accA = f4zero();
+#pragma unroll 1
+      for (int sa = 1; sa < 4; ++sa) {
+        f4 xT = f4zero(), xA = f4zero();
+#pragma unroll 1
+        for (int p = 0; p < KS; ++p) {
+          const int c0 = 32 * p + 8 * g;
+          float Gr[8], Gp[8], ks[8], kr[8], br[8], qr[8], rk[8], le[8], lq[8];
+          ldf8(sG + r * LG + c0, Gr);  // the lane's key row is r too (i = j)
+          ldf8(sG + (16 * i + 4 * sa) * LG + c0, Gp);
+          unpack8(ld8(sK + r * LKB + c0), kr);
+          unpack8(ld8(Br + c0), br);
+          unpack8(ld8(Qr + c0), qr);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            rk[e] = kr[e] * ex2(fminf(Gp[e] - Gr[e], 0.f));
+            const float f = ex2(fminf(Gr[e] - Gp[e], 0.f));
+            le[e] = br[e] * kr[e] * f;
+            lq[e] = qn(qr[e]) * f;
+          }
+          const Fr rkf = split8(rk);
+          xT = mma3(rkf, split8(le), xT);
+          xA = mma3(rkf, split8(lq), xA);
+        }
+        if ((r16 >> 2) == sa && g < sa) accT = xT, accA = xA;
+      }
+      // a quarter of the channels in each of the four lanes that hold row r
+      f4 dT = f4zero(), dA = f4zero();
+      const int sd = 16 * i + 4 * (r16 >> 2);
+#pragma unroll 1
+      for (int c = (DK / 4) * g; c < (DK / 4) * (g + 1); ++c) {
+        const float Gr = sG[r * LG + c], bk = (float)Br[c] * (float)sK[r * LKB + c], qv = qn((float)Qr[c]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float x = (float)sK[(sd + u) * LKB + c] * ex2(fminf(Gr - sG[(sd + u) * LG + c], 0.f));
+          dT[u] += bk * x;
+          dA[u] += qv * x;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        dT[u] += row_partner16(dT[u], (g & 1) != 0);
+        dT[u] += row_partner32(dT[u], g >= 2);
+        dA[u] += row_partner16(dA[u], (g & 1) != 0);
+        dA[u] += row_partner32(dA[u], g >= 2);
+      }
+      if ((r16 >> 2) == g) accT = dT, accA = dA;
+      emit(i, i, accT, accA);
     }
     // zero A_qk tiles above the diagonal that share fragment blocks with causal
     // tiles, (0,1) and (2,3); the blocks of query rows 0..31 and keys 32..63 are

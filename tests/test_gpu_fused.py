@@ -105,6 +105,25 @@ def test_fused_strong_decay_diagonal_blocks():
     _check(_run(d), _oracle(d), TOL["bf16"])
 
 
+@pytest.mark.parametrize("Dk", [64, 128])
+@pytest.mark.parametrize("per_token", [5.0, 7.4, 7.6, 30.0])
+def test_fused_diagonal_block_bounds(Dk, per_token):
+    """Decay of some channels around the bounds of the diagonal blocks: a whole
+    block past e^60 with both halves below (5 a token), halves just below and just
+    above (7.4 and 7.6 over 8 tokens), far above; slow channels beside them."""
+    d = make_fused(1, 150, 2, Dk, 64, seed=330, s0_std=0.05, with_dST=True)
+    d["a"] = np.zeros_like(d["a"])
+    f = np.full(d["f"].shape, -7.0, dtype=np.float32)  # softplus(-7) = 9e-4 a token
+    f[..., ::5] = per_token                            # softplus(x) = x within 1 % from 5 on
+    f[:, 40:60, 1, 3] = per_token
+    d["f"] = f
+    d["delta"] = np.zeros_like(d["delta"])
+    _case(f"fused bf16 B1 T150 H2 Dk{Dk}, {per_token} a token on some channels")
+    # df of the fast channels is a sum that cancels to a part in e^-decay of its terms: o, S_T, and the
+    # gradients that do not run through the decay
+    _check(_run(d), _oracle(d), TOL["bf16"], names=("o", "S_T", "dq", "dk", "dv", "db", "dw", "dS0"))
+
+
 def test_fused_grouped_value_heads():
     d = make_fused(2, 130, 2, 128, 128, seed=312, Hv=4, s0_std=0.05, with_dST=True)
     _case("fused bf16 grouped H2 Hv4 B2 T130")
