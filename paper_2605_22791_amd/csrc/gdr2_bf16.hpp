@@ -217,7 +217,7 @@ __device__ __forceinline__ f4 mma_f16(f16x8 a, f16x8 b, f4 c) {
 // read as scalars.
 template <int CTRL>
 __device__ __forceinline__ float dppf(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 __device__ __forceinline__ float wave_max(float x) {
   x = fmaxf(x, dppf<0xB1>(x));   // quad_perm [1, 0, 3, 2]

@@ -1,12 +1,28 @@
-// Recurrent (token-by-token) GDR-2 forward for decoding, App. C.5.
-//
-// One workgroup per (batch, head), or per (sequence, head) of a packed batch
-// (App. C.6: the same cumulative-length layout as the chunk kernels).  The fp32 state (DK x DV) stays in registers
-// for all T tokens of the call: each thread owns RPG rows x 4 columns.  Per token
+// Recurrent (token-by-token) GDR-2 forward for decoding, App. C.5.  Per token
 //     Sbar = Diag(exp g) S,  r = Sbar^T (b*k),  S = Sbar + k (w*v - r)^T,
 //     o    = scale * S^T q = scale * (Sbar^T q + (w*v - r) (k . q)),
-// so S is read and written once per call; the column sums r and Sbar^T q are
-// reduced across the row groups through LDS in a fixed order.
+// for every (batch, head), or (sequence, head) of a packed batch (App. C.6: the
+// same cumulative-length layout as the chunk kernels).  The fp32 state stays in
+// registers for all T tokens of the call: S is read and written once.
+//
+// One token (recurrent_one_kernel) is the state's way through memory and back.
+// A workgroup takes a (batch, head) and each of its four waves a quarter of the
+// rows, one contiguous run, a whole kilobyte an access; the rows' sums meet in
+// LDS behind the only barrier.  B = 256, 16 heads, 128 x 128 (545 MB): 104.4 us,
+// 5.2 TB/s (a large copy runs at 5.1); 108.2 with five barriers and a wave's
+// accesses in two runs 8 KB apart, 110.8 with a wave per 32 columns.  B = 64
+// (within the Infinity Cache): 22.2, 23.1 and 24.4 us.
+//
+// Several tokens (recurrent_kernel) are bound by a token's latency, or with many
+// sequences by the vector instructions (four per state element).  The columns
+// of S never meet, so a wave takes CW value columns over all rows and needs
+// nothing from another: the sums over rows are DPP steps inside 8 or 16 lanes,
+// the key-side factors (exp g, b*k, q, k) are formed once per wave and handed
+// round through the wave's own LDS a token ahead, and the token after that is
+// on its way from memory: no barrier anywhere.  Two sequences x 16 heads x 128
+// x 128: 0.65 us a token, 1.48 with a workgroup per head and five barriers a
+// token; 64 sequences of 65 tokens 188 us, 295 before; a packed batch of 48
+// sequences of 1 to 16 tokens from raw projections 35.5 us, 49.9 before.
 //
 // Fused input stage (a.st.a_log set; App. C.1, App. D.2): q and k are the raw
 // projections, L2-normalised per token in fp32 and rounded to the operand
@@ -14,6 +30,7 @@
 // from the decay projection f.
 
 #include "gdr2_kernels.hpp"
+#include "gdr2_bf16.hpp"
 
 namespace gdr2 {
 
@@ -23,34 +40,212 @@ __device__ __forceinline__ float round_as(float x);
 template <>
 __device__ __forceinline__ float round_as<float>(float x) { return x; }
 template <>
-__device__ __forceinline__ float round_as<bf16_t>(float x) {
-  bf16_t t;
-  put(&t, x);
-  return to_f(t);
+__device__ __forceinline__ float round_as<bf16_t>(float x) { return (float)(__bf16)x; }
+
+// N consecutive values of one token, raw until used (a conversion at the load
+// would wait for it there)
+template <typename TIn, int N>
+struct Raw;
+template <>
+struct Raw<bf16_t, 1> {
+  uint16_t u;
+  __device__ __forceinline__ void load(const bf16_t* p) { u = p->x; }
+  __device__ __forceinline__ float at(int) const { return __uint_as_float((uint32_t)u << 16); }
+};
+template <>
+struct Raw<bf16_t, 2> {
+  uint32_t u;
+  __device__ __forceinline__ void load(const bf16_t* p) { u = *reinterpret_cast<const uint32_t*>(p); }
+  __device__ __forceinline__ float at(int i) const { return __uint_as_float(i == 0 ? u << 16 : u & 0xffff0000u); }
+};
+template <>
+struct Raw<bf16_t, 4> {
+  uint2 u;
+  __device__ __forceinline__ void load(const bf16_t* p) { u = *reinterpret_cast<const uint2*>(p); }
+  __device__ __forceinline__ float at(int i) const {
+    const uint32_t x = i < 2 ? u.x : u.y;
+    return __uint_as_float((i & 1) == 0 ? x << 16 : x & 0xffff0000u);
+  }
+};
+template <>
+struct Raw<float, 1> {
+  float u;
+  __device__ __forceinline__ void load(const float* p) { u = *p; }
+  __device__ __forceinline__ float at(int) const { return u; }
+};
+template <>
+struct Raw<float, 2> {
+  float2 u;
+  __device__ __forceinline__ void load(const float* p) { u = *reinterpret_cast<const float2*>(p); }
+  __device__ __forceinline__ float at(int i) const { return i == 0 ? u.x : u.y; }
+};
+template <>
+struct Raw<float, 4> {
+  f4 u;
+  __device__ __forceinline__ void load(const float* p) { u = *reinterpret_cast<const f4*>(p); }
+  __device__ __forceinline__ float at(int i) const { return u[i]; }
+};
+__device__ __forceinline__ void put4(float* p, const float (&x)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
+}
+__device__ __forceinline__ void put4(bf16_t* p, const float (&x)[4]) {
+  st4(reinterpret_cast<__bf16*>(p), x[0], x[1], x[2], x[3]);
+}
+// sum over the wave's 64 lanes
+__device__ __forceinline__ float wave_sum(float x, int lane) {
+  x = row_sum(x);
+  x += row_partner16(x, (lane & 16) != 0);
+  return x + row_partner32(x, lane >= 32);
 }
 
-template <int DK, int DV, typename TIn, bool FUSED>
-__global__ __launch_bounds__(256) void recurrent_kernel(RecurArgs<TIn> a) {
-  constexpr int NTHR = 256;
-  constexpr int CG = DV / 4;        // column groups of 4
-  constexpr int RG = NTHR / CG;     // row groups
-  constexpr int RPG = DK / RG;      // rows per thread
-  static_assert(NTHR % CG == 0 && DK % RG == 0, "thread split");
-  static_assert(DK <= NTHR, "one key channel per thread");
-  const int seq = blockIdx.x;
-  const int bb = seq / a.H, h = seq % a.H;
-  const int tid = threadIdx.x, cg = tid % CG, rg = tid / CG;
-  const int T = a.T, H = a.H;
-
-  __shared__ float sAl[DK], sE[DK], sK[DK], sQ[DK], sZ[DV];
-  __shared__ float redR[RG * DV], redP[RG * DV];
-  __shared__ float sRes[DV], sP[DV];
-  __shared__ float sKQ[NTHR / 64], sKK[NTHR / 64], sQQ[NTHR / 64];
-
-  float* Sg = a.S + (size_t)seq * DK * DV;
-  float4 S[RPG];
+// A wave's part of a token: NK = DK / 64 key-side rows and four value columns per lane
+template <int DK, typename TIn, bool FUSED>
+struct Token {
+  static constexpr int NK = DK / 64;
+  Raw<TIn, NK> q, k, b;
+  Raw<float, NK> g;
+  Raw<TIn, 4> v, w;
+  // ok, ov: element offsets of the lane's rows and columns
+  __device__ __forceinline__ void load(const RecurArgs<TIn>& a, size_t ok, size_t ov) {
+    k.load(a.k + ok);
+    q.load(a.q + ok);
+    b.load(a.b + ok);
+    g.load(a.g + ok);
+    v.load(a.v + ov);
+    w.load(a.w + ov);
+  }
+  // put(row, exp g, b k, q, k) for the lane's rows NK lane ..; returns k . q (all lanes)
+  template <class Put>
+  __device__ __forceinline__ float factors(const Raw<float, NK>& dl, float Adec, float eps, int lane, Put&& put) const {
+    float kv[NK], qv[NK];
 #pragma unroll
-  for (int i = 0; i < RPG; ++i) S[i] = ld4(Sg + (rg * RPG + i) * DV + 4 * cg);
+    for (int j = 0; j < NK; ++j) kv[j] = k.at(j), qv[j] = q.at(j);
+    if constexpr (FUSED) {
+      // y = x (sum x^2 + eps)^(-1/2) in the operand dtype
+      float kk = 0.f, qq = 0.f;
+#pragma unroll
+      for (int j = 0; j < NK; ++j) kk += kv[j] * kv[j], qq += qv[j] * qv[j];
+      const float rk = inv_norm(wave_sum(kk, lane), eps), rq = inv_norm(wave_sum(qq, lane), eps);
+#pragma unroll
+      for (int j = 0; j < NK; ++j) kv[j] = round_as<TIn>(kv[j] * rk), qv[j] = round_as<TIn>(qv[j] * rq);
+    }
+    float kq = 0.f;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) {
+      const float al = expf(FUSED ? decay_act(g.at(j), dl.at(j), Adec) : g.at(j));
+      put(NK * lane + j, al, b.at(j) * kv[j], qv[j], kv[j]);
+      kq += kv[j] * qv[j];
+    }
+    return wave_sum(kq, lane);
+  }
+};
+
+// ---- T = 1 -----------------------------------------------------------------
+template <int DK, int DV, typename TIn, bool FUSED>
+__global__ __launch_bounds__(256) void recurrent_one_kernel(RecurArgs<TIn> a) {
+  constexpr int NW = 4, RW = DK / NW;       // waves, rows per wave
+  constexpr int CG = DV / 4, RG = 64 / CG;  // the lanes' column and row groups
+  constexpr int RPL = RW / RG;              // rows per lane: RW wave + RG i + rg
+  static_assert(RG == 2 || RG == 4, "row groups are halves or quarters of a wave");
+  __shared__ __align__(16) float sF[NW][4 * DK];
+  __shared__ __align__(16) float sSum[2][NW][DV];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int seq = blockIdx.x, bb = seq / a.H, h = seq % a.H;
+  const int cg = lane % CG, rg = lane / CG;
+  const int HK = a.H / a.G, hk = h / a.G;  // key side (q, k, g, b) on the H / G key heads
+
+  using Tok = Token<DK, TIn, FUSED>;
+  Tok x;
+  x.load(a, ((size_t)bb * HK + hk) * DK + Tok::NK * lane, (size_t)seq * DV + 4 * cg);
+  Raw<float, Tok::NK> dl{};
+  float Adec = 0.f;
+  if constexpr (FUSED) {
+    dl.load(a.st.delta + (size_t)hk * DK + Tok::NK * lane);
+    Adec = expf(a.st.a_log[hk]);
+  }
+  float* const Sg = a.S + (size_t)seq * DK * DV + (size_t)RW * DV * wave;
+  unsigned ls = rg * DV + 4 * cg;
+  f4 S[RPL];
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) S[i] = *reinterpret_cast<const f4*>(Sg + (ls + RG * i * DV));
+
+  float* const F = sF[wave];
+  const float kq = x.factors(dl, Adec, a.st.eps, lane, [&](int row, float al, float e, float q, float k) {
+    *reinterpret_cast<float4*>(F + 4 * row) = make_float4(al, e, q, k);
+  });
+  __builtin_amdgcn_wave_barrier();
+  const float* Fl = F + 4 * (RW * wave + rg);
+  f4 pr = f4zero(), pp = f4zero();
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) {
+    const float4 f = *reinterpret_cast<const float4*>(Fl + 4 * RG * i);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      S[i][u] *= f.x;
+      pr[u] += S[i][u] * f.y;
+      pp[u] += S[i][u] * f.z;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if constexpr (RG == 4) {
+      pr[u] += row_partner16(pr[u], (lane & 16) != 0);
+      pp[u] += row_partner16(pp[u], (lane & 16) != 0);
+    }
+    pr[u] += row_partner32(pr[u], lane >= 32);
+    pp[u] += row_partner32(pp[u], lane >= 32);
+  }
+  if (rg == 0) {
+    *reinterpret_cast<f4*>(&sSum[0][wave][4 * cg]) = pr;
+    *reinterpret_cast<f4*>(&sSum[1][wave][4 * cg]) = pp;
+  }
+  __syncthreads();
+  float res[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    float r = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) r += sSum[0][w][4 * cg + u];
+    res[u] = x.v.at(u) * x.w.at(u) - r;
+  }
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) {
+    const float k = Fl[4 * RG * i + 3];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) S[i][u] += k * res[u];
+  }
+  asm volatile("" : "+v"(ls));  // addresses anew: kept from the loads they would hold registers
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) *reinterpret_cast<f4*>(Sg + (ls + RG * i * DV)) = S[i];
+  if (wave == 0 && rg == 0) {
+    float o4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float p = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) p += sSum[1][w][4 * cg + u];
+      o4[u] = a.scale * (p + res[u] * kq);
+    }
+    put4(a.o + (size_t)seq * DV + 4 * cg, o4);
+  }
+}
+
+// ---- any number of tokens --------------------------------------------------
+template <int DK, int DV, typename TIn, bool FUSED, int CW, int NW>
+__global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
+  constexpr int NSL = DV / CW;              // column slices, one per wave
+  constexpr int CG = CW / 4, RG = 64 / CG;  // the lanes' column and row groups
+  constexpr int RPL = DK / RG;              // rows per lane: RG i + rg
+  static_assert(RG == 8 || RG == 16, "row sums within 8 or 16 lanes");
+  // floats of one row group's factors: (exp g, b k, q, -) per row, then k of its rows; padded
+  constexpr int RGS = 5 * RPL + 4;
+  __shared__ __align__(16) float sF[NW][2][RG * RGS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int unit = blockIdx.x * NW + wave;
+  const int seq = unit / NSL, v0 = CW * (unit % NSL);
+  const int bb = seq / a.H, h = seq % a.H;
+  const int rg = lane % RG, cg = lane / RG;
+  const int T = a.T, H = a.H;
 
   // tokens of this sequence: bb's T tokens, or cu[bb] .. cu[bb+1) of a packed batch (clamped into [0, T])
   int t0 = 0, t1 = T;
@@ -60,106 +255,136 @@ __global__ __launch_bounds__(256) void recurrent_kernel(RecurArgs<TIn> a) {
     t1 = min(max(a.cu[bb + 1], t0), T);
     rbase = 0;
   }
+  if (t0 >= t1) return;  // no token: the state stays as it is
   const int HK = H / a.G, hk = h / a.G;  // key side (q, k, g, b) on the H / G key heads
-  const float Adec = FUSED ? expf(a.st.a_log[hk]) : 0.f;
-  for (int t = t0; t < t1; ++t) {
-    const size_t row = (rbase + t) * H + h, rowk = (rbase + t) * HK + hk;
-    // thread c < DK holds key channel c of this token (DK <= NTHR)
-    const int c = tid;
-    float kv = 0.f, qv = 0.f, bv = 0.f, kq = 0.f;
-    if (c < DK) {
-      kv = to_f(a.k[rowk * DK + c]);
-      qv = to_f(a.q[rowk * DK + c]);
-      bv = to_f(a.b[rowk * DK + c]);
-      const float gv = a.g[rowk * DK + c];
-      sAl[c] = expf(FUSED ? decay_act(gv, a.st.delta[(size_t)hk * DK + c], Adec) : gv);
-      if constexpr (!FUSED) {
-        sK[c] = kv;
-        sQ[c] = qv;
-        sE[c] = bv * kv;
-        kq = kv * qv;
-      }
-    }
-    for (int v = tid; v < DV; v += NTHR) sZ[v] = to_f(a.w[row * DV + v]) * to_f(a.v[row * DV + v]);
-    if constexpr (FUSED) {
-      // fused stage: sums of squares over the row, then y = x (sum x^2 + eps)^(-1/2) in the operand dtype
-      float kk = kv * kv, qq = qv * qv;
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) {
-        kk += __shfl_xor(kk, m);
-        qq += __shfl_xor(qq, m);
-      }
-      if ((tid & 63) == 0) {
-        sKK[tid >> 6] = kk;
-        sQQ[tid >> 6] = qq;
-      }
-      __syncthreads();
-      float sk = 0.f, sq = 0.f;
-#pragma unroll
-      for (int w2 = 0; w2 < NTHR / 64; ++w2) {
-        sk += sKK[w2];
-        sq += sQQ[w2];
-      }
-      kv = round_as<TIn>(kv * inv_norm(sk, a.st.eps));
-      qv = round_as<TIn>(qv * inv_norm(sq, a.st.eps));
-      if (c < DK) {
-        sK[c] = kv;
-        sQ[c] = qv;
-        sE[c] = bv * kv;
-        kq = kv * qv;
-      }
-    }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) kq += __shfl_xor(kq, m);
-    if ((tid & 63) == 0) sKQ[tid >> 6] = kq;
-    __syncthreads();
+  const size_t ks = (size_t)HK * DK, vs = (size_t)H * DV;  // token strides
+  using Tok = Token<DK, TIn, FUSED>;
+  const size_t ok = (rbase + t0) * ks + (size_t)hk * DK + Tok::NK * lane;
+  const size_t ov = (rbase + t0) * vs + (size_t)h * DV + v0 + 4 * cg;
 
-    float4 pr = make_float4(0.f, 0.f, 0.f, 0.f), pp = pr;
-#pragma unroll
-    for (int i = 0; i < RPG; ++i) {
-      const int c = rg * RPG + i;
-      const float al = sAl[c], e = sE[c], q = sQ[c];
-      S[i].x *= al; S[i].y *= al; S[i].z *= al; S[i].w *= al;
-      pr.x += S[i].x * e; pr.y += S[i].y * e; pr.z += S[i].z * e; pr.w += S[i].w * e;
-      pp.x += S[i].x * q; pp.y += S[i].y * q; pp.z += S[i].z * q; pp.w += S[i].w * q;
-    }
-    *reinterpret_cast<float4*>(redR + rg * DV + 4 * cg) = pr;
-    *reinterpret_cast<float4*>(redP + rg * DV + 4 * cg) = pp;
-    __syncthreads();
-    for (int v = tid; v < DV; v += NTHR) {
-      float r = 0.f, p = 0.f;
-      for (int g2 = 0; g2 < RG; ++g2) {
-        r += redR[g2 * DV + v];
-        p += redP[g2 * DV + v];
-      }
-      const float res = sZ[v] - r;
-      sRes[v] = res;
-      sP[v] = p;
-    }
-    __syncthreads();
-    float kqa = 0.f;
-#pragma unroll
-    for (int w2 = 0; w2 < NTHR / 64; ++w2) kqa += sKQ[w2];
-    const float4 res = ld4(sRes + 4 * cg);
-#pragma unroll
-    for (int i = 0; i < RPG; ++i) {
-      const float kc = sK[rg * RPG + i];
-      S[i].x += kc * res.x; S[i].y += kc * res.y; S[i].z += kc * res.z; S[i].w += kc * res.w;
-    }
-    for (int v = tid; v < DV; v += NTHR) put(a.o + row * DV + v, a.scale * (sP[v] + sRes[v] * kqa));
-    __syncthreads();
+  // Past the last token the last one is read again, so that every path issues
+  // the same loads (waits count them in issue order).
+  Tok x;
+  const auto fetch = [&](int t) {
+    const size_t d = (size_t)(min(t, t1 - 1) - t0);
+    x.load(a, ok + d * ks, ov + d * vs);
+  };
+  fetch(t0);
+  Raw<float, Tok::NK> dl{};
+  float Adec = 0.f;
+  if constexpr (FUSED) {
+    dl.load(a.st.delta + (size_t)hk * DK + Tok::NK * lane);
+    Adec = expf(a.st.a_log[hk]);
   }
+  float* const Sg = a.S + (size_t)seq * DK * DV + v0;
+  unsigned ls = rg * DV + 4 * cg;
+  f4 S[RPL];
 #pragma unroll
-  for (int i = 0; i < RPG; ++i) *reinterpret_cast<float4*>(Sg + (rg * RPG + i) * DV + 4 * cg) = S[i];
+  for (int i = 0; i < RPL; ++i) S[i] = *reinterpret_cast<const f4*>(Sg + (ls + RG * i * DV));
+
+  // the fetched token's factors into F for the lanes that hold its rows; its k . q and w * v
+  const auto stage = [&](float* F, float& kq, float (&z)[4]) {
+    kq = x.factors(dl, Adec, a.st.eps, lane, [&](int row, float al, float e, float q, float k) {
+      float* const f = F + (row % RG) * RGS;
+      *reinterpret_cast<float4*>(f + 4 * (row / RG)) = make_float4(al, e, q, 0.f);
+      f[4 * RPL + row / RG] = k;
+    });
+#pragma unroll
+    for (int u = 0; u < 4; ++u) z[u] = x.v.at(u) * x.w.at(u);
+  };
+  float kq, z[4];
+  stage(sF[wave][0], kq, z);
+  fetch(t0 + 1);
+  // the state has arrived: later waits are for tokens' operands alone
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) asm volatile("" : "+v"(S[i]));
+
+  // Token t computes from one half of sF while the next one's factors go into the
+  // other and the one after that is on its way from memory.
+  for (int t = t0, p = 0; t < t1; ++t, p ^= 1) {
+    const float* F = sF[wave][p] + rg * RGS;
+    float kqn, zn[4];
+    __builtin_amdgcn_wave_barrier();
+    stage(sF[wave][p ^ 1], kqn, zn);
+    fetch(t + 2);
+    __builtin_amdgcn_wave_barrier();
+
+    // decay, the two sums over the rows, update.  Four rows' factors at a time,
+    // the next four in flight: all at once would take 64 registers
+    float pr[4] = {0.f, 0.f, 0.f, 0.f}, pp[4] = {0.f, 0.f, 0.f, 0.f};
+    float4 f[2][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[0][j] = *reinterpret_cast<const float4*>(F + 4 * j);
+#pragma unroll
+    for (int i4 = 0; i4 < RPL / 4; ++i4) {
+      if (i4 + 1 < RPL / 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[(i4 + 1) & 1][j] = *reinterpret_cast<const float4*>(F + 4 * (4 * i4 + 4 + j));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = 4 * i4 + j;
+        const float4 y = f[i4 & 1][j];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          S[i][u] *= y.x;
+          pr[u] += S[i][u] * y.y;
+          pp[u] += S[i][u] * y.z;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    f4 kr[RPL / 4];
+#pragma unroll
+    for (int j = 0; j < RPL / 4; ++j) kr[j] = *reinterpret_cast<const f4*>(F + 4 * RPL + 4 * j);
+    float res[4], o4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      res[u] = z[u] - row_sum<RG == 8>(pr[u]);
+      o4[u] = a.scale * (row_sum<RG == 8>(pp[u]) + res[u] * kq);
+    }
+#pragma unroll
+    for (int i = 0; i < RPL; ++i)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) S[i][u] += kr[i / 4][i % 4] * res[u];
+    if (rg == 0) put4(a.o + ov + (size_t)(t - t0) * vs, o4);
+    kq = kqn;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) z[u] = zn[u];
+  }
+  asm volatile("" : "+v"(ls));  // as in recurrent_one_kernel
+#pragma unroll
+  for (int i = 0; i < RPL; ++i) *reinterpret_cast<f4*>(Sg + (ls + RG * i * DV)) = S[i];
+}
+
+template <int DK, int DV, typename TIn, bool FUSED>
+hipError_t launch_recurrent_t(const RecurArgs<TIn>& a, int B, hipStream_t st) {
+  const unsigned seqs = (unsigned)B * a.H;
+  if (a.cu == nullptr && a.T == 1) {
+    hipLaunchKernelGGL((recurrent_one_kernel<DK, DV, TIn, FUSED>), dim3(seqs), dim3(256), 0, st, a);
+  } else if (seqs * (DV / 32) <= 1024) {
+    // No more 32-column waves than SIMDs: 16 columns a wave halve a token's
+    // instructions (17 tokens, 16 heads, 128 x 128: 2 sequences 17.3 against 19.9
+    // us, 16 sequences 24.5 against 25.7; 32 sequences 38.3 against 34.9).  Each in
+    // a workgroup of its own while they still have a SIMD each, else a head's
+    // together, whose token rows then come from one L1 (16 sequences 27.8 apart).
+    constexpr int NW = DV / 16;
+    if (seqs * NW <= 1024)
+      hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, FUSED, 16, 1>), dim3(seqs * NW), dim3(64), 0, st, a);
+    else
+      hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, FUSED, 16, NW>), dim3(seqs), dim3(64 * NW), 0, st, a);
+  } else {
+    constexpr int NW = DV / 32;
+    hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, FUSED, 32, NW>), dim3(seqs), dim3(64 * NW), 0, st, a);
+  }
+  return hipGetLastError();
 }
 
 template <int DK, int DV, typename TIn>
 hipError_t launch_recurrent(const RecurArgs<TIn>& a, int B, hipStream_t st) {
-  if (a.st.a_log != nullptr)
-    hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, true>), dim3(B * a.H), dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, false>), dim3(B * a.H), dim3(256), 0, st, a);
-  return hipGetLastError();
+  return a.st.a_log != nullptr ? launch_recurrent_t<DK, DV, TIn, true>(a, B, st)
+                               : launch_recurrent_t<DK, DV, TIn, false>(a, B, st);
 }
 
 #define GDR2_INST_REC(DK, DV, TIN) \

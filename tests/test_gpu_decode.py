@@ -97,3 +97,38 @@ def test_chunk_then_decode_handoff(dtype):
     o_ref, S_ref = gdr2_recurrent_fwd(d["q"], d["k"], d["v"], d["log_alpha"], d["b"], d["w"], d["S0"], d["scale"])
     assert rel_l2(np.concatenate(outs, axis=1), o_ref) < TOL[dtype]
     assert rel_l2(host(S), S_ref) < TOL[dtype]
+
+
+# the sizes where the recurrent kernels change: one token or several, and 16 columns a wave
+# (apart, together) or 32 by the number of (sequence, head) pairs
+@pytest.mark.parametrize("B,T,H,Dk,Dv,dtype", [
+    (1, 1, 1, 64, 64, "fp32"), (3, 1, 2, 128, 64, "bf16"), (2, 1, 3, 64, 128, "bf16"), (2, 1, 1, 128, 128, "fp32"),
+    (32, 2, 4, 64, 128, "bf16"), (43, 3, 3, 128, 128, "bf16"), (64, 2, 4, 128, 128, "fp32"),
+    (257, 2, 1, 128, 128, "bf16"), (513, 3, 1, 128, 64, "fp32")])
+@pytest.mark.parametrize("fused", [False, True])
+def test_recurrent_routes(B, T, H, Dk, Dv, dtype, fused):
+    import torch
+    import paper_2605_22791_amd as g2
+    from paper_2605_22791_amd.inputs import make_fused
+    from oracle import gdr2_fused_fwd
+    _case(f"recurrent B{B} T{T} H{H} Dk{Dk} Dv{Dv} {dtype} fused={fused}")
+    dev = lambda a, t: torch.from_numpy(np.ascontiguousarray(a)).cuda().to(t)
+    io = torch.bfloat16 if dtype == "bf16" else torch.float32
+    if fused:
+        d = make_fused(B, T, H, Dk, Dv, seed=90 + B, dtype=dtype, s0_std=0.05)
+        S = dev(d["S0"], torch.float32)
+        o = g2.gdr2_fused_recurrent(*[dev(d[n], io) for n in ("q", "k", "v")], dev(d["f"], torch.float32),
+                                    dev(d["a"], torch.float32), dev(d["delta"], torch.float32), dev(d["b"], io),
+                                    dev(d["w"], io), S, scale=d["scale"], eps=d["eps"])
+        o_ref, S_ref = gdr2_fused_fwd(*[d[n] for n in ("q", "k", "v", "f", "a", "delta", "b", "w")], d["S0"],
+                                      scale=d["scale"], eps=d["eps"], dtype=dtype)
+    else:
+        d = make_inputs(B, T, H, Dk, Dv, seed=90 + B, dtype=dtype, s0_std=0.05)
+        x = dev_inputs(d)
+        S = x["S0"].clone()
+        o = g2.gdr2_recurrent_step(x["q"], x["k"], x["v"], x["log_alpha"], x["b"], x["w"], S, scale=d["scale"])
+        o_ref, S_ref = gdr2_recurrent_fwd(d["q"], d["k"], d["v"], d["log_alpha"], d["b"], d["w"], d["S0"], d["scale"])
+    assert rel_l2(host(o), o_ref) < TOL[dtype]
+    # fp32 state arithmetic; fused bf16 rounds the normalised k, where a value next to a tie can go
+    # either way (2^-8 of that value)
+    assert rel_l2(host(S), S_ref) < (1e-4 if fused and dtype == "bf16" else 1e-5)
