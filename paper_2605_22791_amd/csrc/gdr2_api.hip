@@ -496,7 +496,7 @@ struct FwdRun {
                         float* ST, void* ws, bool save, const Geo& G, hipStream_t st) {
     const Layout& L = G.L;
     const int NT = G.NT;
-    if (std::is_same<TIn, bf16_t>::value) {
+    if constexpr (std::is_same<TIn, bf16_t>::value) {
       // bf16: chunk-parallel intra-chunk kernel, then the state scan with the output
       IntraBf16Args ia{static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
                        static_cast<const bf16_t*>(v), g, static_cast<const bf16_t*>(b),
@@ -522,24 +522,24 @@ struct FwdRun {
           return save ? launch_scan_bf16<DK, DV, true, true>(x, st) : launch_scan_bf16<DK, DV, true, false>(x, st);
         }, st);
       });
+    } else {
+      IntraArgs<TIn> ia{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
+                        static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
+                        static_cast<const TIn*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
+                        at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
+                        at<float>(ws, L.GC), p->T, p->H, NT};
+      ia.vl = G.vl;
+      ia.G = G.G;
+      hipError_t e = timed(GDR2_K_FWD_INTRA, st, [&] { return launch_fwd_intra<DK, DV, TIn>(ia, p->B, st); });
+      if (e != hipSuccess) return e;
+      StateArgs<TIn> sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, ST, static_cast<TIn*>(o),
+                        save ? at<float>(ws, L.Hs) : nullptr, save ? at<float>(ws, L.Rs) : nullptr,
+                        p->T, p->H, NT, p->scale, G.nscan * p->H};
+      sa.vl = G.vl;
+      return timed(GDR2_K_FWD_STATE, st, [&] {
+        return save ? launch_fwd_state<DK, DV, true, true>(sa, st) : launch_fwd_state<DK, DV, true, false>(sa, st);
+      });
     }
-    IntraArgs<TIn> ia{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
-                      static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
-                      static_cast<const TIn*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
-                      at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
-                      at<float>(ws, L.GC), p->T, p->H, NT};
-    ia.vl = G.vl;
-    ia.G = G.G;
-    hipError_t e = timed(GDR2_K_FWD_INTRA, st, [&] { return launch_fwd_intra<DK, DV, TIn>(ia, p->B, st); });
-    if (e != hipSuccess) return e;
-    StateArgs<TIn> sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, ST, static_cast<TIn*>(o),
-                      save ? at<float>(ws, L.Hs) : nullptr, save ? at<float>(ws, L.Rs) : nullptr,
-                      p->T, p->H, NT, p->scale};
-    sa.vl = G.vl;
-    return timed(GDR2_K_FWD_STATE, st, [&] {
-      return save ? launch_fwd_state<DK, DV, TIn, true, true>(sa, G.nscan, st)
-                  : launch_fwd_state<DK, DV, TIn, true, false>(sa, G.nscan, st);
-    });
   }
 };
 
@@ -555,7 +555,7 @@ struct BwdRun {
     const int NT = G.NT;
     const bool fused = G.st.a_log != nullptr;
     hipError_t e = hipSuccess;
-    if (std::is_same<TIn, bf16_t>::value) {
+    if constexpr (std::is_same<TIn, bf16_t>::value) {
       IntraBf16Args ia{static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),
                        static_cast<const bf16_t*>(v), g, static_cast<const bf16_t*>(b),
                        static_cast<const bf16_t*>(w), at<unsigned char>(ws, L.bY),
@@ -629,51 +629,54 @@ struct BwdRun {
       });
       if (e != hipSuccess || !fused) return e;
       return timed(GDR2_K_STAGE_BWD, st, [&] { return stage_bwd<DK>(p, G, ws, q, k, dq, dk, da, ddelta, st); });
-    }
-    IntraArgs<TIn> ia{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
-                      static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
-                      static_cast<const TIn*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
-                      at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
-                      at<float>(ws, L.GC), p->T, p->H, NT};
-    ia.vl = G.vl;
-    ia.G = G.G;
-    StateArgs<TIn> sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, nullptr, nullptr,
-                      at<float>(ws, L.Hs), at<float>(ws, L.Rs), p->T, p->H, NT, p->scale};
-    sa.vl = G.vl;
-    if (!saved) {
-      e = timed(GDR2_K_BWD_RECOMPUTE_INTRA, st, [&] { return launch_fwd_intra<DK, DV, TIn>(ia, p->B, st); });
+    } else {
+      IntraArgs<TIn> ia{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
+                        static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
+                        static_cast<const TIn*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
+                        at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
+                        at<float>(ws, L.GC), p->T, p->H, NT};
+      ia.vl = G.vl;
+      ia.G = G.G;
+      StateArgs<TIn> sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, nullptr, nullptr,
+                        at<float>(ws, L.Hs), at<float>(ws, L.Rs), p->T, p->H, NT, p->scale,
+                        G.nscan * p->H};
+      sa.vl = G.vl;
+      if (!saved) {
+        e = timed(GDR2_K_BWD_RECOMPUTE_INTRA, st, [&] { return launch_fwd_intra<DK, DV, TIn>(ia, p->B, st); });
+        if (e != hipSuccess) return e;
+        e = timed(GDR2_K_BWD_RECOMPUTE_STATE, st,
+                  [&] { return launch_fwd_state<DK, DV, false, true>(sa, st); });
+        if (e != hipSuccess) return e;
+      }
+      BwdStateArgs<TIn> ba{ia.Qg, ia.Kt, ia.Y, ia.Aqk, ia.GC, static_cast<const TIn*>(dout), dST,
+                           dS0, at<float>(ws, L.DH), at<float>(ws, L.DR), p->T, p->H, NT, p->scale,
+                           G.nscan * p->H};
+      ba.vl = G.vl;
+      e = timed(GDR2_K_BWD_STATE, st, [&] { return launch_bwd_state<DK, DV>(ba, st); });
       if (e != hipSuccess) return e;
-      e = timed(GDR2_K_BWD_RECOMPUTE_STATE, st,
-                [&] { return launch_fwd_state<DK, DV, TIn, false, true>(sa, G.nscan, st); });
+      BwdChunkArgs<TIn> ca{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
+                           static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
+                           static_cast<const TIn*>(w), static_cast<const TIn*>(dout),
+                           sa.Hs, ba.DH, sa.Rs, ba.DR, at<float>(ws, L.DAqk), at<float>(ws, L.DT),
+                           at<float>(ws, L.DEg), static_cast<TIn*>(dq), static_cast<TIn*>(dk),
+                           static_cast<TIn*>(dv), static_cast<TIn*>(db), static_cast<TIn*>(dw), dg,
+                           p->T, p->H, NT, p->scale};
+      ca.vl = G.vl;
+      ca.G = G.G;
+      e = timed(GDR2_K_BWD_WY, st, [&] { return launch_bwd_wy<DK, DV, TIn>(ca, p->B, st); });
       if (e != hipSuccess) return e;
+      if (G.G > 1) {  // the key-side gradients of each value head go to the fp32 partials
+        ca.dq = reinterpret_cast<TIn*>(at<float>(ws, L.pQ));
+        ca.dk = reinterpret_cast<TIn*>(at<float>(ws, L.pK));
+        ca.db = reinterpret_cast<TIn*>(at<float>(ws, L.pB));
+        ca.dg = at<float>(ws, L.pG);
+      }
+      return timed(GDR2_K_BWD_INTRA, st, [&] {
+        hipError_t r = launch_bwd_intra<DK, DV, TIn>(ca, p->B, st);
+        if (r == hipSuccess && G.G > 1) r = group_reduce<TIn>(p, G, L, ws, dq, dk, db, dg, st);
+        return r;
+      });
     }
-    BwdStateArgs<TIn> ba{ia.Qg, ia.Kt, ia.Y, ia.Aqk, ia.GC, static_cast<const TIn*>(dout), dST,
-                         dS0, at<float>(ws, L.DH), at<float>(ws, L.DR), p->T, p->H, NT, p->scale};
-    ba.vl = G.vl;
-    e = timed(GDR2_K_BWD_STATE, st, [&] { return launch_bwd_state<DK, DV, TIn>(ba, G.nscan, st); });
-    if (e != hipSuccess) return e;
-    BwdChunkArgs<TIn> ca{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
-                         static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
-                         static_cast<const TIn*>(w), static_cast<const TIn*>(dout),
-                         sa.Hs, ba.DH, sa.Rs, ba.DR, at<float>(ws, L.DAqk), at<float>(ws, L.DT),
-                         at<float>(ws, L.DEg), static_cast<TIn*>(dq), static_cast<TIn*>(dk),
-                         static_cast<TIn*>(dv), static_cast<TIn*>(db), static_cast<TIn*>(dw), dg,
-                         p->T, p->H, NT, p->scale};
-    ca.vl = G.vl;
-    ca.G = G.G;
-    e = timed(GDR2_K_BWD_WY, st, [&] { return launch_bwd_wy<DK, DV, TIn>(ca, p->B, st); });
-    if (e != hipSuccess) return e;
-    if (G.G > 1) {  // the key-side gradients of each value head go to the fp32 partials
-      ca.dq = reinterpret_cast<TIn*>(at<float>(ws, L.pQ));
-      ca.dk = reinterpret_cast<TIn*>(at<float>(ws, L.pK));
-      ca.db = reinterpret_cast<TIn*>(at<float>(ws, L.pB));
-      ca.dg = at<float>(ws, L.pG);
-    }
-    return timed(GDR2_K_BWD_INTRA, st, [&] {
-      hipError_t r = launch_bwd_intra<DK, DV, TIn>(ca, p->B, st);
-      if (r == hipSuccess && G.G > 1) r = group_reduce<TIn>(p, G, L, ws, dq, dk, db, dg, st);
-      return r;
-    });
   }
 };
 

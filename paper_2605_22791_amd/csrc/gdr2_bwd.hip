@@ -3,7 +3,7 @@
 //   bwd_state  reverse inter-chunk scan (state and output paths, App. B.1):
 //                dR_n  = scale * Aqk^T dO_n + Ktail dS_{n+1}
 //                dS_n  = Diag(gamma_C) dS_{n+1} + scale * Qg^T dO_n - Y^T dR_n
-//              one workgroup per (value slice, head, batch), dS slice in LDS.
+//              one workgroup per (sequence, head) and 16-column value slice.
 //   bwd_wy     the gate-aware WY vector-Jacobian product (App. B.2, the
 //              method-specific step): dA_qk, dY = -dR S0^T, dZ = A^T dR (-> dw,
 //              dv), dEbar = A^T dY, dA = dR Z^T + dY Ebar^T with the gates inside
@@ -22,132 +22,187 @@
 
 #include "gdr2_kernels.hpp"
 
+#include <type_traits>
+
 namespace gdr2 {
 
 // ---------------------------------------------------------------------------
-template <int DK, int DV, int DVS, typename TIn>
-__global__ __launch_bounds__(256) void bwd_state_kernel(BwdStateArgs<TIn> a) {
-  constexpr int NTHR = 256, NW = 4;
-  constexpr int LSS = DVS + 4;
-  constexpr int NVB = DVS / 16;
-  const int vs = blockIdx.x, h = blockIdx.y, bb = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int T = a.T, H = a.H, NT = a.NT;
-  const int v0 = vs * DVS;
-  const size_t seq = (size_t)scan_pair(a.vl, bb * H + h, H);  // (sequence, head) pair
-  const ScanRange rng = scan_range(a.vl, (int)seq, H, NT);
+// The forward state kernel's plan (gdr2_fwd.hip) run backwards: 16 value columns
+// a workgroup, a dS tile per wave in registers, operands two chunks ahead.  Waves
+// 0-3 form dR while waves 4-7 form Qg^T dO, which needs no dS, for their own tile
+// and for that of wave - 4.  8 sequences x 16 chunks at 128 x 128: 65 us (385
+// with 32 columns, four waves and operands loaded where they are used).
+template <int DK, int DV>
+__global__ __launch_bounds__(512) void bwd_state_kernel(BwdStateArgs<float> a) {
+  constexpr int NCB = DK / 16;
+  constexpr int LT = DK + 4, LR = CH + 4;
+  int q, vs;
+  if (!state_slot<DV / 16>(blockIdx.x, a.nq, q, vs)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4, v0 = 16 * vs + lr;
+  const size_t seq = (size_t)scan_pair(a.vl, q, a.H);  // (sequence, head) pair
+  const int h = (int)(seq % a.H);
+  const ScanRange rng = scan_range(a.vl, (int)seq, a.H, a.NT);
+  const bool low = wave < 4, own = NCB == 8 || low;
+  const int i = wave & 3, cb = own ? wave : 0;
 
-  __shared__ float sdS[DK * LSS];
-  __shared__ float sdO[CH * LSS];
-  __shared__ float sdR[CH * LSS];
+  __shared__ __align__(16) float sS[16 * LT];     // dS [v][c]
+  __shared__ __align__(16) float sO[2][16 * LR];  // scale dO [v][r], by chunk parity
+  __shared__ __align__(16) float sR[16 * LR];     // dR [v][r]
+  __shared__ __align__(16) f4 sQ[4][64];          // Qg^T dO tiles of waves 0-3
 
-  for (int e = tid; e < DK * DVS; e += NTHR) {
-    const int c = e / DVS, v = e % DVS;
-    sdS[c * LSS + v] = a.dST ? a.dST[(seq * DK + c) * DV + v0 + v] : 0.f;
+  f4 st = f4{0.f, 0.f, 0.f, 0.f};  // dS[16 cb + 4 lg + u][v0]
+  const size_t so = (seq * DK + 16 * cb + 4 * lg) * DV + v0;
+  if (own) {
+    if (a.dST != nullptr) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) st[u] = a.dST[so + (size_t)u * DV];
+    }
+    *reinterpret_cast<f4*>(sS + lr * LT + 16 * cb + 4 * lg) = st;
   }
-  __syncthreads();
 
-  for (int n = rng.c1 - 1; n >= rng.c0; --n) {
-    const size_t ch = rng.chs + n;
-    const float* Qg = a.Qg + ch * CH * DK;
-    const float* Kt = a.Kt + ch * CH * DK;
-    const float* Y = a.Y + ch * CH * DK;
-    const float* Aqk = a.Aqk + ch * CH * CH;
-    const float* GC = a.GC + ch * DK;
-    size_t orow0;
-    int olen;
-    scan_rows(a.vl, (int)seq, H, T, n, orow0, olen);
-
-    for (int e = tid; e < CH * DVS; e += NTHR) {
-      const int r = e / DVS, v = e % DVS;
-      sdO[r * LSS + v] = a.scale * to_fz(a.dout + ((orow0 + r) * H + h) * DV + v0 + v, r < olen);
-    }
-    {
-      float* DHn = a.DH + ch * DK * DV;
-      for (int e = tid; e < DK * DVS; e += NTHR) {
-        const int c = e / DVS, v = e % DVS;
-        DHn[c * DV + v0 + v] = sdS[c * LSS + v];
-      }
-    }
-    __syncthreads();
-
-    // dR = Aqk^T dO + Ktail dS   (wave -> row block of dR)
-    {
-      const int i = wave;
-      f4 acc[NVB];
+  // the two roles as code of their own (as in the forward kernel)
+  const auto run = [&](auto LOWC) {
+    constexpr bool LOW = decltype(LOWC)::value, OWN = NCB == 8 || LOW;
+    struct Ops {
+      // waves 0-3: row 16 i + lr of Ktail; waves 4-7: Qg[16 j + 4 lg + t][16 wave + lr] in p[j],
+      // the same of key block wave - 4 in p[4 + j] (DK = 64: that one alone, in p[j])
+      float4 p[8];
+      float x[4][4];  // waves 0-3: Aqk[16 j + 4 lg + t][16 i + lr]
+      float y[4][4];  // Y[16 j + 4 lg + t][16 cb + lr]
+      float4 g;       // gamma_C of channels 16 cb + 4 lg ..
+      float2 d;       // dO row tid / 8, columns 2 (tid % 8) .. of the slice
+      bool in;        // the row is one of the chunk's
+    };
+    const auto cols = [&](const float* P, int ld, float (&o)[4][4]) {  // P at row 4 lg
 #pragma unroll
-      for (int vb = 0; vb < NVB; ++vb) acc[vb] = f4{0.f, 0.f, 0.f, 0.f};
-      for (int kk = 16 * i; kk < CH; kk += 4) {
-        const int r = kk + lg;
-        const float av = Aqk[r * CH + 16 * i + lr];
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) acc[vb] = mfma4(av, sdO[r * LSS + 16 * vb + lr], acc[vb]);
-      }
-      const float* pk = Kt + (16 * i + lr) * DK + 4 * lg;
-      for (int kk = 0; kk < DK; kk += 16) {
-        const float4 kt = ld4(pk + kk);
-        const int c0 = kk + 4 * lg;
+        for (int t = 0; t < 4; ++t) o[j][t] = P[(16 * j + t) * ld];
+    };
+    const auto col4 = [&](const float* P) { return make_float4(P[0], P[DK], P[2 * DK], P[3 * DK]); };
+    const auto load = [&](Ops& o, int n) {
+      n = max(n, rng.c0);  // past the start: the first chunk again, unused
+      const size_t ch = rng.chs + n;
+      size_t row0;
+      int len;
+      scan_rows(a.vl, (int)seq, a.H, a.T, n, row0, len);
+      // rows past the chunk's end read its last row; put_dO makes them zero
+      const int r = tid >> 3;
+      o.in = r < len;
+      o.d = *reinterpret_cast<const float2*>(a.dout + ((row0 + min(r, len - 1)) * a.H + h) * DV + 16 * vs + 2 * (tid & 7));
+      if (LOW) {
+        const float* K = a.Kt + (ch * CH + 16 * i + lr) * DK + 4 * lg;
 #pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) {
-          acc[vb] = mfma4(kt.x, sdS[(c0 + 0) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(kt.y, sdS[(c0 + 1) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(kt.z, sdS[(c0 + 2) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(kt.w, sdS[(c0 + 3) * LSS + 16 * vb + lr], acc[vb]);
+        for (int j = 0; j < DK / 16; ++j) o.p[j] = ld4(K + 16 * j);
+        cols(a.Aqk + (ch * CH + 4 * lg) * CH + 16 * i + lr, CH, o.x);
+      } else {
+        const float* Q = a.Qg + (ch * CH + 4 * lg) * DK + lr;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o.p[j] = col4(Q + 16 * j * DK + 16 * (OWN ? wave : wave - 4));
+        if (OWN) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) o.p[4 + j] = col4(Q + 16 * j * DK + 16 * (wave - 4));
         }
       }
-      float* DRn = a.DR + ch * CH * DV;
+      if (OWN) {
+        cols(a.Y + (ch * CH + 4 * lg) * DK + 16 * cb + lr, DK, o.y);
+        o.g = ld4(a.GC + ch * DK + 16 * cb + 4 * lg);
+      }
+    };
+    const auto put_dO = [&](const Ops& o, int par) {
+      float* d = sO[par] + 2 * (tid & 7) * LR + (tid >> 3);
+      d[0] = o.in ? a.scale * o.d.x : 0.f;
+      d[LR] = o.in ? a.scale * o.d.y : 0.f;
+    };
+    // nx: the next chunk's operands
+    const auto step = [&](Ops& o, const Ops& nx, int n, int par) {
+      const size_t ch = rng.chs + n;
+      if (OWN) {
+        float* Hn = a.DH + (ch * DK + 16 * cb + 4 * lg) * DV + v0;
 #pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
+        for (int u = 0; u < 4; ++u) Hn[u * DV] = st[u];
+      }
+      const float* dO = sO[par] + lr * LR + 4 * lg;
+      f4 acc = f4{0.f, 0.f, 0.f, 0.f}, ac2 = acc;
+      if (LOW) {  // dR = Ktail dS + Aqk^T dO, rows of block i
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int r = 16 * i + 4 * lg + u;
-          sdR[r * LSS + 16 * vb + lr] = acc[vb][u];
-          DRn[r * DV + v0 + 16 * vb + lr] = acc[vb][u];
+        for (int j = 0; j < DK / 16; ++j) {
+          const float4 k = o.p[j], s = ld4(sS + lr * LT + 16 * j + 4 * lg);
+          acc = mfma4(k.x, s.x, acc);
+          ac2 = mfma4(k.y, s.y, ac2);
+          acc = mfma4(k.z, s.z, acc);
+          ac2 = mfma4(k.w, s.w, ac2);
         }
-    }
-    __syncthreads();
-
-    // dS <- Diag(gamma_C) dS + Qg^T dO - Y^T dR
-    constexpr int NTILE = (DK / 16) * NVB;
-    constexpr int TPW = (NTILE + NW - 1) / NW;
-    f4 nacc[TPW];
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      const int t = wave + q * NW;
-      if (t < NTILE) {
-        const int cb = t / NVB, vb = t % NVB;
-        f4 acc;
+        for (int j = 0; j < 4; ++j) {
+          if (j < i) continue;
+          const float4 d = ld4(dO + 16 * j);
+          acc = mfma4(o.x[j][0], d.x, acc);
+          ac2 = mfma4(o.x[j][1], d.y, ac2);
+          acc = mfma4(o.x[j][2], d.z, acc);
+          ac2 = mfma4(o.x[j][3], d.w, ac2);
+        }
+        acc += ac2;
+        *reinterpret_cast<f4*>(sR + lr * LR + 16 * i + 4 * lg) = acc;
+        float* Rn = a.DR + (ch * CH + 16 * i + 4 * lg) * DV + v0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int c = 16 * cb + 4 * lg + u;
-          acc[u] = GC[c] * sdS[c * LSS + 16 * vb + lr];
+        for (int u = 0; u < 4; ++u) Rn[u * DV] = acc[u];
+      } else {  // Qg^T dO: this wave's tile in acc, that of wave - 4 through LDS
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float4 d = ld4(dO + 16 * j), x = o.p[j], y = o.p[4 + j];
+          acc = mfma4(x.x, d.x, acc);
+          if (OWN) ac2 = mfma4(y.x, d.x, ac2);
+          acc = mfma4(x.y, d.y, acc);
+          if (OWN) ac2 = mfma4(y.y, d.y, ac2);
+          acc = mfma4(x.z, d.z, acc);
+          if (OWN) ac2 = mfma4(y.z, d.z, ac2);
+          acc = mfma4(x.w, d.w, acc);
+          if (OWN) ac2 = mfma4(y.w, d.w, ac2);
         }
-        for (int kk = 0; kk < CH; kk += 4) {
-          const int r = kk + lg;
-          acc = mfma4(Qg[r * DK + 16 * cb + lr], sdO[r * LSS + 16 * vb + lr], acc);
-          acc = mfma4(-Y[r * DK + 16 * cb + lr], sdR[r * LSS + 16 * vb + lr], acc);
+        sQ[i][lane] = OWN ? ac2 : acc;
+      }
+      __syncthreads();  // dR and the tiles are there, and nobody reads this chunk's dS any more
+      if (OWN) {
+        // dS <- Diag(gamma_C) dS + Qg^T dO - Y^T dR
+        const f4 qd = LOW ? sQ[i][lane] : acc;
+        st = f4{o.g.x * st[0], o.g.y * st[1], o.g.z * st[2], o.g.w * st[3]} + qd;
+        f4 y1 = f4{0.f, 0.f, 0.f, 0.f}, y2 = y1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float4 r = ld4(sR + lr * LR + 16 * j + 4 * lg);
+          y1 = mfma4(o.y[j][0], r.x, y1);
+          y2 = mfma4(o.y[j][1], r.y, y2);
+          y1 = mfma4(o.y[j][2], r.z, y1);
+          y2 = mfma4(o.y[j][3], r.w, y2);
         }
-        nacc[q] = acc;
+        st -= y1 + y2;
+        *reinterpret_cast<f4*>(sS + lr * LT + 16 * cb + 4 * lg) = st;
+      }
+      put_dO(nx, par ^ 1);
+      load(o, n - 2);
+      __syncthreads();
+    };
+    if (rng.c0 < rng.c1) {
+      Ops oa, ob;
+      load(oa, rng.c1 - 1);
+      load(ob, rng.c1 - 2);
+      put_dO(oa, 0);
+      __syncthreads();
+      for (int n = rng.c1 - 1; n >= rng.c0; n -= 2) {
+        step(oa, ob, n, 0);
+        if (n - 1 >= rng.c0) step(ob, oa, n - 1, 1);
       }
     }
-    __syncthreads();
+  };
+  if (low)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
+  if (a.dS0 != nullptr && own) {
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      const int t = wave + q * NW;
-      if (t < NTILE) {
-        const int cb = t / NVB, vb = t % NVB;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) sdS[(16 * cb + 4 * lg + u) * LSS + 16 * vb + lr] = nacc[q][u];
-      }
-    }
-    __syncthreads();
-  }
-  if (a.dS0) {
-    for (int e = tid; e < DK * DVS; e += NTHR) {
-      const int c = e / DVS, v = e % DVS;
-      a.dS0[(seq * DK + c) * DV + v0 + v] = sdS[c * LSS + v];
-    }
+    for (int u = 0; u < 4; ++u) a.dS0[so + (size_t)u * DV] = st[u];
   }
 }
 
@@ -586,11 +641,9 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
 }
 
 // ---------------------------------------------------------------------------
-template <int DK, int DV, typename TIn>
-hipError_t launch_bwd_state(const BwdStateArgs<TIn>& a, int B, hipStream_t st) {
-  constexpr int DVS = 32;
-  dim3 grid(DV / DVS, a.H, B);
-  hipLaunchKernelGGL((bwd_state_kernel<DK, DV, DVS, TIn>), grid, dim3(256), 0, st, a);
+template <int DK, int DV>
+hipError_t launch_bwd_state(const BwdStateArgs<float>& a, hipStream_t st) {
+  hipLaunchKernelGGL((bwd_state_kernel<DK, DV>), dim3(state_slots<DV / 16>(a.nq)), dim3(512), 0, st, a);
   return hipGetLastError();
 }
 
@@ -617,18 +670,14 @@ hipError_t launch_bwd_intra(const BwdChunkArgs<TIn>& a, int B, hipStream_t st) {
   return hipGetLastError();
 }
 
-#define GDR2_INST_BWD(DK, DV, TIN)                                                                \
-  template hipError_t launch_bwd_state<DK, DV, TIN>(const BwdStateArgs<TIN>&, int, hipStream_t); \
-  template hipError_t launch_bwd_wy<DK, DV, TIN>(const BwdChunkArgs<TIN>&, int, hipStream_t);    \
-  template hipError_t launch_bwd_intra<DK, DV, TIN>(const BwdChunkArgs<TIN>&, int, hipStream_t);
+#define GDR2_INST_BWD(DK, DV)                                                                     \
+  template hipError_t launch_bwd_state<DK, DV>(const BwdStateArgs<float>&, hipStream_t);          \
+  template hipError_t launch_bwd_wy<DK, DV, float>(const BwdChunkArgs<float>&, int, hipStream_t); \
+  template hipError_t launch_bwd_intra<DK, DV, float>(const BwdChunkArgs<float>&, int, hipStream_t);
 
-GDR2_INST_BWD(64, 64, float)
-GDR2_INST_BWD(64, 128, float)
-GDR2_INST_BWD(128, 64, float)
-GDR2_INST_BWD(128, 128, float)
-GDR2_INST_BWD(64, 64, bf16_t)
-GDR2_INST_BWD(64, 128, bf16_t)
-GDR2_INST_BWD(128, 64, bf16_t)
-GDR2_INST_BWD(128, 128, bf16_t)
+GDR2_INST_BWD(64, 64)
+GDR2_INST_BWD(64, 128)
+GDR2_INST_BWD(128, 64)
+GDR2_INST_BWD(128, 128)
 
 }  // namespace gdr2

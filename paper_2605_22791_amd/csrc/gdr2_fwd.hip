@@ -13,6 +13,8 @@
 
 #include "gdr2_kernels.hpp"
 
+#include <type_traits>
+
 namespace gdr2 {
 
 // ---------------------------------------------------------------------------
@@ -173,161 +175,172 @@ __global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
 }
 
 // ---------------------------------------------------------------------------
-// fwd_state: S (DK x DVS slice, fp32, LDS) carried across chunks.  Per chunk:
+// fwd_state: S carried across chunks, one workgroup per (sequence, head) and
+// 16-column slice of the values.  Per chunk:
 //   R   = U - Y S                         (eq. eq_app_residual_matrix)
 //   O   = scale * (Qg S + Aqk R)          (eq. eq_app_chunk_output)  [WITH_O]
 //   S  <- Diag(gamma_C) S + Ktail^T R     (eq. eq_app_chunk_state)
 // With STORE_H the chunk-start states h_n and R are kept for the backward.
-template <int DK, int DV, int DVS, typename TIn, bool WITH_O, bool STORE_H>
-__global__ __launch_bounds__(256) void fwd_state_kernel(StateArgs<TIn> a) {
-  constexpr int NTHR = 256, NW = 4;
-  constexpr int LSS = DVS + 4;
-  constexpr int NVB = DVS / 16;
-  const int vs = blockIdx.x, h = blockIdx.y, bb = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int T = a.T, H = a.H, NT = a.NT;
-  const int v0 = vs * DVS;
-  const size_t seq = (size_t)scan_pair(a.vl, bb * H + h, H);  // (sequence, head) pair
-  const ScanRange rng = scan_range(a.vl, (int)seq, H, NT);
+//
+// A chunk is a serial chain and few sequences leave most of the chip idle, so
+// what counts is the chain's length: narrow slices (a product is 32 fp32 MFMAs
+// deep at most), waves 0-3 forming R while waves 4-7 form Qg S, one 16 x 16 tile
+// of S per wave kept in its registers, two barriers a chunk, and every operand
+// loaded straight into the registers of the wave that multiplies it two chunks
+// ahead.  S and R meet the other waves through LDS transposed ([v][c], [v][r]),
+// so that four K-steps' values are one 16-byte access without bank conflicts.
+// 8 sequences x 16 chunks at 128 x 128: 59 us, without the output 40 (32 columns
+// a workgroup, four waves, operands loaded where they are used: 160 and 110; the
+// two roles in one body, whose waits then counted the barer role: 95 and 45).
+// The slices of a sequence share their XCD (state_slot), hence its L2.
+template <int DK, int DV, bool WITH_O, bool STORE_H>
+__global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
+  constexpr int NCB = DK / 16;      // key blocks: S tiles, one per wave
+  constexpr int LT = DK + 4, LR = CH + 4;
+  int q, vs;
+  if (!state_slot<DV / 16>(blockIdx.x, a.nq, q, vs)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4, v0 = 16 * vs + lr;
+  const size_t seq = (size_t)scan_pair(a.vl, q, a.H);  // (sequence, head) pair
+  const int h = (int)(seq % a.H);
+  const ScanRange rng = scan_range(a.vl, (int)seq, a.H, a.NT);
+  const bool low = wave < 4, own = NCB == 8 || low;
+  const int i = wave & 3, cb = own ? wave : 0;  // row block of the products; key block of the S tile
 
-  __shared__ float sS[DK * LSS];
-  __shared__ float sR[CH * LSS];
+  __shared__ __align__(16) float sS[16 * LT];  // [v][c]
+  __shared__ __align__(16) float sR[16 * LR];  // [v][r]
 
-  for (int e = tid; e < DK * DVS; e += NTHR) {
-    const int c = e / DVS, v = e % DVS;
-    sS[c * LSS + v] = a.S0 ? a.S0[(seq * DK + c) * DV + v0 + v] : 0.f;
-  }
-  __syncthreads();
-
-  const int lr = lane & 15, lg = lane >> 4;
-  for (int n = rng.c0; n < rng.c1; ++n) {
-    const size_t ch = rng.chs + n;
-    const float* Y = a.Y + ch * CH * DK;
-    const float* U = a.U + ch * CH * DV;
-    const float* Kt = a.Kt + ch * CH * DK;
-    const float* GC = a.GC + ch * DK;
-
-    if (STORE_H) {
-      float* Hn = a.Hs + ch * DK * DV;
-      for (int e = tid; e < DK * DVS; e += NTHR) {
-        const int c = e / DVS, v = e % DVS;
-        Hn[c * DV + v0 + v] = sS[c * LSS + v];
-      }
-    }
-    // R = U - Y S : wave -> row block, all value tiles of the slice
-    {
-      const int i = wave;
-      f4 acc[NVB];
+  f4 st = f4{0.f, 0.f, 0.f, 0.f};  // S[16 cb + 4 lg + u][v0]
+  const size_t so = (seq * DK + 16 * cb + 4 * lg) * DV + v0;
+  if (own) {
+    if (a.S0 != nullptr) {
 #pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
+      for (int u = 0; u < 4; ++u) st[u] = a.S0[so + (size_t)u * DV];
+    }
+    *reinterpret_cast<f4*>(sS + lr * LT + 16 * cb + 4 * lg) = st;
+  }
+
+  // the two roles as code of their own: on each the same loads and stores go out
+  // every chunk, so that a wait for one chunk's operands leaves the rest in flight
+  const auto run = [&](auto LOWC) {
+    constexpr bool LOW = decltype(LOWC)::value, OWN = NCB == 8 || LOW;
+    struct Ops {
+      float4 p[DK / 16];  // row 16 i + lr of Y (waves 0-3) or Qg, channels 16 j + 4 lg ..
+      float4 x[4];        // waves 4-7: Aqk row 16 i + lr, keys 16 j + 4 lg ..; waves 0-3: x[0] = U's tile
+      float k[4][4];      // Ktail[16 j + 4 lg + t][16 cb + lr]
+      float4 g;           // gamma_C of channels 16 cb + 4 lg ..
+    };
+    const auto load = [&](Ops& o, int n) {
+      const size_t ch = rng.chs + min(n, rng.c1 - 1);  // past the end: the last chunk again, unused
+      const float* P = (LOW ? a.Y : a.Qg) + (ch * CH + 16 * i + lr) * DK + 4 * lg;
+      if (LOW || WITH_O) {
+#pragma unroll
+        for (int j = 0; j < DK / 16; ++j) o.p[j] = ld4(P + 16 * j);
+      }
+      if (LOW) {
+        const float* U = a.U + (ch * CH + 16 * i + 4 * lg) * DV + v0;
+        o.x[0] = make_float4(U[0], U[DV], U[2 * DV], U[3 * DV]);
+      } else if (WITH_O) {
+        const float* A = a.Aqk + (ch * CH + 16 * i + lr) * CH + 4 * lg;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o.x[j] = ld4(A + 16 * min(j, i));
+      }
+      if (OWN) {
+        const float* K = a.Kt + (ch * CH + 4 * lg) * DK + 16 * cb + lr;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) o.k[j][t] = K[(16 * j + t) * DK];
+        o.g = ld4(a.GC + ch * DK + 16 * cb + 4 * lg);
+      }
+    };
+    const auto step = [&](Ops& o, int n) {
+      const size_t ch = rng.chs + n;
+      if (STORE_H && OWN) {
+        float* Hn = a.Hs + (ch * DK + 16 * cb + 4 * lg) * DV + v0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) Hn[u * DV] = st[u];
+      }
+      // Y S (waves 0-3), Qg S (waves 4-7): two accumulators, so that a product does not wait for the one before
+      f4 acc = f4{0.f, 0.f, 0.f, 0.f}, ac2 = acc;
+      if (LOW || WITH_O) {
+#pragma unroll
+        for (int j = 0; j < DK / 16; ++j) {
+          const float4 y = o.p[j], s = ld4(sS + lr * LT + 16 * j + 4 * lg);
+          acc = mfma4(y.x, s.x, acc);
+          ac2 = mfma4(y.y, s.y, ac2);
+          acc = mfma4(y.z, s.z, acc);
+          ac2 = mfma4(y.w, s.w, ac2);
+        }
+      }
+      acc += ac2;
+      if (LOW) {
+        const f4 R = f4{o.x[0].x, o.x[0].y, o.x[0].z, o.x[0].w} - acc;
+        *reinterpret_cast<f4*>(sR + lr * LR + 16 * i + 4 * lg) = R;
+        if (STORE_H) {
+          float* Rn = a.Rs + (ch * CH + 16 * i + 4 * lg) * DV + v0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) Rn[u * DV] = R[u];
+        }
+      }
+      __syncthreads();  // R is there, and nobody reads this chunk's S any more
+      float4 r[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = ld4(sR + lr * LR + 16 * j + 4 * lg);
+      if (OWN) {
+        st = f4{o.g.x * st[0], o.g.y * st[1], o.g.z * st[2], o.g.w * st[3]};
+        f4 s2 = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          st = mfma4(o.k[j][0], r[j].x, st);
+          s2 = mfma4(o.k[j][1], r[j].y, s2);
+          st = mfma4(o.k[j][2], r[j].z, st);
+          s2 = mfma4(o.k[j][3], r[j].w, s2);
+        }
+        st += s2;
+        *reinterpret_cast<f4*>(sS + lr * LT + 16 * cb + 4 * lg) = st;
+      }
+      if (WITH_O && !LOW) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (j > i) break;
+          acc = mfma4(o.x[j].x, r[j].x, acc);
+          acc = mfma4(o.x[j].y, r[j].y, acc);
+          acc = mfma4(o.x[j].z, r[j].z, acc);
+          acc = mfma4(o.x[j].w, r[j].w, acc);
+        }
+        size_t row0;
+        int len;
+        scan_rows(a.vl, (int)seq, a.H, a.T, n, row0, len);
+        // rows past the chunk's end go over U's, which nobody reads any more: a
+        // store on every path (waits count stores too)
+        float* O = a.o + ((row0 + 16 * i + 4 * lg) * a.H + h) * DV + v0;
+        float* X = const_cast<float*>(a.U) + (ch * CH + 16 * i + 4 * lg) * DV + v0;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          acc[vb][u] = U[(16 * i + 4 * lg + u) * DV + v0 + 16 * vb + lr];
-      const float* py = Y + (16 * i + lr) * DK + 4 * lg;
-      for (int kk = 0; kk < DK; kk += 16) {
-        const float4 y = ld4(py + kk);
-        const int c0 = kk + 4 * lg;
-#pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) {
-          acc[vb] = mfma4(-y.x, sS[(c0 + 0) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(-y.y, sS[(c0 + 1) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(-y.z, sS[(c0 + 2) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(-y.w, sS[(c0 + 3) * LSS + 16 * vb + lr], acc[vb]);
-        }
+          *(16 * i + 4 * lg + u < len ? O + (size_t)u * a.H * DV : X + u * DV) = a.scale * acc[u];
       }
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int r = 16 * i + 4 * lg + u;
-          sR[r * LSS + 16 * vb + lr] = acc[vb][u];
-          if (STORE_H) a.Rs[ch * CH * DV + r * DV + v0 + 16 * vb + lr] = acc[vb][u];
-        }
-    }
-    __syncthreads();
-
-    if (WITH_O) {
-      const float* Qg = a.Qg + ch * CH * DK;
-      const float* Aqk = a.Aqk + ch * CH * CH;
-      const int i = wave;
-      f4 acc[NVB];
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb) acc[vb] = f4{0.f, 0.f, 0.f, 0.f};
-      const float* pq = Qg + (16 * i + lr) * DK + 4 * lg;
-      for (int kk = 0; kk < DK; kk += 16) {
-        const float4 qv = ld4(pq + kk);
-        const int c0 = kk + 4 * lg;
-#pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) {
-          acc[vb] = mfma4(qv.x, sS[(c0 + 0) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(qv.y, sS[(c0 + 1) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(qv.z, sS[(c0 + 2) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(qv.w, sS[(c0 + 3) * LSS + 16 * vb + lr], acc[vb]);
-        }
-      }
-      const float* pa = Aqk + (16 * i + lr) * CH + 4 * lg;
-      for (int kb = 0; kb <= i; ++kb) {
-        const float4 av = ld4(pa + 16 * kb);
-        const int s0 = 16 * kb + 4 * lg;
-#pragma unroll
-        for (int vb = 0; vb < NVB; ++vb) {
-          acc[vb] = mfma4(av.x, sR[(s0 + 0) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(av.y, sR[(s0 + 1) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(av.z, sR[(s0 + 2) * LSS + 16 * vb + lr], acc[vb]);
-          acc[vb] = mfma4(av.w, sR[(s0 + 3) * LSS + 16 * vb + lr], acc[vb]);
-        }
-      }
-      size_t orow0;
-      int olen;
-      scan_rows(a.vl, (int)seq, H, T, n, orow0, olen);
-#pragma unroll
-      for (int vb = 0; vb < NVB; ++vb)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int r = 16 * i + 4 * lg + u;
-          if (r < olen) put(a.o + ((orow0 + r) * H + h) * DV + v0 + 16 * vb + lr, a.scale * acc[vb][u]);
-        }
-    }
-
-    // S <- Diag(gamma_C) S + Ktail^T R : tiles over (key block, value block)
-    constexpr int NTILE = (DK / 16) * NVB;
-    constexpr int TPW = (NTILE + NW - 1) / NW;
-    f4 nacc[TPW];
-#pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      const int t = wave + q * NW;
-      if (t < NTILE) {
-        const int cb = t / NVB, vb = t % NVB;
-        f4 acc;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int c = 16 * cb + 4 * lg + u;
-          acc[u] = GC[c] * sS[c * LSS + 16 * vb + lr];
-        }
-        for (int kk = 0; kk < CH; kk += 4) {
-          const int r = kk + lg;
-          acc = mfma4(Kt[r * DK + 16 * cb + lr], sR[r * LSS + 16 * vb + lr], acc);
-        }
-        nacc[q] = acc;
+      load(o, n + 2);
+      __syncthreads();
+    };
+    if (rng.c0 < rng.c1) {
+      Ops oa, ob;
+      load(oa, rng.c0);
+      load(ob, rng.c0 + 1);
+      __syncthreads();
+      for (int n = rng.c0; n < rng.c1; n += 2) {
+        step(oa, n);
+        if (n + 1 < rng.c1) step(ob, n + 1);
       }
     }
-    __syncthreads();
+  };
+  if (low)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
+  if (a.ST != nullptr && own) {
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      const int t = wave + q * NW;
-      if (t < NTILE) {
-        const int cb = t / NVB, vb = t % NVB;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) sS[(16 * cb + 4 * lg + u) * LSS + 16 * vb + lr] = nacc[q][u];
-      }
-    }
-    __syncthreads();
-  }
-  if (a.ST) {
-    for (int e = tid; e < DK * DVS; e += NTHR) {
-      const int c = e / DVS, v = e % DVS;
-      a.ST[(seq * DK + c) * DV + v0 + v] = sS[c * LSS + v];
-    }
+    for (int u = 0; u < 4; ++u) a.ST[so + (size_t)u * DV] = st[u];
   }
 }
 
@@ -346,30 +359,21 @@ hipError_t launch_fwd_intra(const IntraArgs<TIn>& a, int B, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int DK, int DV, typename TIn, bool WITH_O, bool STORE_H>
-hipError_t launch_fwd_state(const StateArgs<TIn>& a, int B, hipStream_t st) {
-  constexpr int DVS = 32;
-  dim3 grid(DV / DVS, a.H, B);
-  hipLaunchKernelGGL((fwd_state_kernel<DK, DV, DVS, TIn, WITH_O, STORE_H>), grid, dim3(256), 0, st, a);
+template <int DK, int DV, bool WITH_O, bool STORE_H>
+hipError_t launch_fwd_state(const StateArgs<float>& a, hipStream_t st) {
+  hipLaunchKernelGGL((fwd_state_kernel<DK, DV, WITH_O, STORE_H>), dim3(state_slots<DV / 16>(a.nq)), dim3(512), 0, st, a);
   return hipGetLastError();
 }
 
-#define GDR2_INST_FWD(DK, DV, TIN)                                                          \
-  template hipError_t launch_fwd_intra<DK, DV, TIN>(const IntraArgs<TIN>&, int, hipStream_t); \
-  template hipError_t launch_fwd_state<DK, DV, TIN, true, false>(const StateArgs<TIN>&, int,  \
-                                                                 hipStream_t);               \
-  template hipError_t launch_fwd_state<DK, DV, TIN, false, true>(const StateArgs<TIN>&, int,  \
-                                                                 hipStream_t);               \
-  template hipError_t launch_fwd_state<DK, DV, TIN, true, true>(const StateArgs<TIN>&, int,   \
-                                                                hipStream_t);
+#define GDR2_INST_FWD(DK, DV)                                                                \
+  template hipError_t launch_fwd_intra<DK, DV, float>(const IntraArgs<float>&, int, hipStream_t); \
+  template hipError_t launch_fwd_state<DK, DV, true, false>(const StateArgs<float>&, hipStream_t); \
+  template hipError_t launch_fwd_state<DK, DV, false, true>(const StateArgs<float>&, hipStream_t); \
+  template hipError_t launch_fwd_state<DK, DV, true, true>(const StateArgs<float>&, hipStream_t);
 
-GDR2_INST_FWD(64, 64, float)
-GDR2_INST_FWD(64, 128, float)
-GDR2_INST_FWD(128, 64, float)
-GDR2_INST_FWD(128, 128, float)
-GDR2_INST_FWD(64, 64, bf16_t)
-GDR2_INST_FWD(64, 128, bf16_t)
-GDR2_INST_FWD(128, 64, bf16_t)
-GDR2_INST_FWD(128, 128, bf16_t)
+GDR2_INST_FWD(64, 64)
+GDR2_INST_FWD(64, 128)
+GDR2_INST_FWD(128, 64)
+GDR2_INST_FWD(128, 128)
 
 }  // namespace gdr2

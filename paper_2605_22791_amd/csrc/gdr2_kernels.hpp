@@ -99,6 +99,20 @@ __device__ __forceinline__ void scan_rows(const Varlen& vl, int q, int H, int T,
   }
 }
 
+// Workgroup x of the fp32 state kernels: slice vs (of NS) of scanned pair q; false
+// past the nq pairs.  Workgroups go to the eight XCDs in turn, so x % 8 picks
+// the pair and x / 8 the slice: a pair's slices read the same tiles from one L2.
+template <int NS>
+__device__ __forceinline__ bool state_slot(int x, int nq, int& q, int& vs) {
+  q = x / (8 * NS) * 8 + x % 8;
+  vs = x / 8 % NS;
+  return q < nq;
+}
+template <int NS>
+unsigned state_slots(int nq) {
+  return (unsigned)((nq + 7) / 8 * 8) * NS;
+}
+
 // Fused input stage (App. C.1, App. D.2), active when a_log is set: q and k
 // are the raw projections and are L2-normalised per (token, key head) on load,
 // y = x (sum x^2 + eps)^(-1/2), rounded to bf16 as the operands of the bf16
@@ -152,6 +166,7 @@ struct StateArgs {
   float* Rs;        // R per chunk (backward recompute)
   int T, H, NT;
   float scale;
+  int nq;           // scanned (sequence, head) pairs
   Varlen vl{};
 };
 
@@ -170,6 +185,7 @@ struct BwdStateArgs {
   float* DR;         // dR per chunk
   int T, H, NT;
   float scale;
+  int nq;            // scanned (sequence, head) pairs
   Varlen vl{};
 };
 
@@ -433,10 +449,10 @@ hipError_t launch_segcombine(const SegCombineArgs& a, hipStream_t st);
 
 template <int DK, int DV, typename TIn>
 hipError_t launch_fwd_intra(const IntraArgs<TIn>& a, int B, hipStream_t st);
-template <int DK, int DV, typename TIn, bool WITH_O, bool STORE_H>
-hipError_t launch_fwd_state(const StateArgs<TIn>& a, int B, hipStream_t st);
-template <int DK, int DV, typename TIn>
-hipError_t launch_bwd_state(const BwdStateArgs<TIn>& a, int B, hipStream_t st);
+template <int DK, int DV, bool WITH_O, bool STORE_H>
+hipError_t launch_fwd_state(const StateArgs<float>& a, hipStream_t st);
+template <int DK, int DV>
+hipError_t launch_bwd_state(const BwdStateArgs<float>& a, hipStream_t st);
 template <int DK, int DV, typename TIn>
 hipError_t launch_bwd_wy(const BwdChunkArgs<TIn>& a, int B, hipStream_t st);
 template <int DK, int DV, typename TIn>

@@ -510,3 +510,26 @@ def test_scalarized_gate_modes(mode, dtype):
     floor = rel_l2(rnd(ref[gn].astype(np.float32)).sum(-1), ref[gn].sum(-1)) if dtype == "bf16" else 0.0
     print(f"scalar-gate gradient {e_g:.2e} (rounding floor {floor:.2e})")
     assert e_g < np.hypot(floor, TOL[dtype] if dtype == "fp32" else 1.2e-3), (e_g, floor)
+
+
+@pytest.mark.parametrize("B,H,T,Dk,Dv", [(1, 1, 1, 128, 128), (1, 1, 64, 64, 128), (1, 9, 65, 128, 64),
+                                         (3, 3, 128, 64, 64), (1, 8, 191, 128, 128), (2, 5, 260, 64, 128)])
+@pytest.mark.parametrize("save", [False, True])
+def test_fp32_state_kernels(B, H, T, Dk, Dv, save):
+    """The fp32 state scans at one to five chunks (they run two a trip), whole and partial last
+    chunks, and numbers of (sequence, head) pairs around a multiple of eight (their XCD order)."""
+    import torch
+    import paper_2605_22791_amd as g2
+    from oracle import gdr2_recurrent_fwd
+    d = make_inputs(B, T, H, Dk, Dv, seed=400 + T, dtype="fp32", s0_std=0.1, with_dST=True)
+    _case(f"fp32 states B{B} H{H} T{T} Dk{Dk} Dv{Dv} save={save}")
+    x = dev_inputs(d)
+    args = [x[n] for n in ("q", "k", "v", "log_alpha", "b", "w")]
+    need = g2.gdr2_chunk_workspace_bytes(g2._problem(x["q"], x["v"], d["scale"]), 1)
+    # what lies in the workspace beforehand reaches no result
+    ws = torch.full(((need + 3) // 4,), float("nan"), device="cuda").view(torch.uint8)
+    o, ST = g2.gdr2_chunk_fwd(*args, x["S0"], scale=d["scale"], ws=ws, save=save)
+    g = g2.gdr2_chunk_bwd(*args, x["S0"], x["do"], x["dST"], scale=d["scale"], ws=ws, saved=save)
+    o_ref, S_ref = gdr2_recurrent_fwd(d["q"], d["k"], d["v"], d["log_alpha"], d["b"], d["w"], d["S0"], d["scale"])
+    assert rel_l2(host(o), o_ref) < TOL["fp32"] and rel_l2(host(ST), S_ref) < TOL["fp32"]
+    _compare({n: host(t) for n, t in g.items()}, _adjoint(d), TOL["fp32"])
