@@ -78,6 +78,13 @@ struct Layout {
   size_t total;
 };
 
+// Sequences of fewer chunks than this are scanned whole, in narrow slices
+// (narrow_scan): two passes over the segments and the chain between cost more than
+// one walk of 1.8 us a chunk.  One sequence, 16 heads, 128 x 128, whole / segmented:
+// 16 chunks 52 / 94 us forward, 156 / 230 training; 32 chunks 88 / 114, 263 / 276;
+// 64 chunks 188 / 194, 506 / 476.
+constexpr int kSegmentChunks = 48;
+
 constexpr int kParamSplits = 64;  // slot ranges of the first decay-parameter reduction pass
 
 // Sequence-parallel scans (bf16 path).  The state scans run one workgroup per
@@ -88,7 +95,8 @@ constexpr int kParamSplits = 64;  // slot ranges of the first decay-parameter re
 // are doubled while the scan grid stays within one workgroup per compute unit
 // and a segment keeps at least 8 chunks.  The rule depends on the problem's
 // shape alone, so a problem always runs the same schedule (and rounds the same
-// way).
+// way).  The workspace has the segments' regions from 16 chunks on; kSegmentChunks
+// says from where they are used.
 void scan_segments(const gdr2_problem* p, int& nseg, int& seg_len) {
   const int NT = chunks_per_seq(p);
   const long long slices = (long long)p->B * p->H * (p->Dv / 64);
@@ -254,6 +262,7 @@ Geo make_geo(const gdr2_problem* p, bool bwd, int nseq, const int* cu, void* ws,
   Geo G{};
   G.G = grp;
   G.L = layout(p, bwd, nseq, grp, stage != nullptr);
+  if (nseq == 0 && chunks_per_seq(p) < kSegmentChunks) G.L.nseg = 1;
   if (stage != nullptr) {
     G.st.a_log = stage->a_log;
     G.st.delta = stage->delta;
@@ -447,8 +456,8 @@ hipError_t scan_fwd_bf16(const ScanArgs& sa, const Layout& L, void* ws, Last&& l
 // forward phase of this backward (or the saving forward) left in sM: the map
 // pass of the reverse scan is then skipped.
 template <int DK, int DV>
-hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, hipStream_t st) {
-  if (L.nseg == 1) return launch_bscan_bf16<DK, DV>(ba, st);
+hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, bool narrow, hipStream_t st) {
+  if (L.nseg == 1) return launch_bscan_bf16<DK, DV>(ba, narrow, st);
   BScanArgs pn = ba;
   pn.dST = nullptr;
   pn.dS0 = nullptr;
@@ -457,14 +466,14 @@ hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, hipStre
   pn.nseg = L.nseg;
   pn.seg_len = L.seg_len;
   pn.dSseg_out = at<float>(ws, L.sN);
-  hipError_t e = launch_bscan_bf16<DK, DV>(pn, st);
+  hipError_t e = launch_bscan_bf16<DK, DV>(pn, false, st);
   if (e != hipSuccess) return e;
   if constexpr (DK != DV) {
     BScanArgs pm = pn;
     pm.dout = nullptr;
     pm.flags = kScanNoInput | kScanEye;
     pm.dSseg_out = at<float>(ws, L.sM);
-    e = launch_bscan_bf16<DK, DK>(pm, st);
+    e = launch_bscan_bf16<DK, DK>(pm, false, st);
     if (e != hipSuccess) return e;
   }
   SegCombineArgs ca{at<float>(ws, L.sM), at<float>(ws, L.sN), ba.dST, at<float>(ws, L.sX),
@@ -476,7 +485,23 @@ hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, hipStre
   p3.nseg = L.nseg;
   p3.seg_len = L.seg_len;
   p3.dSseg_in = at<float>(ws, L.sX);
-  return launch_bscan_bf16<DK, DV>(p3, st);
+  return launch_bscan_bf16<DK, DV>(p3, false, st);
+}
+
+// Whether the state scans take 32-wide value slices (gdr2_nscan_bf16.hip, and the
+// reverse scan's narrow instance): when the 64-wide ones are at most half the
+// CUs.  4 x 16 (sequence, head) pairs of 2048 tokens, 128 wide scans: 207 us
+// forward narrow, 235 wide; 96 pairs, 192 wide scans: 363 and 288.  The sequences
+// of a packed batch differ in length, which the host does not know, and the
+// longest one's walk often sets the time (9 prompts of 37 to 3000 tokens x 16 heads:
+// 265 narrow, 317 wide; 4096 tokens and three of 64: 207 and 326): up to 512 wide
+// scans, as long as they are no more than 32 chunks for each CU (16 equal
+// sequences of 512, 16 chunks a CU: 228 and 202; the long packed training batch,
+// 64 a CU: 2065 and 1905).
+bool narrow_scan(const gdr2_problem* p, const Geo& G) {
+  if (G.L.nseg > 1) return false;
+  const long long per_seq = (long long)p->H * (p->Dv / 64), wide = G.nscan * per_seq;
+  return wide <= 128 || (G.vl.cu != nullptr && wide <= 512 && G.NT * per_seq <= 32 * 256);
 }
 
 // ---- dispatch over (Dk, Dv) ------------------------------------------------
@@ -519,6 +544,8 @@ struct FwdRun {
       sa.G = G.G;
       return timed(GDR2_K_FWD_STATE, st, [&] {
         return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& x) {
+          if (narrow_scan(p, G))
+            return save ? launch_nscan_bf16<DK, DV, true, true>(x, st) : launch_nscan_bf16<DK, DV, true, false>(x, st);
           return save ? launch_scan_bf16<DK, DV, true, true>(x, st) : launch_scan_bf16<DK, DV, true, false>(x, st);
         }, st);
       });
@@ -578,7 +605,8 @@ struct BwdRun {
         sa.G = G.G;
         e = timed(GDR2_K_BWD_RECOMPUTE_STATE, st, [&] {
           return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& x) {
-            return launch_scan_bf16<DK, DV, false, true>(x, st);
+            return narrow_scan(p, G) ? launch_nscan_bf16<DK, DV, false, true>(x, st)
+                                     : launch_scan_bf16<DK, DV, false, true>(x, st);
           }, st);
         });
         if (e != hipSuccess) return e;
@@ -588,7 +616,7 @@ struct BwdRun {
       ba.DHsc = at<float>(ws, L.DHsc);
       ba.vl = G.vl;
       ba.G = G.G;
-      e = timed(GDR2_K_BWD_STATE, st, [&] { return scan_bwd_bf16<DK, DV>(ba, L, ws, st); });
+      e = timed(GDR2_K_BWD_STATE, st, [&] { return scan_bwd_bf16<DK, DV>(ba, L, ws, narrow_scan(p, G), st); });
       if (e != hipSuccess) return e;
       // the WY VJP and the intra-chunk VJP in one chunk-parallel kernel
       BChunkBf16Args ca{static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),

@@ -29,10 +29,10 @@
 
 namespace gdr2 {
 
-template <int DK, int DV>
+template <int DK, int DV, int DVSL>
 struct BScanCfg {
   static constexpr int NTHR = 512;
-  static constexpr int DVS = DV < 64 ? DV : 64;
+  static constexpr int DVS = DVSL;  // value slice: 64, or 32 for few sequences
   static constexpr int NS = DV / DVS;
   static constexpr int KS = DK / 32, NCB = DK / 16, NVB = DVS / 16;
   static constexpr int TPW = NCB * NVB / 8;
@@ -51,15 +51,15 @@ struct BScanCfg {
   static constexpr int LDS = OFF_OP + SZ_OP;
   static_assert(SZ_Y % SLICE == 0 && SZ_Q % SLICE == 0 && SZ_A % SLICE == 0 && SZ_K % SLICE == 0,
                 "regions are whole staging slices");
-  static_assert(64 * DVS * 2 == SLICE, "one dO chunk per thread");
+  static_assert(64 * DVS * 2 <= SLICE, "at most one dO piece per thread");
   static_assert(LDS <= 160 * 1024, "LDS budget");
   static_assert(TPW >= 1 && NVB % 2 == 0, "wave split");
 };
 
 // STORE_D: the pass writes dh and dR (both set; the segment-map passes write neither)
-template <int DK, int DV, bool STORE_D>
+template <int DK, int DV, int DVSL, bool STORE_D>
 __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
-  using C = BScanCfg<DK, DV>;
+  using C = BScanCfg<DK, DV, DVSL>;
   constexpr int DVS = C::DVS, NS = C::NS, KS = C::KS, NCB = C::NCB, NVB = C::NVB, TPW = C::TPW;
   constexpr int LSD = C::LSD, LDR = C::LDR, LDO = C::LDO, NSTG = C::NSTG, SLICE = C::SLICE;
   constexpr int E_Y = C::SZ_Y / SLICE, E_Q = E_Y + C::SZ_Q / SLICE, E_A = E_Q + C::SZ_A / SLICE;
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
         if ((!no_input || m < E_Y || m >= E_A) && (m != E_Q || (tid & 128) == 0))                       \
           sts16(sOp + m * SLICE + 16 * tid, STG[m]);                                                   \
     const int r_ = tid / (DVS / 8), c8_ = (tid % (DVS / 8)) * 8;                                       \
-    sts16(sdO + r_ * LDO + c8_, STO);                                                                  \
+    if (64 * DVS * 2 == SLICE || r_ < 64) sts16(sdO + r_ * LDO + c8_, STO);                            \
     _Pragma("unroll") for (int u2 = 0; u2 < 4; ++u2) gcur[u2] = GN[u2];                                \
   }
 
@@ -399,26 +399,30 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
   }
 }
 
-template <int DK, int DV, bool STORE_D>
+template <int DK, int DV, int DVSL, bool STORE_D>
 hipError_t launch_bscan_bf16_t(const BScanArgs& a, hipStream_t st) {
-  using C = BScanCfg<DK, DV>;
-  const void* fn = reinterpret_cast<const void*>(&bscan_bf16_kernel<DK, DV, STORE_D>);
+  using C = BScanCfg<DK, DV, DVSL>;
+  const void* fn = reinterpret_cast<const void*>(&bscan_bf16_kernel<DK, DV, DVSL, STORE_D>);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
   if (e != hipSuccess) return e;
   dim3 grid(a.B * a.H * a.nseg * C::NS);
-  hipLaunchKernelGGL((bscan_bf16_kernel<DK, DV, STORE_D>), grid, dim3(C::NTHR), C::LDS, st, a);
+  hipLaunchKernelGGL((bscan_bf16_kernel<DK, DV, DVSL, STORE_D>), grid, dim3(C::NTHR), C::LDS, st, a);
   return hipGetLastError();
 }
 
 template <int DK, int DV>
-hipError_t launch_bscan_bf16(const BScanArgs& a, hipStream_t st) {
+hipError_t launch_bscan_bf16(const BScanArgs& a, bool narrow, hipStream_t st) {
   if ((a.DH == nullptr) != (a.DR == nullptr)) return hipErrorInvalidValue;  // both or neither
-  return a.DH ? launch_bscan_bf16_t<DK, DV, true>(a, st) : launch_bscan_bf16_t<DK, DV, false>(a, st);
+  // a wave's dS tiles form whole 16 x 32 blocks (one scale each) in 32-wide slices at Dk = 128 alone
+  if constexpr (DK == 128) {
+    if (narrow && a.DH) return launch_bscan_bf16_t<DK, DV, 32, true>(a, st);
+  }
+  return a.DH ? launch_bscan_bf16_t<DK, DV, 64, true>(a, st) : launch_bscan_bf16_t<DK, DV, 64, false>(a, st);
 }
 
-template hipError_t launch_bscan_bf16<64, 64>(const BScanArgs&, hipStream_t);
-template hipError_t launch_bscan_bf16<64, 128>(const BScanArgs&, hipStream_t);
-template hipError_t launch_bscan_bf16<128, 64>(const BScanArgs&, hipStream_t);
-template hipError_t launch_bscan_bf16<128, 128>(const BScanArgs&, hipStream_t);
+template hipError_t launch_bscan_bf16<64, 64>(const BScanArgs&, bool, hipStream_t);
+template hipError_t launch_bscan_bf16<64, 128>(const BScanArgs&, bool, hipStream_t);
+template hipError_t launch_bscan_bf16<128, 64>(const BScanArgs&, bool, hipStream_t);
+template hipError_t launch_bscan_bf16<128, 128>(const BScanArgs&, bool, hipStream_t);
 
 }  // namespace gdr2

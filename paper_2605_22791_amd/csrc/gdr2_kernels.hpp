@@ -435,9 +435,12 @@ struct BChunkBf16Args {
 template <int DK, int DV>
 hipError_t launch_intra_bf16(const IntraBf16Args& a, hipStream_t st);
 template <int DK, int DV>
-hipError_t launch_bscan_bf16(const BScanArgs& a, hipStream_t st);
+hipError_t launch_bscan_bf16(const BScanArgs& a, bool narrow, hipStream_t st);
 template <int DK, int DV, bool WITH_O, bool STORE_H>
 hipError_t launch_scan_bf16(const ScanArgs& a, hipStream_t st);
+// the same scan in 32-wide value slices, for few sequences (nseg = 1)
+template <int DK, int DV, bool WITH_O, bool STORE_H>
+hipError_t launch_nscan_bf16(const ScanArgs& a, hipStream_t st);
 // both segment maps of the sequence-parallel forward scan in one launch (Dk = Dv = D):
 // N into a.STseg, M into a.STseg_m
 template <int D>

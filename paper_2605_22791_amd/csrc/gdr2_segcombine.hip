@@ -14,105 +14,90 @@
 // its forward step, so the reverse chain of a square state can use the
 // forward's maps as M_k^T (transpose_m).
 //
-// One 4-wave workgroup per (sequence, 64-wide value slice).  X lives in fp32
-// MFMA accumulators and, for the product, as a split bf16 copy X^T in LDS;
-// M_k X is fp32-accurate (split hi/lo, three passes).
+// The chain is serial and short, so its length counts: one workgroup per
+// (sequence, 16-wide value slice) with a wave per key block of X, each wave's rows
+// of M_k and N_k loaded straight into its registers two links ahead, fp32 MFMA
+// (no splitting; 32 products deep at Dk = 128), X handed round through LDS with
+// one barrier a link.  The slices of a sequence share their XCD (state_slot).
+// 16 sequences x 8 segments at 128 x 128: 23 us (39 with split-bf16 products on
+// 64-wide slices and M_k loaded where it is used, 4.7 us a link).
 
 #include "gdr2_kernels.hpp"
-#include "gdr2_bf16.hpp"
 
 namespace gdr2 {
 
 template <int DK, int DV>
-__global__ __launch_bounds__(256) void segcombine_kernel(SegCombineArgs a) {
-  constexpr int DVS = 64, NCB = DK / 16, KS = DK / 32;
-  constexpr int CPW = NCB / 4;  // key blocks of X per wave
-  constexpr int LX = DK + 8;    // X^T hi / lo, bf16 [DVS][LX]
-  static_assert(NCB % 4 == 0 && DV % DVS == 0, "tiling");
-  __shared__ __align__(16) __bf16 sXh[DVS * LX];
-  __shared__ __align__(16) __bf16 sXl[DVS * LX];
+__global__ __launch_bounds__(4 * DK) void segcombine_kernel(SegCombineArgs a) {
+  constexpr int LX = DK + 4;
+  __shared__ __align__(16) float sX[2][16 * LX];  // X [v][c], by link parity
+  int seq, vs;
+  if (!state_slot<DV / 16>(blockIdx.x, a.nseq, seq, vs)) return;
+  const int lane = threadIdx.x & 63, cb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lg = lane >> 4, v0 = 16 * vs + lr, nseg = a.nseg;
+  const size_t o = (size_t)(16 * cb + 4 * lg) * DV + v0;  // the lane's X[16 cb + 4 lg + u][v0], u = 0
+  const auto seg = [&](int step) { return (size_t)seq * nseg + (a.reverse ? nseg - 1 - step : step); };
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, r16 = lane & 15;
-  const int seq = blockIdx.x, v0 = blockIdx.y * DVS;
-  const int nseg = a.nseg;
-
-  // lane holds X[c][v] for c = 16 cb + 4 g + u (cb = CPW * wave + c'), v = v0 + 16 vb + r16
-  f4 x[CPW][4];
+  struct Ops {
+    f4 m[DK / 16];  // M[16 cb + lr][16 j + 4 lg ..] (transposed: M[16 j + 4 lg ..][16 cb + lr])
+    f4 n;           // N's tile
+  };
+  const auto load = [&](Ops& x, int step) {
+    const size_t sk = seg(min(step, nseg - 1));  // past the end: unused
+    const float *M = a.M + sk * DK * DK, *N = a.N + sk * DK * DV + o;
+    if (a.transpose_m) {
 #pragma unroll
-  for (int cc = 0; cc < CPW; ++cc)
+      for (int j = 0; j < DK / 16; ++j)
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
+        for (int t = 0; t < 4; ++t) x.m[j][t] = M[(size_t)(16 * j + 4 * lg + t) * DK + 16 * cb + lr];
+    } else {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = 16 * (CPW * wave + cc) + 4 * g + u, v = v0 + 16 * vb + r16;
-        x[cc][vb][u] = a.X0 ? a.X0[((size_t)seq * DK + c) * DV + v] : 0.f;
-      }
-
-#pragma unroll 1
-  for (int step = 0; step < nseg; ++step) {
-    const int k = a.reverse ? nseg - 1 - step : step;
-    const size_t sk = (size_t)seq * nseg + k;
-    float* xs = a.Xs + sk * DK * DV;
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc)
-#pragma unroll
-      for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          xs[(size_t)(16 * (CPW * wave + cc) + 4 * g + u) * DV + v0 + 16 * vb + r16] = x[cc][vb][u];
-    if (step == nseg - 1) break;
-
-    __syncthreads();  // the previous step's readers of X^T are done
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc)
-#pragma unroll
-      for (int vb = 0; vb < 4; ++vb) {
-        const int off = (16 * vb + r16) * LX + 16 * (CPW * wave + cc) + 4 * g;
-        st4split(sXh + off, sXl + off, x[cc][vb]);
-      }
-    __syncthreads();
-
-    // X <- M_k X + N_k
-    const float* M = a.M + sk * DK * DK;
-    const float* N = a.N + sk * DK * DV;
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc)
-#pragma unroll
-      for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          x[cc][vb][u] = N[(size_t)(16 * (CPW * wave + cc) + 4 * g + u) * DV + v0 + 16 * vb + r16];
-#pragma unroll
-    for (int p = 0; p < KS; ++p) {
-      Fr xf[4];
-#pragma unroll
-      for (int vb = 0; vb < 4; ++vb) {
-        xf[vb].hi = ld8(sXh + (16 * vb + r16) * LX + 32 * p + 8 * g);
-        xf[vb].lo = ld8(sXl + (16 * vb + r16) * LX + 32 * p + 8 * g);
-      }
-#pragma unroll
-      for (int cc = 0; cc < CPW; ++cc) {
-        float m[8];
-        const int mr = 16 * (CPW * wave + cc) + r16, mc = 32 * p + 8 * g;
-        if (a.transpose_m) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) m[e] = M[(size_t)(mc + e) * DK + mr];
-        } else {
-          ldf8(M + (size_t)mr * DK + mc, m);
-        }
-        const Fr mf = split8(m);
-#pragma unroll
-        for (int vb = 0; vb < 4; ++vb) x[cc][vb] = mma3(mf, xf[vb], x[cc][vb]);
-      }
+      for (int j = 0; j < DK / 16; ++j) x.m[j] = *reinterpret_cast<const f4*>(M + (16 * cb + lr) * DK + 16 * j + 4 * lg);
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x.n[u] = N[(size_t)u * DV];
+    asm volatile("" ::: "memory");  // the loads stay here: the compiler would sink them to their use
+  };
+  f4 x = f4{0.f, 0.f, 0.f, 0.f};
+  if (a.X0 != nullptr) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = a.X0[(size_t)seq * DK * DV + o + (size_t)u * DV];
   }
+  // the value entering segment `step`, then X <- M X + N
+  const auto link = [&](Ops& w, int step) {
+    float* xs = a.Xs + seg(step) * DK * DV + o;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) xs[(size_t)u * DV] = x[u];
+    float* X = sX[step & 1] + lr * LX;
+    *reinterpret_cast<f4*>(X + 16 * cb + 4 * lg) = x;
+    __syncthreads();  // (the readers of the link before last are done, or they had not met the last link's)
+    f4 x2 = f4{0.f, 0.f, 0.f, 0.f};
+    x = w.n;
+#pragma unroll
+    for (int j = 0; j < DK / 16; ++j) {
+      const f4 y = *reinterpret_cast<const f4*>(X + 16 * j + 4 * lg);
+      x = mfma4(w.m[j][0], y[0], x);
+      x2 = mfma4(w.m[j][1], y[1], x2);
+      x = mfma4(w.m[j][2], y[2], x);
+      x2 = mfma4(w.m[j][3], y[3], x2);
+    }
+    x += x2;
+    load(w, step + 2);
+  };
+  Ops oa, ob;
+  load(oa, 0);
+  load(ob, 1);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the loop's waits then count its own loads and stores alone
+  int step = 0;
+  for (; step + 1 < nseg; step += 2) {
+    link(oa, step);
+    link(ob, step + 1);
+  }
+  if (step < nseg) link(oa, step);
 }
 
 template <int DK, int DV>
 hipError_t launch_segcombine(const SegCombineArgs& a, hipStream_t st) {
-  dim3 grid(a.nseq, DV / 64);
-  hipLaunchKernelGGL((segcombine_kernel<DK, DV>), grid, dim3(256), 0, st, a);
+  hipLaunchKernelGGL((segcombine_kernel<DK, DV>), dim3(state_slots<DV / 16>(a.nseq)), dim3(4 * DK), 0, st, a);
   return hipGetLastError();
 }
 

@@ -149,3 +149,34 @@ def test_bf16_workspace_intermediates(Dk, Dv):
         assert worst[k_] < 1e-4, (k_, worst[k_])
     assert worst["U"] < 1e-5, worst["U"]   # about 3e-7
     assert worst["Y"] < 3e-3, worst["Y"]
+
+
+@pytest.mark.parametrize("T", [1, 64, 130, 200])
+@pytest.mark.parametrize("Dk,Dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_narrow_scans_equal_wide(Dk, Dv, T):
+    """A few heads alone (32-wide value slices) give the bits that the same heads give inside a
+    batch large enough for the 64-wide scans: one to four chunks, whole and partial last ones."""
+    import torch
+    import paper_2605_22791_amd as g2
+    B, H = 9, 16 * 128 // Dv   # 288 wide scans
+    d = make_inputs(B, T, H, Dk, Dv, seed=500 + T + Dk, dtype="bf16", decay_shift=-2.0, s0_std=0.05, with_dST=True)
+    _case(f"narrow against wide scans, Dk{Dk} Dv{Dv} T{T}")
+    x = dev_inputs(d)
+
+    def run(t, save):
+        args = [t[n] for n in ("q", "k", "v", "log_alpha", "b", "w")]
+        need = g2.gdr2_chunk_workspace_bytes(g2._problem(t["q"], t["v"], d["scale"]), 1)
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+        o, ST = g2.gdr2_chunk_fwd(*args, t["S0"], scale=d["scale"], ws=ws, save=save)
+        g = g2.gdr2_chunk_bwd(*args, t["S0"], t["do"], t["dST"], scale=d["scale"], ws=ws, saved=save)
+        return {"o": o, "S_T": ST, **g}
+
+    wide = run(x, True)
+    for h0, nh in ((0, 1), (3, 5)):   # one head; five (no multiple of the XCDs)
+        sub = {n: (t[2:3, :, h0:h0 + nh] if n not in ("S0", "dST") else t[2:3, h0:h0 + nh]).contiguous()
+               for n, t in x.items()}
+        for save in (True, False):
+            for n, t in run(sub, save).items():
+                w = wide[n]
+                w = w[2:3, h0:h0 + nh] if n in ("S_T", "dS0") else w[2:3, :, h0:h0 + nh]
+                assert torch.equal(t, w), (n, h0, save)

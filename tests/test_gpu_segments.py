@@ -103,3 +103,21 @@ def test_segmented_saved_path_and_chunk_states():
     for n in GRADS:
         assert np.array_equal(g_s[n], g_r[n]), n
     _check(d, o_s, S_s, g_s)
+
+
+@pytest.mark.parametrize("T,H", [(47 * 64 + 1, 2), (56 * 64, 3), (3072 - 64, 1)])
+def test_segment_use_bound(T, H):
+    """The shortest sequences that are cut into segments (48 chunks) and the longest that are not,
+    on the stored path, bit-identical to the recomputing one."""
+    import torch
+    import paper_2605_22791_amd as g2
+    d = make_inputs(1, T, H, 128, 128, seed=96 + H, dtype="bf16", decay_shift=-3.0, s0_std=0.05, with_dST=True)
+    x = dev_inputs(d)
+    nbytes = g2.gdr2_chunk_workspace_bytes(g2._problem(x["q"], x["v"], d["scale"]), 1)
+    _case(f"segments at their bound T{T} H{H}")
+    o, ST, g = _fwd_bwd(d, ws=torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda"), save=True)
+    o_r, S_r, g_r = _fwd_bwd(d)
+    assert np.array_equal(o, o_r) and np.array_equal(ST, S_r)
+    for n in GRADS:
+        assert np.array_equal(g[n], g_r[n]), n
+    _check(d, o, ST, g)
