@@ -21,6 +21,12 @@
 // and the dO rows come through a range-checked buffer load, so that every
 // path issues the same loads and stores.
 //
+// For few sequences (narrow_scan in gdr2_api.hip) the slices are 32 wide: half the
+// products and fragments a step, and with LDS room for a second dO the operands are
+// copied there beside the products that do not read them, two barriers a step
+// instead of three.  4 x 16 pairs of 4000 tokens at 128 x 128: 215 us, 275 with
+// 64-wide slices (231 with the three barriers); 64 x 128, 2048 tokens: 88, 105.
+//
 // Precision: every product is fp32-accurate (split hi/lo; dO and Y are exact
 // bf16 and keep a single part).
 
@@ -35,7 +41,10 @@ struct BScanCfg {
   static constexpr int DVS = DVSL;  // value slice: 64, or 32 for few sequences
   static constexpr int NS = DV / DVS;
   static constexpr int KS = DK / 32, NCB = DK / 16, NVB = DVS / 16;
-  static constexpr int TPW = NCB * NVB / 8;
+  // 32-wide slices (few sequences): a wave per key block has both its tiles, and
+  // the next chunk's operands go to LDS beside the products (see step)
+  static constexpr bool NAR = DVS == 32;
+  static constexpr int TPW = NAR ? NVB : NCB * NVB / 8;
   static constexpr int LSD = DK + 8;   // dS hi/lo [DVS][LSD]
   static constexpr int LDR = 64 + 8;   // dR hi/lo [DVS][LDR]
   static constexpr int LDO = DVS + 8;  // dO [64][LDO]
@@ -47,13 +56,13 @@ struct BScanCfg {
   static constexpr int OFF_D = 0;
   static constexpr int OFF_R = OFF_D + 2 * DVS * LSD * 2;
   static constexpr int OFF_O = OFF_R + 2 * DVS * LDR * 2;
-  static constexpr int OFF_OP = OFF_O + 64 * LDO * 2;
+  static constexpr int OFF_OP = OFF_O + (NAR ? 2 : 1) * 64 * LDO * 2;
   static constexpr int LDS = OFF_OP + SZ_OP;
   static_assert(SZ_Y % SLICE == 0 && SZ_Q % SLICE == 0 && SZ_A % SLICE == 0 && SZ_K % SLICE == 0,
                 "regions are whole staging slices");
   static_assert(64 * DVS * 2 <= SLICE, "at most one dO piece per thread");
   static_assert(LDS <= 160 * 1024, "LDS budget");
-  static_assert(TPW >= 1 && NVB % 2 == 0, "wave split");
+  static_assert(TPW >= 1 && NVB % 2 == 0 && TPW % 2 == 0, "wave split");
 };
 
 // STORE_D: the pass writes dh and dR (both set; the segment-map passes write neither)
@@ -69,7 +78,8 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
   __bf16* sDlo = sDhi + DVS * LSD;
   __bf16* sRhi = reinterpret_cast<__bf16*>(smem + C::OFF_R);
   __bf16* sRlo = sRhi + DVS * LDR;
-  __bf16* sdO = reinterpret_cast<__bf16*>(smem + C::OFF_O);
+  __bf16* const sdO0 = reinterpret_cast<__bf16*>(smem + C::OFF_O);
+  constexpr bool NAR = C::NAR;
   unsigned char* sOp = smem + C::OFF_OP;
   const unsigned char* sY = sOp;
   const unsigned char* sQ = sY + C::SZ_Y;
@@ -108,7 +118,8 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
   const int iO = wave >> 1;                // row block of the dR tiles
   const int vbO = (wave & 1) * (NVB / 2);  // their value blocks
   const int cs = wave % NCB;               // key block of the dS tiles
-  const int sv0 = (wave / NCB) * TPW;      // their value blocks
+  const int sv0 = NAR ? 0 : (wave / NCB) * TPW;  // their value blocks
+  const bool own = !NAR || NCB == 8 || wave < NCB;  // the wave has dS tiles
 
   // ---- staging: operand blocks, the dO slice and gamma_C of a chunk, in two
   // register buffers (A, B): a chunk's values are fetched over the step two
@@ -162,15 +173,20 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
     _Pragma("unroll") for (int u2 = 0; u2 < 4; ++u2) GN[u2] =                                          \
         a.GC[chx * (WsBf16::gc(DK) / 4) + 16 * cs + 4 * g + u2];                                       \
   }
-#define GDR2_STORE_CHUNK(STG, STO, GN)                                                                   \
+// slices [M0, M1) to LDS
+#define GDR2_STORE_OPS(STG, M0, M1)                                                                      \
+  _Pragma("unroll") for (int m = (M0); m < (M1); ++m)                                                  \
+      if ((!no_input || m < E_Y || m >= E_A) && (m != E_Q || (tid & 128) == 0))                         \
+        sts16(sOp + m * SLICE + 16 * tid, STG[m]);
+// dO (buffer SDO) and gamma_C
+#define GDR2_STORE_DOG(STO, GN, SDO)                                                                     \
   {                                                                                                    \
-    _Pragma("unroll") for (int m = 0; m < NSTG; ++m)                                                   \
-        if ((!no_input || m < E_Y || m >= E_A) && (m != E_Q || (tid & 128) == 0))                       \
-          sts16(sOp + m * SLICE + 16 * tid, STG[m]);                                                   \
     const int r_ = tid / (DVS / 8), c8_ = (tid % (DVS / 8)) * 8;                                       \
-    if (64 * DVS * 2 == SLICE || r_ < 64) sts16(sdO + r_ * LDO + c8_, STO);                            \
+    if (64 * DVS * 2 == SLICE || r_ < 64) sts16((SDO) + r_ * LDO + c8_, STO);                          \
     _Pragma("unroll") for (int u2 = 0; u2 < 4; ++u2) gcur[u2] = GN[u2];                                \
   }
+#define GDR2_SETTLE(STG, M0, M1)                                                                         \
+  _Pragma("unroll") for (int m = (M0); m < (M1); ++m) asm volatile("" : "+v"(STG[m])::"memory");
 
   // ---- dS: tiles (key block cs, value blocks sv0..) as fp32 accumulators, starting
   // from identity columns, the given segment end, dS_T (last segment) or zero
@@ -190,12 +206,15 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) sreg[t][u] = (eye && 16 * cs + 4 * g + u == v0 + 16 * (sv0 + t) + r16) ? 1.f : 0.f;
   }
+  const auto put_dS = [&] {
 #pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int vb = sv0 + t;
-    st4split(sDhi + (16 * vb + r16) * LSD + 16 * cs + 4 * g, sDlo + (16 * vb + r16) * LSD + 16 * cs + 4 * g,
-             sreg[t]);
-  }
+    for (int t = 0; t < TPW; ++t) {
+      const int vb = sv0 + t;
+      st4split(sDhi + (16 * vb + r16) * LSD + 16 * cs + 4 * g, sDlo + (16 * vb + r16) * LSD + 16 * cs + 4 * g,
+               sreg[t]);
+    }
+  };
+  if (own) put_dS();
   if (n0 < n1) {
     // the last chunk into B and the one before it (or the first chunk again,
     // unused) into A; B goes to LDS, and A is settled here so that the loop
@@ -203,9 +222,9 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
     // the loop give the buffers differ, and the loop top waits for stale loads)
     GDR2_LOAD_CHUNK(n1 - 1, stgB, stoB, gB)
     GDR2_LOAD_CHUNK(max(n1 - 2, n0), stgA, stoA, gA)
-    GDR2_STORE_CHUNK(stgB, stoB, gB)
-#pragma unroll
-    for (int m = 0; m < NSTG; ++m) asm volatile("" : "+v"(stgA[m])::"memory");
+    GDR2_STORE_OPS(stgB, NAR ? E_Q : 0, NSTG)  // (narrow: Y and Q_g follow at the top of the first step)
+    GDR2_STORE_DOG(stoB, gB, sdO0 + (NAR ? ((n1 - 1) & 1) * 64 * LDO : 0))
+    GDR2_SETTLE(stgA, 0, NSTG)
     asm volatile("" : "+v"(stoA)::"memory");
 #pragma unroll
     for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(gA[u])::"memory");
@@ -213,7 +232,11 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
   __syncthreads();
 
   // one step: chunk n is in LDS, chunk n - 1 in the buffer (cstg, csto, cg),
-  // chunk n - 2 is fetched into the other one (nstg, nsto, ng)
+  // chunk n - 2 is fetched into the other one (nstg, nsto, ng).  Narrow: a step has
+  // two barriers instead of three and no copy of its own.  Ktail, A_qk and dO of chunk
+  // n are in LDS, its Y and Q_g still in (nstg): they go there beside the dR products,
+  // which do not read them, and chunk n - 1's Ktail, A_qk and dO (two buffers) beside
+  // the dS products.
   auto step = [&](const int n, u4v(&cstg)[NSTG], u4v& csto, float(&cg)[4], u4v(&nstg)[NSTG], u4v& nsto,
                   float(&ng)[4]) {
     const size_t ch = chs + n;
@@ -224,13 +247,15 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
     // its products.  The last two steps load the first chunk again (unused),
     // so that the same loads are issued on every path
     const int nn = max(n - 2, n0);
+    __bf16* const sdO = sdO0 + (NAR ? (n & 1) * 64 * LDO : 0);
+    if constexpr (NAR) GDR2_STORE_OPS(nstg, 0, E_Q)
     GDR2_LOAD_OPS(nn, 0, 2, nstg)
     GDR2_LOAD_DOG(nn, nsto, ng)
 
     // scale exponents of the fp16 copy of dS, early in the step so that their
     // cross-lane reductions overlap the products below
     int dsh[TPW / 2];
-    if constexpr (STORE_D) state_shifts<TPW>(sreg, dsh);
+    if (STORE_D && own) state_shifts<TPW>(sreg, dsh);
 
     // ---- dR = scale * A_qk^T dO + Ktail dS   (tiles: row block iO, value blocks vbO..)
     f4 racc[NVB / 2], aacc[NVB / 2];
@@ -282,7 +307,7 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
     }
     GDR2_LOAD_OPS(nn, 6, 8, nstg)
     // gradient of this chunk's end state (sreg is not updated before the barrier below)
-    if constexpr (STORE_D) {
+    if (STORE_D && own) {
       const int col0 = v0 + 16 * sv0;
       store_state_f16<TPW>(sreg, dsh, a.DH + (ch * DK + 16 * cs) * DV + col0, DV,
                            a.DHsc + ch * (WsBf16::hsc(DK, DV) / 4) + cs * (DV / 32) + col0 / 32, lane);
@@ -301,6 +326,10 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
 
     // ---- dS <- Diag(gamma_C) dS + scale * Q_g^T dO - Y^T dR
     GDR2_LOAD_OPS(nn, 8, 10, nstg)
+    if constexpr (NAR) {
+      GDR2_SETTLE(cstg, E_Q, NSTG)
+      GDR2_STORE_OPS(cstg, E_Q, NSTG)
+    }
     f4 qacc[TPW];
 #pragma unroll
     for (int t = 0; t < TPW; ++t) qacc[t] = f4zero();
@@ -321,7 +350,7 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
         const __bf16* y0 = reinterpret_cast<const __bf16*>(sY + yoff);
         yf = neg8(ld_tr8p(y0, y0 + 32));
       }
-      if (!no_input) {
+      if (!no_input && own) {
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
           const int vb = sv0 + t;
@@ -336,6 +365,7 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
       }
 #pragma unroll
       for (int t = 0; t < TPW; ++t) {
+        if (!own) break;
         const int vb = sv0 + t;
         Fr rf;
         rf.hi = ld8(sRhi + (16 * vb + r16) * LDR + 32 * kb + 8 * g);
@@ -355,11 +385,14 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
     // now: settle them ahead of the dR stores, on every path, so that neither
     // their copy to LDS nor the reuse of their registers waits for those
     // stores (one vmcnt counts loads and stores in issue order)
-#pragma unroll
-    for (int m = 0; m < NSTG; ++m) asm volatile("" : "+v"(cstg[m])::"memory");
+    GDR2_SETTLE(cstg, 0, NSTG)
     asm volatile("" : "+v"(csto)::"memory");
 #pragma unroll
     for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(cg[u])::"memory");
+    if constexpr (NAR) {
+      if (own) put_dS();
+      GDR2_STORE_DOG(csto, cg, sdO0 + ((n & 1) ^ 1) * 64 * LDO)
+    }
     if constexpr (STORE_D) {
 #pragma unroll
       for (int t = 0; t < NVB / 2; ++t) {
@@ -368,15 +401,14 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
       }
     }
     __syncthreads();
-
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      const int vb = sv0 + t;
-      st4split(sDhi + (16 * vb + r16) * LSD + 16 * cs + 4 * g, sDlo + (16 * vb + r16) * LSD + 16 * cs + 4 * g,
-               sreg[t]);
+    if constexpr (!NAR) {
+      put_dS();
+      if (n > n0) {
+        GDR2_STORE_OPS(cstg, 0, NSTG)
+        GDR2_STORE_DOG(csto, cg, sdO0)
+      }
+      __syncthreads();
     }
-    if (n > n0) GDR2_STORE_CHUNK(cstg, csto, cg)
-    __syncthreads();
   };
   // two steps per trip, so that the buffers trade roles without copies
   for (int n = n1 - 1; n >= n0; n -= 2) {
@@ -386,11 +418,13 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
 #undef GDR2_LOAD_CHUNK
 #undef GDR2_LOAD_OPS
 #undef GDR2_LOAD_DOG
-#undef GDR2_STORE_CHUNK
+#undef GDR2_STORE_OPS
+#undef GDR2_STORE_DOG
+#undef GDR2_SETTLE
 
   float* dstart = a.dSseg_out ? a.dSseg_out + (size_t)vs * DK * DV
                               : ((a.dS0 && seg == 0) ? a.dS0 + (size_t)seq * DK * DV : nullptr);
-  if (dstart) {
+  if (dstart && own) {
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
 #pragma unroll
@@ -413,10 +447,7 @@ hipError_t launch_bscan_bf16_t(const BScanArgs& a, hipStream_t st) {
 template <int DK, int DV>
 hipError_t launch_bscan_bf16(const BScanArgs& a, bool narrow, hipStream_t st) {
   if ((a.DH == nullptr) != (a.DR == nullptr)) return hipErrorInvalidValue;  // both or neither
-  // a wave's dS tiles form whole 16 x 32 blocks (one scale each) in 32-wide slices at Dk = 128 alone
-  if constexpr (DK == 128) {
-    if (narrow && a.DH) return launch_bscan_bf16_t<DK, DV, 32, true>(a, st);
-  }
+  if (narrow && a.DH) return launch_bscan_bf16_t<DK, DV, 32, true>(a, st);
   return a.DH ? launch_bscan_bf16_t<DK, DV, 64, true>(a, st) : launch_bscan_bf16_t<DK, DV, 64, false>(a, st);
 }
 
