@@ -124,6 +124,18 @@ def test_fused_diagonal_block_bounds(Dk, per_token):
     _check(_run(d), _oracle(d), TOL["bf16"], names=("o", "S_T", "dq", "dk", "dv", "db", "dw", "dS0"))
 
 
+@pytest.mark.parametrize("per_token", [4.5, 5.1, 5.4])
+def test_fused_fp32_diagonal_block_bound(per_token):
+    """fp32: decay of some channels within a 16-row block below and above the bound of e^78."""
+    d = make_fused(1, 100, 2, 64, 128, seed=331, dtype="fp32", s0_std=0.05, with_dST=True)
+    d["a"] = np.zeros_like(d["a"])
+    f = np.full(d["f"].shape, -7.0, dtype=np.float32)
+    f[..., ::5] = per_token
+    d["f"], d["delta"] = f, np.zeros_like(d["delta"])
+    _case(f"fused fp32 B1 T100 H2, {per_token} a token on some channels")
+    _check(_run(d), _oracle(d), TOL["fp32"], names=("o", "S_T", "dq", "dk", "dv", "db", "dw", "dS0"))
+
+
 def test_fused_grouped_value_heads():
     d = make_fused(2, 130, 2, 128, 128, seed=312, Hv=4, s0_std=0.05, with_dST=True)
     _case("fused bf16 grouped H2 Hv4 B2 T130")
