@@ -401,10 +401,8 @@ hipError_t stage_bwd(const gdr2_problem* p, const Geo& G, void* ws, const void* 
   const int splits = nslots < kParamSplits ? nslots : kParamSplits;
   float* PT = at<float>(ws, L.PT);
   float* PT1 = PT + (size_t)kParamSplits * Hk * DK;
-  e = launch_param_reduce_pass(at<float>(ws, L.PD), PT, nslots, Hk, 4 * G.G, DK, splits, st);
-  if (e == hipSuccess) e = launch_param_reduce_pass(PT, ddelta, splits, Hk, 1, DK, 1, st);
-  if (e == hipSuccess) e = launch_param_reduce_pass(at<float>(ws, L.PA), PT1, nslots, Hk, 4 * G.G, 1, splits, st);
-  if (e == hipSuccess) e = launch_param_reduce_pass(PT1, da, splits, Hk, 1, 1, 1, st);
+  e = launch_param_reduce_pass({at<float>(ws, L.PD), PT, at<float>(ws, L.PA), PT1, nslots, Hk, 4 * G.G, DK}, splits, st);
+  if (e == hipSuccess) e = launch_param_reduce_pass({PT, ddelta, PT1, da, splits, Hk, 1, DK}, 1, st);
   return e;
 }
 
@@ -870,10 +868,8 @@ gdr2_status chunk_bwd(const gdr2_problem* p, const int32_t* cu, int nseq, const 
       const int Hk = pv.H / G.G, nrow = pv.B * pv.T, splits = nrow < kParamSplits ? nrow : kParamSplits;
       float* PT = at<float>(ws, G.L.PT);
       float* PT1 = PT + (size_t)kParamSplits * Hk * pv.Dk;
-      if (x == hipSuccess) x = launch_param_reduce_pass(sa.df, PT, nrow, Hk, 1, pv.Dk, splits, stream);
-      if (x == hipSuccess) x = launch_param_reduce_pass(PT, ddelta, splits, Hk, 1, pv.Dk, 1, stream);
-      if (x == hipSuccess) x = launch_param_reduce_pass(sa.pa, PT1, nrow, Hk, 1, 1, splits, stream);
-      if (x == hipSuccess) x = launch_param_reduce_pass(PT1, da, splits, Hk, 1, 1, 1, stream);
+      if (x == hipSuccess) x = launch_param_reduce_pass({sa.df, PT, sa.pa, PT1, nrow, Hk, 1, pv.Dk}, splits, stream);
+      if (x == hipSuccess) x = launch_param_reduce_pass({PT, ddelta, PT1, da, splits, Hk, 1, pv.Dk}, 1, stream);
       return x;
     });
     return hip_status(e, stream);

@@ -516,10 +516,18 @@ hipError_t launch_stage_f32(const StageF32Args& a, bool backward, hipStream_t st
 
 // Sums of the per-workgroup partials of the decay parameters, one pass:
 // out[(z * Hk + hk) * D + c] = sum over the slots s of range z (nslots cut into
-// `splits` ranges) and m < M of P[((s * Hk + hk) * M + m) * D + c].  A second
-// pass with nslots = splits, M = 1, splits = 1 adds the ranges.
-hipError_t launch_param_reduce_pass(const float* P, float* out, int nslots, int Hk, int M, int D, int splits,
-                                    hipStream_t st);
+// `splits` ranges) and m < M of P[((s * Hk + hk) * M + m) * D + c], and the same of
+// P1 into out1 with D = 1.  A second pass with nslots = splits, M = 1, splits = 1
+// adds the ranges.
+struct ParamReduceArgs {
+  const float* P;
+  float* out;
+  const float* P1;
+  float* out1;
+  int nslots, Hk, M, D;
+  int per = 0;  // slots of a range (set by the launch)
+};
+hipError_t launch_param_reduce_pass(ParamReduceArgs a, int splits, hipStream_t st);
 
 // Builds the chunk table of a packed call (Varlen) from cu_seqlens: lengths
 // are clamped into [0, T] and the chunk count to ncmax, so malformed offsets

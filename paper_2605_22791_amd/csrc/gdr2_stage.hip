@@ -68,32 +68,41 @@ hipError_t launch_norm_vjp(const NormVjpArgs& a, hipStream_t st) {
 template hipError_t launch_norm_vjp<64>(const NormVjpArgs&, hipStream_t);
 template hipError_t launch_norm_vjp<128>(const NormVjpArgs&, hipStream_t);
 
+// Two reductions of one shape in a launch, D = a.D channels wide and 1 wide:
 // out[(z * Hk + hk) * D + c] = sum over slots s of split z (and m < M) of
-// P[((s * Hk + hk) * M + m) * D + c]; block (hk, 64-channel group, split z),
-// four parts of 64 threads interleaved over the slots, combined in order.
-__global__ __launch_bounds__(256) void param_reduce_kernel(const float* __restrict__ P, float* __restrict__ out,
-                                                           int nslots, int Hk, int M, int D, int per) {
-  __shared__ float red[4][64];
-  const int hk = blockIdx.x, cl = threadIdx.x & 63, part = threadIdx.x >> 6, z = blockIdx.z;
-  const int c = blockIdx.y * 64 + cl;
-  const int s0 = z * per, s1 = min(nslots, s0 + per);
+// P[((s * Hk + hk) * M + m) * D + c]; block (hk, 64-channel group or the narrow one,
+// split z), parts of 64 threads (one channel each; the narrow one 256 parts of one
+// thread) interleaved over the slots, combined in pairs.  A launch is all latency: the two
+// parameters' passes share it (train shape of 128 slots, 16 heads, Dk = 64: four
+// launches of 5.8 us, two of 6.1).
+__global__ __launch_bounds__(256) void param_reduce_kernel(ParamReduceArgs a) {
+  __shared__ float red[256];
+  const int hk = blockIdx.x, z = blockIdx.z, tid = threadIdx.x;
+  const bool wide = (int)blockIdx.y + 1 < (int)gridDim.y;
+  const int D = wide ? a.D : 1, W = wide ? 64 : 1;  // channels; threads of a part
+  const int part = tid / W, parts = 256 / W, c = wide ? blockIdx.y * 64 + tid % W : 0;
+  const float* __restrict__ P = wide ? a.P : a.P1;
+  const int s0 = z * a.per, s1 = min(a.nslots, s0 + a.per);
   float acc = 0.f;
   if (c < D) {
-    for (int s = s0 + part; s < s1; s += 4) {
-      const float* p = P + (((size_t)s * Hk + hk) * M) * D + c;
-      for (int m = 0; m < M; ++m) acc += p[(size_t)m * D];
+    for (int s = s0 + part; s < s1; s += parts) {
+      const float* p = P + (((size_t)s * a.Hk + hk) * a.M) * D + c;
+      for (int m = 0; m < a.M; ++m) acc += p[(size_t)m * D];
     }
   }
-  red[part][cl] = acc;
+  red[tid] = acc;
   __syncthreads();
-  if (part == 0 && c < D) out[((size_t)z * Hk + hk) * D + c] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
+  for (int o = 128; o >= W; o >>= 1) {  // the parts in pairs (uniform: W is the block's)
+    if (tid < o) red[tid] += red[tid + o];
+    __syncthreads();
+  }
+  if (part == 0 && c < D) (wide ? a.out : a.out1)[((size_t)z * a.Hk + hk) * D + c] = red[tid];
 }
 
-hipError_t launch_param_reduce_pass(const float* P, float* out, int nslots, int Hk, int M, int D, int splits,
-                                    hipStream_t st) {
-  const int per = (nslots + splits - 1) / splits;
-  dim3 grid(Hk, (D + 63) / 64, splits);
-  hipLaunchKernelGGL(param_reduce_kernel, grid, dim3(256), 0, st, P, out, nslots, Hk, M, D, per);
+hipError_t launch_param_reduce_pass(ParamReduceArgs a, int splits, hipStream_t st) {
+  a.per = (a.nslots + splits - 1) / splits;
+  dim3 grid(a.Hk, (a.D + 63) / 64 + 1, splits);
+  hipLaunchKernelGGL(param_reduce_kernel, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
