@@ -18,18 +18,26 @@
 // Precision: every product is fp32-accurate (split hi/lo operands: T, the
 // solve, A in Y and U, A_qk, Q_g, Ktail, Ebar, Z); Y is stored in bf16.
 //
-// Decay factors are 2^(G2_r - G2_s) for r >= s, split at a row p:
-// 2^(G2_r - G2_p) * 2^(G2_p - G2_s).  Off the diagonal p is the first row of r's
-// 16-row block and both factors are <= 1.  In a diagonal block p is its middle
-// row (8 of 16), so that each factor is bounded by half a block's decay; entries
-// above the diagonal may overflow there and are masked.  A diagonal block with
-// a half whose decay exceeds e^60 takes four 4-row sub-blocks: products split at
-// each sub-block's first row (both factors <= 1) and its own 4 x 4 pairs element
-// by element.  Split at the block's first row, blocks of the layer's own decay
-// distribution (exp(a) up to 16) exceeded the bound for 3 to 6 in 10^4
-// (block, head) pairs, and the element-by-element tile they took then (16 x 16 x
-// Dk serial steps, some 90 us) set the kernel's time: 8192 tokens x 16 heads
-// from raw projections took 212 us, 146 now.
+// Decay factors are 2^(G2_r - G2_s) for r >= s, split at a row p of r's 16-row
+// block: 2^(G2_r - G2_p) * 2^(G2_p - G2_s).  p is the middle row (8 of 16): in the
+// diagonal block each factor is bounded by half a block's decay (entries above
+// the diagonal may overflow and are masked), and left of it the first factor is
+// and the second is <= 1.  In a block with a half whose decay exceeds e^60 p is the
+// first row, both factors <= 1 left of the diagonal, and the diagonal block takes
+// four 4-row sub-blocks: products split at each sub-block's first row (both
+// factors <= 1) and its own 4 x 4 pairs element by element.  Split at the block's
+// first row and beyond that element by element (16 x 16 x Dk serial steps, some
+// 90 us), the 3 to 6 in 10^4 (block, head) pairs over the bound at the layer's own
+// decay distribution (exp(a) up to 16) set the kernel's time: 8192 tokens x 16
+// heads from raw projections took 212 us, 146 then.
+//
+// A row block's tiles share p, so a wave takes a row block's tiles side by side
+// and forms their query side (decay factor, b * k, splits) once a K-step.  Dealt
+// out three and two to a wave the tiles are more even but form ten query sides, not
+// four, and the factors' VALU work counts for more here than the products.  Whole
+// calls, dealt out and by row block (16 heads, 128 x 128): forward of 1000 tokens
+// 51.6 and 48.5 us, of 8192 packed from raw projections 265 and 241, of 32768 947
+// and 909.
 //
 // T and A_qk are computed transposed (rows = keys) so that each lane's four
 // outputs are consecutive keys of one query row: T goes to LDS as float4 rows
@@ -71,18 +79,6 @@ struct IntraCfg {
   static_assert(LDS <= 80 * 1024, "two workgroups per CU");
 };
 
-// T / A_qk tiles per wave: (row block i of queries, column block j of keys)
-// encoded as 4 * i + j; -1 marks "no tile".  The A_qk tiles above the
-// diagonal are written as zeros (they share fragment blocks with causal tiles).
-__device__ __forceinline__ int tile_of(int wave, int t) {
-  // w0: (0,0) (1,0) (1,1)   w1: (2,0) (2,1) (2,2)   w2: (3,0) (3,1)   w3: (3,2) (3,3)
-  switch (wave) {
-    case 0: return t == 0 ? 0 : (t == 1 ? 4 : 5);
-    case 1: return 8 + t;
-    case 2: return t < 2 ? 12 + t : -1;
-    default: return t < 2 ? 14 + t : -1;
-  }
-}
 // A_qk tiles above the diagonal that share fragment blocks with causal tiles,
 // written as zeros: (0,1) and (2,3).  (0,2) (0,3) (1,2) (1,3) make up two whole
 // blocks, which are not stored.
@@ -156,26 +152,14 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
     const int e = tid + 256 * m, r = e / (DK / 8), c8 = (e % (DK / 8)) * 8;
     kst[m] = ldg16(K + kofs(r) + c8);
   }
-  // q and b rows of the row blocks whose T / A_qk tiles this wave forms (wave 0:
-  // blocks 0 and 1, wave 1: block 2, waves 2 and 3: block 3), as K-step
-  // fragments (row 16 rb + r16, channels 32 p + 8 g ..): the same registers
-  // feed Q_g and Ebar, so each row of q and b is fetched once per wave that needs it
-  const int rbA = wave == 0 ? 0 : (wave == 1 ? 2 : 3);
-  u4v qreg[2][KS], breg[2][KS];
+  // q and b rows of the wave's row block (block `wave`), as K-step fragments (row
+  // 16 wave + r16, channels 32 p + 8 g ..): the same registers feed the block's
+  // T / A_qk tiles, Q_g and Ebar, so each row of q and b is fetched once
+  u4v qreg[KS], breg[KS];
 #pragma unroll
   for (int p = 0; p < KS; ++p) {
-    qreg[0][p] = ldg16(Q + kofs(16 * rbA + r16) + 32 * p + 8 * g);
-    breg[0][p] = ldg16(Bg + kofs(16 * rbA + r16) + 32 * p + 8 * g);
-  }
-  if (wave == 0) {
-#pragma unroll
-    for (int p = 0; p < KS; ++p) {
-      qreg[1][p] = ldg16(Q + kofs(16 + r16) + 32 * p + 8 * g);
-      breg[1][p] = ldg16(Bg + kofs(16 + r16) + 32 * p + 8 * g);
-    }
-  } else {
-#pragma unroll
-    for (int p = 0; p < KS; ++p) qreg[1][p] = breg[1][p] = u4v{0u, 0u, 0u, 0u};
+    qreg[p] = ldg16(Q + kofs(16 * wave + r16) + 32 * p + 8 * g);
+    breg[p] = ldg16(Bg + kofs(16 * wave + r16) + 32 * p + 8 * g);
   }
 
   // ---- G2 = log2(e) * cumsum(g): in-register segment scans + segment offsets
@@ -241,31 +225,27 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
   for (int c = tid; c < DK; c += 256) a.GC[ch * (WsBf16::gc(DK) / 4) + c] = ex2(sG[(CH - 1) * LG + c]);
   if constexpr (FUSED) {
     // q rows: the four lane groups of a row reduce its sum of squares
+    float qf[KS][8];
+    float ss = 0.f;
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      if (sl == 1 && wave != 0) continue;
-      float qf[KS][8];
-      float ss = 0.f;
+    for (int p = 0; p < KS; ++p) {
+      unpack8(qreg[p], qf[p]);
 #pragma unroll
-      for (int p = 0; p < KS; ++p) {
-        unpack8(qreg[sl][p], qf[p]);
+      for (int u = 0; u < 8; ++u) ss += qf[p][u] * qf[p][u];
+    }
+    ss += row_partner16(ss, (g & 1) != 0);
+    ss += row_partner32(ss, g >= 2);
+    const float rq = inv_norm(ss, a.st.eps);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) ss += qf[p][u] * qf[p][u];
-      }
-      ss += row_partner16(ss, (g & 1) != 0);
-      ss += row_partner32(ss, g >= 2);
-      const float rq = inv_norm(ss, a.st.eps);
+    for (int p = 0; p < KS; ++p) {
 #pragma unroll
-      for (int p = 0; p < KS; ++p) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) qf[p][u] *= rq;
-        qreg[sl][p] = __builtin_bit_cast(u4v, round8(qf[p]));
-      }
-      const int row = 16 * (sl == 0 ? rbA : 1) + r16;
-      if (g == 0 && !(sl == 0 && wave == 3)) {  // wave 3 holds a copy of wave 2's rows
-        sRQ[row] = rq;
-        if (wr_norm && a.st.RQ != nullptr && row < len) a.st.RQ[(row0 + row) * HK + hk] = rq;
-      }
+      for (int u = 0; u < 8; ++u) qf[p][u] *= rq;
+      qreg[p] = __builtin_bit_cast(u4v, round8(qf[p]));
+    }
+    const int row = 16 * wave + r16;
+    if (g == 0) {
+      sRQ[row] = rq;
+      if (wr_norm && a.st.RQ != nullptr && row < len) a.st.RQ[(row0 + row) * HK + hk] = rq;
     }
   }
   for (int e = tid; e < 6 * 256; e += 256) {  // upper blocks of T/A (the region held scratch)
@@ -279,23 +259,17 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
   // ---- Q_g (standard fragments) and Ktail^T (standard fragments, via transposed k)
   {
     unsigned char* Qo = a.Qg + ch * WsBf16::qg(DK);
-    // row block rb (K-steps kb) from the q fragments; wave 3 holds a copy of block 3
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      if (sl == 0 ? wave == 3 : wave != 0) continue;
-      const int rb = sl == 0 ? rbA : 1;
+    for (int kb = 0; kb < KS; ++kb) {
+      const int r = 16 * wave + r16, c0 = 32 * kb + 8 * g, blk = wave * KS + kb;
+      float Gr[8], qf[8], x[8];
+      ldf8(sG + r * LG + c0, Gr);
+      unpack8(qreg[kb], qf);
 #pragma unroll
-      for (int kb = 0; kb < KS; ++kb) {
-        const int r = 16 * rb + r16, c0 = 32 * kb + 8 * g, blk = rb * KS + kb;
-        float Gr[8], qf[8], x[8];
-        ldf8(sG + r * LG + c0, Gr);
-        unpack8(qreg[sl][kb], qf);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = qf[e] * ex2(Gr[e]);
-        const Fr f = split8(x);
-        st8(reinterpret_cast<__bf16*>(Qo + blk * 2048 + 16 * lane), f.hi);
-        st8(reinterpret_cast<__bf16*>(Qo + blk * 2048 + 1024 + 16 * lane), f.lo);
-      }
+      for (int e = 0; e < 8; ++e) x[e] = qf[e] * ex2(Gr[e]);
+      const Fr f = split8(x);
+      st8(reinterpret_cast<__bf16*>(Qo + blk * 2048 + 16 * lane), f.hi);
+      st8(reinterpret_cast<__bf16*>(Qo + blk * 2048 + 1024 + 16 * lane), f.lo);
     }
     unsigned char* Ko = a.KtT + ch * WsBf16::ktt(DK);
     for (int blk = wave; blk < NCB * 2; blk += 4) {
@@ -330,51 +304,56 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
       const size_t off = (size_t)(i * 2 + (j >> 1)) * 2048 + 16 * lane + 8 * (j & 1);
       st4split(reinterpret_cast<__bf16*>(Ao + off), reinterpret_cast<__bf16*>(Ao + off + 1024), av);
     };
-#pragma unroll 1
-    for (int t = 0; t < 3; ++t) {
-      const int code = tile_of(wave, t);
-      if (code < 0) continue;
-      const int i = code >> 2, j = code & 3;
-      const int r = 16 * i + r16;  // query row of this lane's outputs
-      const int s = 16 * j + r16;  // key row supplied by this lane (A operand)
-      const int ref = 16 * i + (i == j ? 8 : 0);
-      const bool sec = i == 1;  // wave 0's second row block
-      f4 accT = f4zero(), accA = f4zero();
+    // The row block's tiles (wi, j <= wi) side by side: the query side is formed once
+    // a K-step, and the waves' tile counts differ by less than what it takes.
+    const int wi = __builtin_amdgcn_readfirstlane(wave);
+    {
+      const int r = 16 * wi + r16, piv = 16 * wi + (unsafe[wi] != 0 ? 0 : 8);
+      f4 accT[4], accA[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) accT[j] = accA[j] = f4zero();
 #pragma unroll
       for (int p = 0; p < KS; ++p) {
         const int c0 = 32 * p + 8 * g;
-        float Gs[8], Gr[8], Gp[8], ks[8], kr[8], br[8], qr[8];
-        ldf8(sG + s * LG + c0, Gs);
+        float Gr[8], Gp[8], kr[8], br[8], qr[8], le[8], lq[8];
         ldf8(sG + r * LG + c0, Gr);
-        ldf8(sG + ref * LG + c0, Gp);
-        unpack8(ld8(sK + s * LKB + c0), ks);
+        ldf8(sG + piv * LG + c0, Gp);
         unpack8(ld8(sK + r * LKB + c0), kr);
-        unpack8(sec ? breg[1][p] : breg[0][p], br);
-        unpack8(sec ? qreg[1][p] : qreg[0][p], qr);
-        float rk[8], le[8], lq[8];
+        unpack8(breg[p], br);
+        unpack8(qreg[p], qr);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          rk[e] = ks[e] * ex2(Gp[e] - Gs[e]);
           const float f = ex2(Gr[e] - Gp[e]);
           le[e] = br[e] * kr[e] * f;
           lq[e] = qr[e] * f;
         }
-        const Fr rkf = split8(rk);
-        accT = mma3(rkf, split8(le), accT);
-        accA = mma3(rkf, split8(lq), accA);
+        const Fr lef = split8(le), lqf = split8(lq);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (j > wi) break;
+          float Gs[8], ks[8], rk[8];
+          ldf8(sG + (16 * j + r16) * LG + c0, Gs);  // key row supplied by this lane (A operand)
+          unpack8(ld8(sK + (16 * j + r16) * LKB + c0), ks);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) rk[e] = ks[e] * ex2(Gp[e] - Gs[e]);
+          const Fr rkf = split8(rk);
+          accT[j] = mma3(rkf, lef, accT[j]);
+          accA[j] = mma3(rkf, lqf, accA[j]);
+        }
       }
-      emit(i, j, accT, accA);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (j > wi) break;
+        emit(wi, j, accT[j], accA[j]);
+      }
     }
     // An unsafe diagonal block again, over what the loop left there: sub-blocks
     // sa of four rows against the keys before each as products split at the
     // sub-block's first row, both factors <= 1 (a product's other rows and keys
     // are clamped and not used), then its own 4 x 4 pairs element by element.
     // q and b are re-read: rare, and it must not cost the loop registers.
-    // Wave 0 forms diagonal blocks 0 and 1, waves 1 and 3 blocks 2 and 3.
-    const int d0 = wave == 0 ? 0 : (wave == 1 ? 2 : 3), d1 = wave == 0 ? 2 : (wave == 2 ? 3 : d0 + 1);
-#pragma unroll 1
-    for (int i = d0; i < d1; ++i) {
-      if (unsafe[i] == 0) continue;
+    if (unsafe[wi] != 0) {
+      const int i = wi;
       const int r = 16 * i + r16;
       const __bf16 *Qr = Q + kofs(r), *Br = Bg + kofs(r);
       const auto qn = [&](float x) { return FUSED ? (float)(__bf16)(x * sRQ[r]) : x; };
@@ -516,35 +495,26 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
   }
 
   // ---- Ebar = b * k * gamma (split) over the G2 region
-  // (rows of the wave's row blocks, from the b fragments; wave 3 has none of its own)
+  // (rows of the wave's row block, from the b fragments)
   {
-    Fr ef[2][KS];
+    Fr ef[KS];
+    const int re = 16 * wave + r16;
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      if (sl == 0 ? wave == 3 : wave != 0) continue;
-      const int r = 16 * (sl == 0 ? rbA : 1) + r16;
+    for (int p = 0; p < KS; ++p) {
+      const int c0 = 32 * p + 8 * g;
+      float Gv[8], kf[8], bf[8], x[8];
+      ldf8(sG + re * LG + c0, Gv);
+      unpack8(ld8(sK + re * LKB + c0), kf);
+      unpack8(breg[p], bf);
 #pragma unroll
-      for (int p = 0; p < KS; ++p) {
-        const int c0 = 32 * p + 8 * g;
-        float Gv[8], kf[8], bf[8], x[8];
-        ldf8(sG + r * LG + c0, Gv);
-        unpack8(ld8(sK + r * LKB + c0), kf);
-        unpack8(breg[sl][p], bf);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = bf[e] * kf[e] * ex2(Gv[e]);
-        ef[sl][p] = split8(x);
-      }
+      for (int e = 0; e < 8; ++e) x[e] = bf[e] * kf[e] * ex2(Gv[e]);
+      ef[p] = split8(x);
     }
     __syncthreads();
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      if (sl == 0 ? wave == 3 : wave != 0) continue;
-      const int r = 16 * (sl == 0 ? rbA : 1) + r16;
-#pragma unroll
-      for (int p = 0; p < KS; ++p) {
-        st8(sEhi + r * LE + 32 * p + 8 * g, ef[sl][p].hi);
-        st8(sElo + r * LE + 32 * p + 8 * g, ef[sl][p].lo);
-      }
+    for (int p = 0; p < KS; ++p) {
+      st8(sEhi + re * LE + 32 * p + 8 * g, ef[p].hi);
+      st8(sElo + re * LE + 32 * p + 8 * g, ef[p].lo);
     }
     // A split once into bf16 hi / lo planes (the k tile is dead): the Y and U
     // products read their A fragments from there (row r, 16 values per thread)
