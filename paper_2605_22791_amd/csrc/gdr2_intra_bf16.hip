@@ -39,6 +39,11 @@
 // 51.6 and 48.5 us, of 8192 packed from raw projections 265 and 241, of 32768 947
 // and 909.
 //
+// Work without a barrier between it fills the waves' idle time: the Ktail blocks
+// go mostly to the waves with few tiles, and Ebar's rows are formed beside the
+// solve, whose serial parts keep one to three waves busy.  1000 tokens 48.7 and
+// 47.8 us; the long shapes, bound by memory, are unchanged.
+//
 // T and A_qk are computed transposed (rows = keys) so that each lane's four
 // outputs are consecutive keys of one query row: T goes to LDS as float4 rows
 // and A_qk / Y land directly in the permuted fragment order.
@@ -257,6 +262,7 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
   __syncthreads();
 
   // ---- Q_g (standard fragments) and Ktail^T (standard fragments, via transposed k)
+  const int wi = __builtin_amdgcn_readfirstlane(wave);
   {
     unsigned char* Qo = a.Qg + ch * WsBf16::qg(DK);
 #pragma unroll
@@ -272,7 +278,10 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
       st8(reinterpret_cast<__bf16*>(Qo + blk * 2048 + 1024 + 16 * lane), f.lo);
     }
     unsigned char* Ko = a.KtT + ch * WsBf16::ktt(DK);
-    for (int blk = wave; blk < NCB * 2; blk += 4) {
+    // dealt out 7 : 5 : 3 : 1, against the waves' 1 to 4 tiles below
+    const auto first = [](int w) { return NCB * 2 * w * (8 - w) / 16; };
+#pragma unroll 1
+    for (int blk = first(wi); blk < first(wi + 1); ++blk) {
       const int cb = blk >> 1, kb = blk & 1;
       const int c = 16 * cb + r16;
       float kf[8], x[8];
@@ -306,7 +315,6 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
     };
     // The row block's tiles (wi, j <= wi) side by side: the query side is formed once
     // a K-step, and the waves' tile counts differ by less than what it takes.
-    const int wi = __builtin_amdgcn_readfirstlane(wave);
     {
       const int r = 16 * wi + r16, piv = 16 * wi + (unsafe[wi] != 0 ? 0 : 8);
       f4 accT[4], accA[4];
@@ -419,8 +427,27 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
 
   // ---- A = (I + T)^{-1} in place, fp32: diagonal blocks by forward
   // substitution (lane = column), then the off-diagonal blocks row block by
-  // row block:  A_ij = -A_ii * sum_{j <= k < i} T_ik A_kj
-  if (wave == 0) {
+  // row block:  A_ij = -A_ii * sum_{j <= k < i} T_ik A_kj.  Wave 3, which has no
+  // part in the row blocks' solve, does the substitution; beside these each wave
+  // forms its rows of Ebar = b * k * gamma (split) in registers.
+  Fr ef[KS];
+  const int re = 16 * wave + r16;
+  const auto form_ebar = [&]() {
+#pragma unroll
+    for (int p = 0; p < KS; ++p) {
+      const int c0 = 32 * p + 8 * g;
+      float Gv[8], kf[8], bf[8], x[8];
+      ldf8(sG + re * LG + c0, Gv);
+      unpack8(ld8(sK + re * LKB + c0), kf);
+      unpack8(breg[p], bf);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = bf[e] * kf[e] * ex2(Gv[e]);
+      ef[p] = split8(x);
+    }
+  };
+  if (wave != 3) {
+    form_ebar();
+  } else {
     const int blk = lane >> 4, cc = lane & 15;
     float x[16];
 #pragma unroll
@@ -449,6 +476,7 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
     wst[m] = ldg16(Wg + vofs(h0, r) + c8);
   }
   __syncthreads();
+  if (wave == 3) form_ebar();
 #pragma unroll 1
   for (int i = 1; i < 4; ++i) {
     f4 res = f4zero();
@@ -494,23 +522,8 @@ __global__ __launch_bounds__(256, 2) void intra_bf16_kernel(IntraBf16Args a) {
     }
   }
 
-  // ---- Ebar = b * k * gamma (split) over the G2 region
-  // (rows of the wave's row block, from the b fragments)
+  // ---- Ebar over the G2 region (last read when its rows were formed)
   {
-    Fr ef[KS];
-    const int re = 16 * wave + r16;
-#pragma unroll
-    for (int p = 0; p < KS; ++p) {
-      const int c0 = 32 * p + 8 * g;
-      float Gv[8], kf[8], bf[8], x[8];
-      ldf8(sG + re * LG + c0, Gv);
-      unpack8(ld8(sK + re * LKB + c0), kf);
-      unpack8(breg[p], bf);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = bf[e] * kf[e] * ex2(Gv[e]);
-      ef[p] = split8(x);
-    }
-    __syncthreads();
 #pragma unroll
     for (int p = 0; p < KS; ++p) {
       st8(sEhi + re * LE + 32 * p + 8 * g, ef[p].hi);
