@@ -82,7 +82,8 @@ struct Layout {
 // (narrow_scan): two passes over the segments and the chain between cost more than
 // one walk of 1.8 us a chunk.  One sequence, 16 heads, 128 x 128, whole / segmented:
 // 16 chunks 52 / 94 us forward, 156 / 230 training; 32 chunks 88 / 114, 263 / 276;
-// 64 chunks 188 / 194, 506 / 476.
+// 64 chunks 188 / 194, 506 / 476 (with an intra-chunk kernel that took 4 us more at
+// 16 chunks than it does now, on either side).
 constexpr int kSegmentChunks = 48;
 
 constexpr int kParamSplits = 64;  // slot ranges of the first decay-parameter reduction pass

@@ -9,9 +9,8 @@
 // own, four for R, four for Q_g S and A_qk R, one per key block for the state; every
 // operand block goes from memory straight into the registers of the one wave
 // that multiplies it; and LDS holds S and R alone.  A step is 1.7 us on 64
-// workgroups (16 heads, 16 chunks, 128 x 128: 52 us with the intra-chunk kernel
-// against 76 with the wide scan); what is left is LDS time of the products' S and R
-// fragments and, with a workgroup on every CU, the memory's answer (3 us a step,
+// workgroups (16 heads, 16 chunks, 128 x 128: 28 us, the wide scan 52); what is
+// left is LDS time of the products' S and R fragments and, with a workgroup on every CU, the memory's answer (3 us a step,
 // where the wide kernel takes 4).  With the loads of R's and Q_g's waves in front of
 // the barrier they wait at, a step was 2.1 us: the loads of all waves at once take
 // 700 cycles to issue.
