@@ -229,14 +229,14 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
 
   extern __shared__ float smem[];
   float* sR0 = smem;                // G, later X = A^T dA (LD64)
-  float* sLe = sR0 + CH * LS;       // b*k*exp(G_r - G_p)
-  float* sRk = sLe + CH * LS;       // k*exp(G_e - G_s); later solve scratch, then dY
+  float* sLe = sR0 + CH * LS;       // b*k times its left factor (chunk_refs)
+  float* sRk = sLe + CH * LS;       // k times its right factor; later solve scratch, then dY
   float* sTd = sRk + CH * LS;       // T, later dA (LD64)
   float* sA = sTd + CH * LD64;      // A (LD64)
   float* eP = sA + CH * LD64;
   float* brg = eP + 4 * DK;
   float* eGC = brg + 10 * DK;
-  int* unsafe = reinterpret_cast<int*>(eGC + DK);
+  int* split = reinterpret_cast<int*>(eGC + DK);
   float* sG = sR0;
   float* sX = sR0;
   float* sdY = sRk;
@@ -248,9 +248,9 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
   float* DT = a.DT + ch * CH * CH;
   float* DEg = a.DEg + ch * CH * DK;
 
-  if (tid < 4) unsafe[tid] = 0;
+  if (tid < 4) split[tid] = 0;
   chunk_cumsum<DK, NTHR>(a.g + kbase, rs, sG, tid, len);
-  chunk_refs<DK, NTHR>(sG, eP, brg, eGC, unsafe, tid);
+  chunk_refs<DK, NTHR>(sG, eP, brg, eGC, split, tid);
   for (int e = tid; e < CH * DK / 4; e += NTHR) {
     const int r = e / (DK / 4), c4 = (e % (DK / 4)) * 4, i = r >> 4;
     const float4 kk = ld4z(a.k + kbase + r * rs + c4, r < len);
@@ -260,8 +260,8 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
       const int c = c4 + u;
       const float G = sG[r * LS + c];
       const float kv = f4at(kk, u);
-      sLe[r * LS + c] = f4at(bv, u) * kv * expf(G - sG[(16 * i) * LS + c]);
-      sRk[r * LS + c] = kv * expf(sG[(16 * i + 15) * LS + c] - G);
+      sLe[r * LS + c] = f4at(bv, u) * kv * expf(G - sG[left_row(split, i) * LS + c]);
+      sRk[r * LS + c] = kv * expf(sG[right_row(split, i) * LS + c] - G);
     }
   }
   __syncthreads();
@@ -271,10 +271,10 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
     if (it < 10) {
       int i, j;
       pair_of(it, i, j);
-      const f4 acc = (i == j && unsafe[i])
+      const f4 acc = (i == j && split[i] == kSplitNone)
                          ? diag_tile_direct<DK, TIn>(a.b + kbase, a.k + kbase, a.k + kbase,
                                                      a.g + kbase, rs, i, lane, true, len)
-                         : gram_tile<DK>(sLe, sRk, brg + pair_index(i, j) * DK, i, j, lane);
+                         : gram_tile<DK>(sLe, sRk, brg, split, i, j, lane);
       const int s = 16 * j + lr;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
   float* eGC = brg + 10 * DK;
   float* colp = eGC + DK;          // [4 row blocks][4 lane groups][DK]
   float* dgp = colp + 16 * DK;     // [DK][NSPLIT]
-  int* unsafe = reinterpret_cast<int*>(dgp + DK * NSPLIT);
+  int* split = reinterpret_cast<int*>(dgp + DK * NSPLIT);
   float* sdG = sLq;                // reused after the item loop
 
   const float* Hn = a.Hs + ch * DK * DV;
@@ -478,9 +478,9 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
   const float* DT = a.DT + ch * CH * CH;
   const float* DEg = a.DEg + ch * CH * DK;
 
-  if (tid < 4) unsafe[tid] = 0;
+  if (tid < 4) split[tid] = 0;
   chunk_cumsum<DK, NTHR>(a.g + kbase, rs, sG, tid, len);
-  chunk_refs<DK, NTHR>(sG, eP, brg, eGC, unsafe, tid);
+  chunk_refs<DK, NTHR>(sG, eP, brg, eGC, split, tid);
   for (int e = tid; e < CH * DK / 4; e += NTHR) {
     const int r = e / (DK / 4), c4 = (e % (DK / 4)) * 4, i = r >> 4;
     const float4 kk = ld4z(a.k + kbase + r * rs + c4, r < len);
@@ -490,11 +490,11 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
     for (int u = 0; u < 4; ++u) {
       const int c = c4 + u;
       const float G = sG[r * LS + c];
-      const float lf = expf(G - sG[(16 * i) * LS + c]);
+      const float lf = expf(G - sG[left_row(split, i) * LS + c]);
       const float kv = f4at(kk, u);
       sLe[r * LS + c] = f4at(bv, u) * kv * lf;
       sLq[r * LS + c] = f4at(qq, u) * lf;
-      sRk[r * LS + c] = kv * expf(sG[(16 * i + 15) * LS + c] - G);
+      sRk[r * LS + c] = kv * expf(sG[right_row(split, i) * LS + c] - G);
     }
   }
   // state part of d gamma_C: rowsum(dS_C * S0) per key channel
@@ -514,17 +514,18 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
     const int i = it / NCB, cb = it % NCB;
     const int c = 16 * cb + lr;
     f4 P1 = {0.f, 0.f, 0.f, 0.f}, P2 = P1, P3 = P1, dQs = P1, dKt = P1;
-    const bool diag_direct = unsafe[i] != 0;
+    const bool diag_direct = split[i] == kSplitNone, mid = split[i] == kSplitMiddle;
     // P1 / P2: sum_{s<=r} M[r][s] k_s exp(G_r - G_s), without the left factor
     for (int j = 0; j <= i; ++j) {
       if (j == i && diag_direct) break;
-      const float d = brg[pair_index(i, j) * DK + c];
+      const float d = j == i && mid ? 1.f : brg[pair_index(i, j) * DK + c];
+      const float cl = j < i && split[j] == kSplitMiddle ? brg[pair_index(j, j) * DK + c] : 1.f;
       const float4 mt = ld4(DT + (16 * i + lr) * CH + 16 * j + 4 * lg);
       const float4 mq = ld4(DAqk + (16 * i + lr) * CH + 16 * j + 4 * lg);
       const int s0 = 16 * j + 4 * lg;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const float bv = sRk[(s0 + u) * LS + c] * d;
+        const float bv = sRk[(s0 + u) * LS + c] * cl * d;
         P1 = mfma4(f4at(mt, u), bv, P1);
         P2 = mfma4(f4at(mq, u), bv, P2);
       }
@@ -532,12 +533,13 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
     // P3: sum_{r>=s} (dT[r][s] (b k)_r + dAqk[r][s] q_r) exp(G_r - G_s), without the right factor
     for (int i2 = i; i2 < 4; ++i2) {
       if (i2 == i && diag_direct) continue;
-      const float d = brg[pair_index(i2, i) * DK + c];
+      const float d = i2 == i && mid ? 1.f : brg[pair_index(i2, i) * DK + c];
+      const float cl = i2 > i && mid ? brg[pair_index(i, i) * DK + c] : 1.f;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int r = 16 * i2 + 4 * lg + u;
-        P3 = mfma4(DT[r * CH + 16 * i + lr], sLe[r * LS + c] * d, P3);
-        P3 = mfma4(DAqk[r * CH + 16 * i + lr], sLq[r * LS + c] * d, P3);
+        P3 = mfma4(DT[r * CH + 16 * i + lr], sLe[r * LS + c] * d * cl, P3);
+        P3 = mfma4(DAqk[r * CH + 16 * i + lr], sLq[r * LS + c] * d * cl, P3);
       }
     }
     // dQs = dO S0^T and dKt = R dS_C^T
@@ -565,8 +567,8 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
     for (int u = 0; u < 4; ++u) {
       const int r = 16 * i + 4 * lg + u;
       const float G = sG[r * LS + c];
-      const float lf = expf(G - sG[(16 * i) * LS + c]);
-      const float rf = expf(sG[(16 * i + 15) * LS + c] - G);
+      const float lf = expf(G - sG[left_row(split, i) * LS + c]);
+      const float rf = expf(sG[right_row(split, i) * LS + c] - G);
       const float gam = expf(G);
       const float tail = expf(sG[(CH - 1) * LS + c] - G);
       const size_t off = kbase + r * rs + c, offo = kobase + r * rso + c;

@@ -3,8 +3,8 @@
 // Chunk geometry: C = 64 tokens per chunk (App. C.2), split into four 16-row
 // blocks that match the 16x16 MFMA tiles.  Inside a chunk every decay ratio
 // gamma_r / gamma_s = exp(G_r - G_s) (r >= s, App. A.1) is formed as a product
-// of three factors that are each bounded, so no intermediate overflows even
-// when the chunk's total decay is far below fp32's exp range:
+// of factors that are each bounded, so no intermediate overflows even when the
+// chunk's total decay is far below fp32's exp range:
 //
 //   exp(G_r - G_s) = exp(G_r - G_p(i)) * exp(G_p(i) - G_e(j)) * exp(G_e(j) - G_s)
 //                    \_ left, <= 1 _/   \____ bridge d_ij ____/  \_ right, <= 1 _/
@@ -12,14 +12,23 @@
 // with r in block i, s in block j <= i, p(i) = 16 i the first row of block i
 // and e(j) = 16 j + 15 the last row of block j.  For j < i the bridge is <= 1;
 // for j == i it is >= 1 and bounded by the decay accumulated inside one block.
-// When that exceeds kDiagLimit the diagonal block is computed element by element
-// instead (kernels check the per-block `unsafe` flag).  e^78 leaves fp32 room on
-// both sides: the left factor times the bridge stays below 1e34, the right factor of
-// a key of 1e-3 above the smallest normal number.  The layer's own decay (exp(a) up
-// to 16) passes e^60 in some 4 of 10^4 (block, head) pairs, e^78 in none of 3 10^4
-// drawn, and the element-by-element tile is slow enough to set a kernel's time: 500
-// tokens x 2 x 4 heads from raw projections, training, took 373 us at e^60, 273 now.  The paper does not
-// prescribe a stabilisation; this one is this library's.
+//
+// A block whose own decay exceeds e^kDiagLimit is split at its middle row instead
+// (kSplitMiddle): its left and right factors are relative to m(i) = 16 i + 8, each
+// within e^+-(half the block's decay), and its diagonal tile needs no bridge.  Towards
+// the other blocks the bridge starts at m(i), and the right factors are brought back to
+// the last row by a factor of their own, exp(G_e(j) - G_m(j)) <= 1 (`close`).  Where a
+// half exceeds the limit too (kSplitNone), the factors are as at first and the diagonal
+// tile is computed element by element.
+//
+// So whatever a sum is formed of (q, k, b k, an upstream gradient) meets at most e^60
+// = 1.1e26 before its other factor, or e^-60: finite, and nothing lost, for operands
+// of 1e-12 to 1e12.  The limit is that of the operands; a split at the block's ends up
+// to e^78 left 4.5e4.  The element-by-element tile is slow enough to set a kernel's time,
+// and the layer's own decay (exp(a) up to 16) passes e^60 in some 3 of 10^3 (block, head)
+// pairs, e^60 in a half in none of 3 10^4 drawn: 1000 tokens x 16 heads from raw
+// projections, training, 891 us with it past e^60, 438 with the middle.  The paper
+// does not prescribe a stabilisation; this one is this library's.
 
 #pragma once
 
@@ -31,7 +40,7 @@ namespace gdr2 {
 
 constexpr int CH = 64;            // chunk length C
 constexpr int LD64 = CH + 4;      // LDS row stride of 64-wide fp32 tiles
-constexpr float kDiagLimit = 78.f;
+constexpr float kDiagLimit = 60.f;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -146,54 +155,83 @@ __device__ void chunk_cumsum(const float* __restrict__ g, size_t rs, float* sG, 
   __syncthreads();
 }
 
-// Reference exponentials of the block factorisation: eP[i][c] = exp(G_{16i}),
-// brg[pair(i,j)][c] = exp(G_{16i} - G_{16j+15}) for j <= i, eGC[c] = exp(G_63),
-// unsafe[i] = 1 when block i's diagonal bridge would exceed e^kDiagLimit.
+// How a block's decay factors are split (see the top), and the rows that its left and
+// right factors are relative to.
+enum Split : int { kSplitEnds = 0, kSplitMiddle = 1, kSplitNone = 2 };
+__device__ __forceinline__ int left_row(const int* split, int i) { return 16 * i + (split[i] == kSplitMiddle ? 8 : 0); }
+__device__ __forceinline__ int right_row(const int* split, int i) { return 16 * i + (split[i] == kSplitMiddle ? 8 : 15); }
+
+// Reference exponentials of the block factorisation: split[i] (zero before the call),
+// eP[i][c] = exp(G_left(i)), brg[pair(i,j)][c] = exp(G_left(i) - G_{16j+15}) for j < i;
+// brg[pair(j,j)][c] the bridge of block j's diagonal tile or, split at the middle, its
+// close; eGC[c] = exp(G_63).
 template <int DK, int NTHR>
-__device__ void chunk_refs(const float* sG, float* eP, float* brg, float* eGC, int* unsafe,
+__device__ void chunk_refs(const float* sG, float* eP, float* brg, float* eGC, int* split,
                            int tid) {
   constexpr int LG = DK + 4;
   for (int e = tid; e < 4 * DK; e += NTHR) {
     const int i = e / DK, c = e % DK;
-    eP[i * DK + c] = expf(sG[(16 * i) * LG + c]);
+    const float p = sG[(16 * i) * LG + c], m = sG[(16 * i + 8) * LG + c], x = sG[(16 * i + 15) * LG + c];
+    if (p - x > kDiagLimit) atomicMax(split + i, p - m > kDiagLimit || m - x > kDiagLimit ? kSplitNone : kSplitMiddle);
+  }
+  __syncthreads();
+  for (int e = tid; e < 4 * DK; e += NTHR) {
+    const int i = e / DK, c = e % DK;
+    eP[i * DK + c] = expf(sG[left_row(split, i) * LG + c]);
   }
   for (int e = tid; e < 10 * DK; e += NTHR) {
     const int p = e / DK, c = e % DK;
     int i, j;
     pair_of(p, i, j);
-    const float d = sG[(16 * i) * LG + c] - sG[(16 * j + 15) * LG + c];
-    brg[p * DK + c] = expf(d);
-    if (i == j && d > kDiagLimit) unsafe[i] = 1;
+    const float x = sG[(16 * j + 15) * LG + c];
+    const bool close = i == j && split[i] == kSplitMiddle;
+    brg[p * DK + c] = expf(close ? x - sG[(16 * j + 8) * LG + c] : sG[left_row(split, i) * LG + c] - x);
   }
   for (int c = tid; c < DK; c += NTHR) eGC[c] = expf(sG[(CH - 1) * LG + c]);
   __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
-// 16x16 tile of  sum_c L[16i+m][c] * d[c] * R[16j+n][c]  on MFMA (fp32).
-// L, R: LDS tiles with row stride DK+4; d: bridge vector (length DK).
-// The k index c is permuted so that each lane reads 4 consecutive channels.
+// 16x16 tile of  sum_c L[16i+m][c] * R[16j+n][c] * (bridge, close of the pair)  on
+// MFMA (fp32).  L, R: left and right factors, LDS tiles with row stride DK+4; brg and
+// split as chunk_refs leaves them.  The k index c is permuted so that each lane reads 4
+// consecutive channels.
 template <int DK>
-__device__ __forceinline__ f4 gram_tile(const float* L, const float* R, const float* d, int i,
+__device__ __forceinline__ f4 gram_tile(const float* L, const float* R, const float* brg, const int* split, int i,
                                         int j, int lane) {
   constexpr int LS = DK + 4;
   f4 acc = {0.f, 0.f, 0.f, 0.f};
   const float* pa = L + (16 * i + (lane & 15)) * LS + 4 * (lane >> 4);
   const float* pb = R + (16 * j + (lane & 15)) * LS + 4 * (lane >> 4);
-  const float* pd = d + 4 * (lane >> 4);
+  const float* pd = brg + pair_index(i, j) * DK + 4 * (lane >> 4);
+  if (split[j] != kSplitMiddle) {
 #pragma unroll 4
+    for (int kk = 0; kk < DK; kk += 16) {
+      const float4 a = ld4(pa + kk), b = ld4(pb + kk), s = ld4(pd + kk);
+      acc = mfma4(a.x * s.x, b.x, acc);
+      acc = mfma4(a.y * s.y, b.y, acc);
+      acc = mfma4(a.z * s.z, b.z, acc);
+      acc = mfma4(a.w * s.w, b.w, acc);
+    }
+    return acc;
+  }
+  const float* pe = brg + pair_index(j, j) * DK + 4 * (lane >> 4);
+  const float4 one = make_float4(1.f, 1.f, 1.f, 1.f);
+#pragma unroll 2
   for (int kk = 0; kk < DK; kk += 16) {
-    const float4 a = ld4(pa + kk), b = ld4(pb + kk), s = ld4(pd + kk);
-    acc = mfma4(a.x * s.x, b.x, acc);
-    acc = mfma4(a.y * s.y, b.y, acc);
-    acc = mfma4(a.z * s.z, b.z, acc);
-    acc = mfma4(a.w * s.w, b.w, acc);
+    const float4 a = ld4(pa + kk), b = ld4(pb + kk);
+    const float4 s = i == j ? one : ld4(pd + kk), t = i == j ? one : ld4(pe + kk);
+    acc = mfma4(a.x * s.x, b.x * t.x, acc);
+    acc = mfma4(a.y * s.y, b.y * t.y, acc);
+    acc = mfma4(a.z * s.z, b.z * t.z, acc);
+    acc = mfma4(a.w * s.w, b.w * t.w, acc);
   }
   return acc;
 }
 
-// Diagonal 16x16 tile computed element by element (used only for an unsafe
-// block): out[m][n] = sum_c X[r][c] * k[s][c] * exp(G_r - G_s), r = 16i+m,
+// ---------------------------------------------------------------------------
+// Diagonal 16x16 tile computed element by element (used only for a block
+// of kSplitNone): out[m][n] = sum_c X[r][c] * k[s][c] * exp(G_r - G_s), r = 16i+m,
 // s = 16i+n, for r >= s (strict when `strict`), else 0.  X = b*k (Gram T) or
 // q (scores).  Reads the raw inputs; G differences are accumulated locally
 // from g so they never leave the block.  Rows >= len read as zero.

@@ -43,20 +43,20 @@ __global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
 
   extern __shared__ float smem[];
   float* sR0 = smem;                      // G (64 x LS), later T (64 x LD64)
-  float* sLe = sR0 + CH * LS;             // b*k*exp(G_r - G_p)
-  float* sLq = sLe + CH * LS;             // q*exp(G_r - G_p); later Z and solve scratch
-  float* sRk = sLq + CH * LS;             // k*exp(G_e - G_s)
+  float* sLe = sR0 + CH * LS;             // b*k times its left factor (chunk_refs)
+  float* sLq = sLe + CH * LS;             // q times it; later Z and solve scratch
+  float* sRk = sLq + CH * LS;             // k times its right factor
   float* sA = sRk + CH * LS;              // A (64 x LD64)
   float* eP = sA + CH * LD64;             // 4 x DK
   float* brg = eP + 4 * DK;               // 10 x DK
   float* eGC = brg + 10 * DK;             // DK
-  int* unsafe = reinterpret_cast<int*>(eGC + DK);
+  int* split = reinterpret_cast<int*>(eGC + DK);
   float* sG = sR0;
   float* sT = sR0;
 
-  if (tid < 4) unsafe[tid] = 0;
+  if (tid < 4) split[tid] = 0;
   chunk_cumsum<DK, NTHR>(a.g + kbase, rs, sG, tid, len);
-  chunk_refs<DK, NTHR>(sG, eP, brg, eGC, unsafe, tid);
+  chunk_refs<DK, NTHR>(sG, eP, brg, eGC, split, tid);
 
   // gate-absorbed tiles; Qg and Ktail go straight to the workspace
   float* Qg = a.Qg + ch * CH * DK;
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
     for (int u = 0; u < 4; ++u) {
       const int c = c4 + u;
       const float G = sG[r * LS + c];
-      const float lf = expf(G - sG[(16 * i) * LS + c]);
-      const float rf = expf(sG[(16 * i + 15) * LS + c] - G);
+      const float lf = expf(G - sG[left_row(split, i) * LS + c]);
+      const float rf = expf(sG[right_row(split, i) * LS + c] - G);
       const float kv = f4at(kk, u), qv = f4at(qq, u);
       sLe[r * LS + c] = f4at(bv, u) * kv * lf;
       sLq[r * LS + c] = qv * lf;
@@ -96,11 +96,11 @@ __global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
     int i, j;
     pair_of(isT ? it : it - 10, i, j);
     f4 acc;
-    if (i == j && unsafe[i]) {
+    if (i == j && split[i] == kSplitNone) {
       acc = isT ? diag_tile_direct<DK, TIn>(a.b + kbase, a.k + kbase, a.k + kbase, a.g + kbase, rs, i, lane, true, len)
                 : diag_tile_direct<DK, TIn>(a.q + kbase, nullptr, a.k + kbase, a.g + kbase, rs, i, lane, false, len);
     } else {
-      acc = gram_tile<DK>(isT ? sLe : sLq, sRk, brg + pair_index(i, j) * DK, i, j, lane);
+      acc = gram_tile<DK>(isT ? sLe : sLq, sRk, brg, split, i, j, lane);
     }
     const int ccol = 16 * j + (lane & 15);
 #pragma unroll

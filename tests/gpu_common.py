@@ -2,6 +2,8 @@
 
 import numpy as np
 
+from tests.helpers import rel_l2 as rel
+
 CH = 64
 
 
@@ -46,6 +48,25 @@ def pick(x, pairs, state=False):
     if state:
         return np.stack([x[b, h:h + 1] for (b, h) in pairs])
     return np.stack([x[b, :, h:h + 1] for (b, h) in pairs])
+
+
+def decay_terms(x, g):
+    """Magnitudes that the gradient of the log-decay is summed from, for a fixed-length problem x with
+    its gradients g: a row's value is the sum over the rest of its chunk of dq q - dKg k + dEg b k, where
+    |dEg b k| = |db b| and |dKg k| <= |dk k| + |db b|.  On channels that decay fast this sum cancels to a
+    part in e^-decay of its terms, which is what an error of it can be held against there."""
+    mag = np.abs(g["dq"] * x["q"]) + np.abs(g["dk"] * x["k"]) + 2 * np.abs(g["db"] * x["b"])
+    for c in range(0, mag.shape[1], CH):
+        mag[:, c:c + CH] = np.cumsum(mag[:, c:c + CH][:, ::-1], axis=1)[:, ::-1]
+    return mag
+
+
+def check_decay_grad(got, want, terms, fast, tol):
+    """Channels that decay slowly at the relative tolerance; `fast` ones against the terms of their sum."""
+    slow = rel(got[..., ~fast], want[..., ~fast])
+    err = np.linalg.norm((got - want)[..., fast]) / np.linalg.norm(terms[..., fast])
+    print(f"decay gradient: slow channels {slow:.1e}, fast ones over their terms {err:.1e}")
+    assert slow < tol and err < tol, (slow, err)
 
 
 def ws_layout(B, T, H, Dk, Dv, bwd):

@@ -11,7 +11,7 @@ import pytest
 from oracle import gdr2_recurrent_bwd, gdr2_chunk_bwd_ref
 from paper_2605_22791_amd.inputs import config, make_inputs
 from tests.helpers import rel_l2
-from tests.gpu_common import dev_inputs, host, heads, pick, ws_layout, ws_view, CH
+from tests.gpu_common import check_decay_grad, decay_terms, dev_inputs, host, heads, pick, ws_layout, ws_view, CH
 
 pytestmark = pytest.mark.gpu
 
@@ -533,3 +533,38 @@ def test_fp32_state_kernels(B, H, T, Dk, Dv, save):
     o_ref, S_ref = gdr2_recurrent_fwd(d["q"], d["k"], d["v"], d["log_alpha"], d["b"], d["w"], d["S0"], d["scale"])
     assert rel_l2(host(o), o_ref) < TOL["fp32"] and rel_l2(host(ST), S_ref) < TOL["fp32"]
     _compare({n: host(t) for n, t in g.items()}, _adjoint(d), TOL["fp32"])
+
+
+@pytest.mark.parametrize("large", ["dout", "q"])
+@pytest.mark.parametrize("per_token", [3.0, 4.7, 5.3, 8.0])
+def test_fp32_decayed_blocks_with_large_operands(per_token, large):
+    """Some channels decay by e^45 (split at the block's ends), e^70 and e^80 (at its middle) and
+    e^120 (element by element) within a 16-row block, and an operand that the sums are formed of is
+    2^36 times the usual: scaling by a power of two is exact, so the results are 2^36 times those of
+    the usual one, all finite."""
+    import paper_2605_22791_amd as g2
+    d = make_inputs(1, 130, 2, 64, 128, seed=410, dtype="fp32", s0_std=0.05, with_dST=True)
+    d["log_alpha"][..., ::5] = -per_token
+    _case(f"fp32 decay {per_token} a token on some channels, {large} x 2^36")
+
+    def run(e):
+        big = dict(d, dST=np.ldexp(d["dST"], e))
+        n = "do" if large == "dout" else "q"
+        big[n] = np.ldexp(d[n], e)
+        x = dev_inputs(big)
+        args = [x[m] for m in ("q", "k", "v", "log_alpha", "b", "w")]
+        out = {m: host(t) for m, t in g2.gdr2_chunk_bwd(*args, x["S0"], x["do"], x["dST"], scale=d["scale"]).items()}
+        out["o"] = host(g2.gdr2_chunk_fwd(*args, x["S0"], scale=d["scale"])[0])
+        return out
+
+    one, two = run(0), run(36)
+    for n in one:
+        assert np.all(np.isfinite(two[n])), n
+        e = 0 if n == ("o" if large == "dout" else "dq") else 36
+        err = rel_l2(np.ldexp(two[n], -e), one[n])
+        assert err < 1e-6, (n, err)   # (what is left: values below 1e-38 in the smaller problem)
+    ref = _adjoint(d)
+    for n, r in (("dq", "dq"), ("dk", "dk"), ("dv", "dv"), ("db", "db"), ("dw", "dw"), ("dS0", "dS0")):
+        err = rel_l2(one[n], ref[r])
+        assert err < TOL["fp32"], (n, err)
+    check_decay_grad(one["dlog_alpha"], ref["dg"], decay_terms(d, ref), np.arange(64) % 5 == 0, TOL["fp32"])

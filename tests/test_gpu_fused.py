@@ -124,9 +124,11 @@ def test_fused_diagonal_block_bounds(Dk, per_token):
     _check(_run(d), _oracle(d), TOL["bf16"], names=("o", "S_T", "dq", "dk", "dv", "db", "dw", "dS0"))
 
 
-@pytest.mark.parametrize("per_token", [4.5, 5.1, 5.4])
+@pytest.mark.parametrize("per_token", [3.9, 4.1, 4.5, 5.1, 5.4, 7.4, 7.6])
 def test_fused_fp32_diagonal_block_bound(per_token):
-    """fp32: decay of some channels within a 16-row block below and above the bound of e^78."""
+    """fp32: decay of some channels within a 16-row block (15 steps) below and above the e^60 of the
+    split at its ends, and within a half of it (8 steps) below and above the e^60 of the split at its
+    middle row."""
     d = make_fused(1, 100, 2, 64, 128, seed=331, dtype="fp32", s0_std=0.05, with_dST=True)
     d["a"] = np.zeros_like(d["a"])
     f = np.full(d["f"].shape, -7.0, dtype=np.float32)
