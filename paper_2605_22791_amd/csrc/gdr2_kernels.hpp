@@ -31,11 +31,24 @@ __device__ __forceinline__ int ld_table(const int* p, int i) {
   return ((const __attribute__((address_space(4))) int*)p)[i];
 }
 
+// The table of a saved backward lies in the caller's workspace since the forward, and
+// a workspace that no forward filled must not lead out of the tensors: whatever the
+// entries hold, the functions below give chunks of [0, ncmax), sequences of [0, nseq)
+// and rows of [0, T) (a few scalar instructions a chunk; nothing else checks them).
+
 // Scanned pair (sequence, head) of a scan workgroup's index q: for packed
 // calls the sequences are taken longest first, so that the longest scans start
 // with the grid and the short ones fill in behind them.
 __device__ __forceinline__ int scan_pair(const Varlen& vl, int q, int H) {
-  return vl.sorder != nullptr ? ld_table(vl.sorder, q / H) * H + q % H : q;
+  if (vl.sorder == nullptr) return q;
+  return (int)min((unsigned)ld_table(vl.sorder, q / H), (unsigned)vl.nseq - 1) * H + q % H;
+}
+
+// First token row and rows in use of chunk c of the table.
+__device__ __forceinline__ void table_rows(const Varlen& vl, int c, int T, size_t& row0, int& len) {
+  const int t0 = (int)min((unsigned)ld_table(vl.ct0, c), (unsigned)T - 1);
+  row0 = (size_t)t0;
+  len = min(max(ld_table(vl.clen, c), 1), min(CH, T - t0));
 }
 
 struct ChunkPos {
@@ -50,8 +63,7 @@ __device__ __forceinline__ bool chunk_pos(const Varlen& vl, int x, int h, int bb
                                           ChunkPos& p) {
   if (vl.ct0 != nullptr) {
     if (x >= ld_table(vl.coff, vl.nseq)) return false;
-    p.row0 = (size_t)ld_table(vl.ct0, x);
-    p.len = ld_table(vl.clen, x);
+    table_rows(vl, x, T, p.row0, p.len);
     p.ch = (size_t)h * vl.ncmax + x;
   } else {
     p.row0 = (size_t)bb * T + (size_t)x * CH;
@@ -85,14 +97,16 @@ struct ScanRange {
   int c0, c1;
 };
 __device__ __forceinline__ ScanRange scan_range(const Varlen& vl, int q, int H, int NT) {
-  if (vl.coff != nullptr) return {(size_t)(q % H) * vl.ncmax, ld_table(vl.coff, q / H), ld_table(vl.coff, q / H + 1)};
+  if (vl.coff != nullptr) {
+    const int c0 = (int)min((unsigned)ld_table(vl.coff, q / H), (unsigned)vl.ncmax);
+    return {(size_t)(q % H) * vl.ncmax, c0, min(max(ld_table(vl.coff, q / H + 1), c0), vl.ncmax)};
+  }
   return {(size_t)q * NT, 0, NT};
 }
 // First token row and rows in use of chunk c of the scanned pair q.
 __device__ __forceinline__ void scan_rows(const Varlen& vl, int q, int H, int T, int c, size_t& row0, int& len) {
   if (vl.ct0 != nullptr) {
-    row0 = (size_t)ld_table(vl.ct0, c);
-    len = ld_table(vl.clen, c);
+    table_rows(vl, c, T, row0, len);
   } else {
     row0 = (size_t)(q / H) * T + (size_t)c * CH;
     len = min(CH, T - c * CH);

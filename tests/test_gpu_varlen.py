@@ -219,3 +219,42 @@ def test_chunk_table_passes(lengths):
     assert np.array_equal(region("clen")[:off[-1]], np.minimum(64, np.repeat(L, n) - 64 * first))
     order = region("sorder")[:N]
     assert np.array_equal(np.sort(order), np.arange(N)) and np.all(np.diff(n[order]) <= 0)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("entry", [0x7FFFFFFF, -1, -2 ** 31, 1000])
+def test_saved_backward_on_a_foreign_workspace(dtype, entry):
+    """A saved backward takes its chunk table from the workspace.  One that no forward has filled gives
+    undefined gradients, but whatever the table's entries are, nothing outside the tensors is written, and
+    the forward that fills it makes the next backward right."""
+    import torch
+    import paper_2605_22791_amd as g2
+    lengths = [70, 0, 130, 64, 5]
+    d = make_packed(lengths, 2, 64, 64, seed=131, dtype=dtype, s0_std=0.05, with_dST=True)
+    x = dev_inputs(d)
+    cu = torch.from_numpy(d["cu_seqlens"]).cuda()
+    args = [x[n] for n in ("q", "k", "v", "log_alpha", "b", "w")]
+    need = g2.gdr2_varlen_workspace_bytes(g2._problem(x["q"], x["v"], d["scale"]), len(lengths), 1)
+    guard = 1 << 16
+    room = torch.full((need + 2 * guard,), 0x5A, dtype=torch.uint8, device="cuda")
+    ws = room[guard:guard + need]
+    shapes = {"dq": x["q"], "dk": x["k"], "dv": x["v"], "dlog_alpha": x["log_alpha"], "db": x["b"], "dw": x["w"],
+              "dS0": x["S0"]}
+    bufs = {n: torch.full((t.numel() + 2 * guard,), 3.0, dtype=t.dtype, device="cuda") for n, t in shapes.items()}
+    grads = {n: bufs[n][guard:guard + t.numel()].view(t.shape) for n, t in shapes.items()}
+    _case(f"saved backward on a workspace of {entry}, {dtype}")
+
+    def bwd():
+        return g2.gdr2_chunk_bwd_varlen(*args, cu, x["S0"], x["do"], x["dST"], scale=d["scale"], ws=ws, saved=True,
+                                        grads=dict(grads))
+
+    ws.view(torch.int32).fill_(entry)
+    bwd()
+    torch.cuda.synchronize()
+    assert bool((room[:guard] == 0x5A).all()) and bool((room[guard + need:] == 0x5A).all())
+    for n, t in bufs.items():
+        assert bool((t[:guard] == 3.0).all()) and bool((t[-guard:] == 3.0).all()), n
+    o, ST = g2.gdr2_chunk_fwd_varlen(*args, cu, x["S0"], scale=d["scale"], ws=ws, save=True)
+    got = {n: host(t) for n, t in bwd().items()}
+    got.update(o=host(o), S_T=host(ST))
+    _compare(got, oracle_packed(d), TOL[dtype])
