@@ -217,12 +217,12 @@ def decode_u_tiles(raw_f32, Dv):
 
 
 # --------------------------------------------------------------------------- sequence-parallel scans
-def scan_segments(B, T, H, Dv, dtype="bf16"):
-    """(nseg, seg_len) the library picks for its state scans (mirrors its rule:
-    bf16 problems with fewer than 128 (sequence, 64-wide value slice) scans and
-    at least 16 chunks double the segments while the grid stays within 256
+def segment_room(B, T, H, Dv, dtype="bf16"):
+    """(nseg, seg_len) that the workspace has room for (mirrors the library's
+    rule: bf16 problems with fewer than 128 (sequence, 64-wide value slice) scans
+    and at least 16 chunks double the segments while the grid stays within 256
     workgroups and a segment keeps 8 chunks or more)."""
-    NT = T // CH
+    NT = -(-T // CH)
     slices = B * H * (Dv // 64)
     n = 1
     if dtype == "bf16" and slices < 128 and NT >= 16:
@@ -232,9 +232,25 @@ def scan_segments(B, T, H, Dv, dtype="bf16"):
     return -(-NT // seg_len), seg_len
 
 
+def scan_segments(B, T, H, Dv, dtype="bf16"):
+    """(nseg, seg_len) that the state scans run: below 48 chunks a sequence is scanned whole."""
+    NT = -(-T // CH)
+    return segment_room(B, T, H, Dv, dtype) if NT >= 48 else (1, NT)
+
+
+def segments_ran(ws, B, H, T, Dk, Dv):
+    """Whether a call on ws, filled with 0xFF before it, wrote the segments' entry states (the last
+    region of the workspace)."""
+    nvs = B * H * segment_room(B, T, H, Dv)[0]
+    X = ws[ws.numel() - (nvs * Dk * Dv * 4 + 255) // 256 * 256:][:nvs * Dk * Dv * 4]
+    n = int((X != 0xFF).sum())
+    assert n == 0 or n > X.numel() // 2, n
+    return n > 0
+
+
 def seg_buffer_bytes(B, T, H, Dk, Dv, dtype="bf16"):
-    """Workspace bytes of the segment maps M, N and entry states X (0 if unsegmented)."""
-    nseg, _ = scan_segments(B, T, H, Dv, dtype)
+    """Workspace bytes of the segment maps M, N and entry states X (0 without room for segments)."""
+    nseg, _ = segment_room(B, T, H, Dv, dtype)
     if nseg == 1:
         return 0
     r = lambda n: (n * 4 + 255) // 256 * 256

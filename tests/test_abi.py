@@ -232,11 +232,11 @@ def test_saved_training_path_validation():
 def test_workspace_segment_buffers():
     """bf16 problems with few scans and long sequences get the segment maps of
     the sequence-parallel scans appended to the workspace; others do not."""
-    from tests.gpu_common import ws_layout_bf16, seg_buffer_bytes, scan_segments
-    assert scan_segments(1, 65536, 16, 128) == (8, 128)
-    assert scan_segments(8, 4096, 16, 128) == (1, 64)
-    assert scan_segments(1, 640, 2, 128) == (1, 10)
-    assert scan_segments(1, 3200, 2, 64) == (4, 13)
+    from tests.gpu_common import ws_layout_bf16, seg_buffer_bytes, segment_room
+    assert segment_room(1, 65536, 16, 128) == (8, 128)
+    assert segment_room(8, 4096, 16, 128) == (1, 64)
+    assert segment_room(1, 640, 2, 128) == (1, 10)
+    assert segment_room(1, 3200, 2, 64) == (4, 13)
     for (B, T, H, Dk, Dv) in [(1, 3200, 2, 128, 64), (1, 4096, 4, 64, 128), (2, 1024, 4, 128, 128),
                               (8, 4096, 16, 128, 128), (1, 640, 2, 64, 64)]:
         p = _prob(B=B, T=T, H=H, Dk=Dk, Dv=Dv)

@@ -100,12 +100,12 @@ def test_grouped_segmented_scans_grouped_on_xcds():
 
 
 def test_grouped_long_sequence_parallel_scans():
-    """B1 H1 Hv2 T2048: few scans and long sequences switch the sequence-parallel scans on."""
+    """B1 H1 Hv2 T3200: few scans and long sequences switch the sequence-parallel scans on."""
     from tests.gpu_common import scan_segments
-    assert scan_segments(1, 2048, 2, 128)[0] > 1
-    d = make_grouped(1, 2048, 1, 2, 128, 128, seed=147, dtype="bf16", decay_shift=-2.0, s0_std=0.05,
+    assert scan_segments(1, 3200, 2, 128)[0] > 1
+    d = make_grouped(1, 3200, 1, 2, 128, 128, seed=147, dtype="bf16", decay_shift=-2.0, s0_std=0.05,
                      with_dST=True)
-    _case("grouped bf16 B1 T2048 H1 Hv2, segmented scans")
+    _case("grouped bf16 B1 T3200 H1 Hv2, segmented scans")
     _check(_run(d), _oracle(d), TOL["bf16"])
 
 

@@ -17,8 +17,8 @@ from oracle import gdr2_recurrent_bwd, gdr2_recurrent_fwd
 from oracle.chunkwise import gdr2_chunk_fwd_ref
 from paper_2605_22791_amd.inputs import make_inputs
 from tests.helpers import rel_l2
-from tests.gpu_common import dev_inputs, host, scan_segments, seg_buffer_bytes, ws_layout_bf16, CH, \
-    decode_states_f16
+from tests.gpu_common import dev_inputs, host, scan_segments, seg_buffer_bytes, segments_ran, \
+    ws_layout_bf16, CH, decode_states_f16
 
 pytestmark = pytest.mark.gpu
 
@@ -72,9 +72,9 @@ def test_segmented_saved_path_and_chunk_states():
     (the rescan's states across segment boundaries) match the oracle's."""
     import torch
     import paper_2605_22791_amd as g2
-    B, T, H, Dk, Dv = 1, 2048, 2, 128, 128
+    B, T, H, Dk, Dv = 1, 3200, 2, 128, 128
     nseg, seg_len = scan_segments(B, T, H, Dv)
-    assert nseg == 4 and seg_len == 8
+    assert nseg == 4 and seg_len == 13
     d = make_inputs(B, T, H, Dk, Dv, seed=95, dtype="bf16", decay_shift=-3.0, s0_std=0.05, with_dST=True)
     x = dev_inputs(d)
     prob = g2._problem(x["q"], x["v"], d["scale"])
@@ -85,6 +85,7 @@ def test_segmented_saved_path_and_chunk_states():
     _case(f"segmented saved path B{B} H{H} T{T} nseg {nseg}")
     o_s, S_s, g_s = _fwd_bwd(d, ws=ws, save=True)
     torch.cuda.synchronize()
+    assert segments_ran(ws, B, H, T, Dk, Dv)
     off, per = lay["Hs"]
     soff, sper = lay["Hsc"]
     NT = T // CH
@@ -105,8 +106,8 @@ def test_segmented_saved_path_and_chunk_states():
     _check(d, o_s, S_s, g_s)
 
 
-@pytest.mark.parametrize("T,H", [(47 * 64 + 1, 2), (56 * 64, 3), (3072 - 64, 1)])
-def test_segment_use_bound(T, H):
+@pytest.mark.parametrize("T,H,cut", [(47 * 64 + 1, 2, True), (56 * 64, 3, True), (3072 - 64, 1, False)])
+def test_segment_use_bound(T, H, cut):
     """The shortest sequences that are cut into segments (48 chunks) and the longest that are not,
     on the stored path, bit-identical to the recomputing one."""
     import torch
@@ -114,8 +115,10 @@ def test_segment_use_bound(T, H):
     d = make_inputs(1, T, H, 128, 128, seed=96 + H, dtype="bf16", decay_shift=-3.0, s0_std=0.05, with_dST=True)
     x = dev_inputs(d)
     nbytes = g2.gdr2_chunk_workspace_bytes(g2._problem(x["q"], x["v"], d["scale"]), 1)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
     _case(f"segments at their bound T{T} H{H}")
-    o, ST, g = _fwd_bwd(d, ws=torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda"), save=True)
+    o, ST, g = _fwd_bwd(d, ws=ws, save=True)
+    assert (scan_segments(1, T, H, 128)[0] > 1) == cut == segments_ran(ws, 1, H, T, 128, 128)
     o_r, S_r, g_r = _fwd_bwd(d)
     assert np.array_equal(o, o_r) and np.array_equal(ST, S_r)
     for n in GRADS:

@@ -41,8 +41,8 @@ def _one(B, T, H, Dk, Dv, seed):
 
 
 def test_noalloc_forward_two_calls_second_smaller():
-    assert scan_segments(1, 2100, 4, 128)[0] > 1
-    _one(1, 2100, 4, 128, 128, seed=91)
+    assert scan_segments(1, 3100, 4, 128)[0] > 1
+    _one(1, 3100, 4, 128, 128, seed=91)
     _one(2, 300, 2, 64, 64, seed=92)
 
 
