@@ -180,3 +180,88 @@ def test_narrow_scans_equal_wide(Dk, Dv, T):
                 w = wide[n]
                 w = w[2:3, h0:h0 + nh] if n in ("S_T", "dS0") else w[2:3, :, h0:h0 + nh]
                 assert torch.equal(t, w), (n, h0, save)
+
+
+STATES = ("S0", "S_T", "dST", "dS0")
+VALUE_SIDE = ("v", "w", "o", "do", "dv", "dw")
+
+
+def _device_problem(B, T, H, Hv, Dk, Dv, seed, states):
+    """A bf16 problem drawn on the device (S0 and dST for `states` sequences)."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    nrm = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    unit = lambda t: (t / t.norm(dim=-1, keepdim=True)).bfloat16()
+    return {"q": unit(nrm(B, T, H, Dk)), "k": unit(nrm(B, T, H, Dk)), "v": nrm(B, T, Hv, Dv).bfloat16(),
+            "log_alpha": -torch.nn.functional.softplus(nrm(B, T, H, Dk) - 2.0),
+            "b": torch.sigmoid(nrm(B, T, H, Dk)).bfloat16(), "w": torch.sigmoid(nrm(B, T, Hv, Dv)).bfloat16(),
+            "S0": 0.05 * nrm(states, Hv, Dk, Dv), "do": nrm(B, T, Hv, Dv).bfloat16(), "dST": nrm(states, Hv, Dk, Dv)}
+
+
+def _fwd_bwd_device(x, save, cu=None):
+    import torch
+    import paper_2605_22791_amd as g2
+    args = [x[n] for n in ("q", "k", "v", "log_alpha", "b", "w")]
+    prob = g2._problem(x["q"], x["v"], None)
+    need = g2.gdr2_chunk_workspace_bytes(prob, 1) if cu is None else \
+        g2.gdr2_varlen_workspace_bytes(prob, cu.numel() - 1, 1)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    if cu is None:
+        o, ST = g2.gdr2_chunk_fwd(*args, x["S0"], ws=ws, save=save)
+        g = g2.gdr2_chunk_bwd(*args, x["S0"], x["do"], x["dST"], ws=ws, saved=save)
+    else:
+        o, ST = g2.gdr2_chunk_fwd_varlen(*args, cu, x["S0"], ws=ws, save=save)
+        g = g2.gdr2_chunk_bwd_varlen(*args, cu, x["S0"], x["do"], x["dST"], ws=ws, saved=save)
+    return {"o": o, "S_T": ST, **g}
+
+
+# more than 512 wide scans; at most 512, of more than 32 chunks for each of 256 compute units;
+# the same with Dk = 64 and grouped value heads
+@pytest.mark.parametrize("H,Hv,Dk,Dv,lengths", [
+    (16, 16, 128, 128, [70, 0, 130, 64, 5, 300, 1, 200, 128, 0, 65, 63, 90, 33, 250, 77, 140, 12]),
+    (8, 16, 64, 128, [1300, 1984, 40, 0, 2500, 64, 1700, 2049, 800, 1900, 1, 2300, 2500]),
+    (16, 16, 128, 128, [2048, 1, 2047, 2000, 1999, 2100, 0, 2050, 2048, 2113])])
+def test_packed_wide_scans_equal_narrow(H, Hv, Dk, Dv, lengths):
+    """The 64-wide scans over a chunk table (empty sequences, partial chunks) give the bits that two of
+    the sequences give in a batch of their own, whose few heads take the 32-wide scans."""
+    import torch
+    T, N, G = sum(lengths), len(lengths), Hv // H
+    x = _device_problem(1, T, H, Hv, Dk, Dv, 600 + N, N)
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    slots = T // 64 + N
+    per_seq = Hv * Dv // 64
+    assert N * per_seq > 512 or slots * per_seq > 32 * 256   # the wide route whatever the lengths are
+    _case(f"packed wide scans H{H} Hv{Hv} Dk{Dk} Dv{Dv}, {N} sequences, T = {T}")
+    cu = torch.from_numpy(off).cuda()
+    for save in (True, False):
+        wide = _fwd_bwd_device(x, save, cu)
+        for seqs, heads in (((2, 4), slice(0, 1)), ((0, N - 1), slice(H - 3, H))):
+            assert len(seqs) * 3 * G * Dv // 64 <= 128
+            rows = torch.cat([torch.arange(off[s], off[s + 1]) for s in seqs]).cuda()
+            vheads = slice(heads.start * G, heads.stop * G)
+            side = lambda n, t: (t[list(seqs)][:, vheads] if n in STATES else
+                                 t[:, rows][:, :, vheads if n in VALUE_SIDE else heads]).contiguous()
+            few = torch.tensor([0] + list(np.cumsum([lengths[s] for s in seqs])), dtype=torch.int32, device="cuda")
+            for n, t in _fwd_bwd_device({n: side(n, t) for n, t in x.items()}, save, few).items():
+                assert torch.equal(t, side(n, wide[n])), (n, seqs, save)
+
+
+@pytest.mark.parametrize("H", [8, 7])
+@pytest.mark.parametrize("Dk,Dv", [(128, 128), (64, 64)])
+def test_grouped_wide_scans_equal_narrow(H, Dk, Dv):
+    """Grouped value heads on the unsegmented 64-wide scans, with a multiple of eight (sequence, key head)
+    units (placed by XCD) and without: the bits of one sequence's three key heads alone."""
+    import torch
+    B, G, T = 9, 2 * 128 // Dv, 150
+    Hv = G * H
+    assert B * Hv * Dv // 64 > 128 and ((B * H) % 8 == 0) == (H == 8)
+    x = _device_problem(B, T, H, Hv, Dk, Dv, 620 + H + Dk, B)
+    _case(f"grouped wide scans B{B} H{H} Hv{Hv} Dk{Dk} Dv{Dv}")
+    side = lambda n, t: (t[2:3, 3 * G:6 * G] if n in STATES else
+                         t[2:3, :, 3 * G:6 * G] if n in VALUE_SIDE else t[2:3, :, 3:6]).contiguous()
+    few = {n: side(n, t) for n, t in x.items()}
+    for save in (True, False):
+        wide = _fwd_bwd_device(x, save)
+        for n, t in _fwd_bwd_device(few, save).items():
+            assert torch.equal(t, side(n, wide[n])), (n, save)
