@@ -62,11 +62,13 @@ def decay_terms(x, g):
 
 
 def check_decay_grad(got, want, terms, fast, tol):
-    """Channels that decay slowly at the relative tolerance; `fast` ones against the terms of their sum."""
+    """Channels that decay slowly at the relative tolerance; `fast` ones against the terms of their sum, at
+    a twentieth of it: a term is good to 2^-11 (the fp16 copies of a bf16 problem) or some 2^-23 (fp32),
+    and over the 64 rows of a chunk such errors add to an eighth of that of the terms' sum."""
     slow = rel(got[..., ~fast], want[..., ~fast])
     err = np.linalg.norm((got - want)[..., fast]) / np.linalg.norm(terms[..., fast])
     print(f"decay gradient: slow channels {slow:.1e}, fast ones over their terms {err:.1e}")
-    assert slow < tol and err < tol, (slow, err)
+    assert slow < tol and err < tol / 20, (slow, err)
 
 
 def ws_layout(B, T, H, Dk, Dv, bwd):

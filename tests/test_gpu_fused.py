@@ -13,10 +13,11 @@ its adjoint.  Tolerances as elsewhere: rel-L2 2e-3 (bf16), 1e-5 (fp32).
 import numpy as np
 import pytest
 
+from oracle import gdr2_recurrent_bwd
 from oracle.layer import gdr2_fused_bwd, gdr2_fused_fwd
 from paper_2605_22791_amd.inputs import make_fused
 from tests.helpers import rel_l2
-from tests.gpu_common import host
+from tests.gpu_common import check_decay_grad, decay_terms, host
 
 pytestmark = pytest.mark.gpu
 
@@ -105,6 +106,27 @@ def test_fused_strong_decay_diagonal_blocks():
     _check(_run(d), _oracle(d), TOL["bf16"])
 
 
+NO_DECAY = ("o", "S_T", "dq", "dk", "dv", "db", "dw", "dS0")
+
+
+def _check_decay_side(d, got, ref, fast, tol):
+    """df and ddelta: slow channels at the tolerance, the fast ones, whose sums cancel, against the terms
+    of their sums (the gradients of the normalised q, k and of b, from the recurrence); da likewise, a sum
+    over all channels."""
+    unit = lambda x: x / np.sqrt((x.astype(np.float64) ** 2).sum(-1, keepdims=True) + d["eps"])
+    A = np.exp(d["a"].astype(np.float64))[:, None]
+    z = d["f"].astype(np.float64) + d["delta"]
+    g = -A * np.logaddexp(0.0, z)
+    x = {"q": unit(d["q"]), "k": unit(d["k"]), "b": d["b"].astype(np.float64)}
+    r = gdr2_recurrent_bwd(x["q"], x["k"], d["v"], g, x["b"], d["w"], d["S0"], d["do"], d["dST"], d["scale"])
+    terms = decay_terms(x, r)
+    df = terms * A / (1.0 + np.exp(-z))
+    check_decay_grad(got["df"], ref["df"], df, fast, tol)
+    check_decay_grad(got["ddelta"], ref["ddelta"], df.sum(axis=(0, 1)), fast, tol)
+    err = np.abs(got["da"] - ref["da"]) / np.abs(terms * g).sum(axis=(0, 1, 3))
+    assert np.all(err < tol / 20), err
+
+
 @pytest.mark.parametrize("Dk", [64, 128])
 @pytest.mark.parametrize("per_token", [5.0, 7.4, 7.6, 30.0])
 def test_fused_diagonal_block_bounds(Dk, per_token):
@@ -119,9 +141,11 @@ def test_fused_diagonal_block_bounds(Dk, per_token):
     d["f"] = f
     d["delta"] = np.zeros_like(d["delta"])
     _case(f"fused bf16 B1 T150 H2 Dk{Dk}, {per_token} a token on some channels")
-    # df of the fast channels is a sum that cancels to a part in e^-decay of its terms: o, S_T, and the
-    # gradients that do not run through the decay
-    _check(_run(d), _oracle(d), TOL["bf16"], names=("o", "S_T", "dq", "dk", "dv", "db", "dw", "dS0"))
+    got, ref = _run(d), _oracle(d)
+    _check(got, ref, TOL["bf16"], names=NO_DECAY)
+    fast = np.zeros(Dk, dtype=bool)
+    fast[::5] = fast[3] = True
+    _check_decay_side(d, got, ref, fast, TOL["bf16"])
 
 
 @pytest.mark.parametrize("per_token", [3.9, 4.1, 4.5, 5.1, 5.4, 7.4, 7.6])
@@ -135,7 +159,9 @@ def test_fused_fp32_diagonal_block_bound(per_token):
     f[..., ::5] = per_token
     d["f"], d["delta"] = f, np.zeros_like(d["delta"])
     _case(f"fused fp32 B1 T100 H2, {per_token} a token on some channels")
-    _check(_run(d), _oracle(d), TOL["fp32"], names=("o", "S_T", "dq", "dk", "dv", "db", "dw", "dS0"))
+    got, ref = _run(d), _oracle(d)
+    _check(got, ref, TOL["fp32"], names=NO_DECAY)
+    _check_decay_side(d, got, ref, np.arange(64) % 5 == 0, TOL["fp32"])
 
 
 def test_fused_grouped_value_heads():
