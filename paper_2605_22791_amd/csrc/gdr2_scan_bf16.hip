@@ -70,18 +70,18 @@ struct ScanCfg2 {
 
 // Map pass: element (row v, key c) of S^T in LDS, keys in the permuted order of
 // Y's fragments (4 m + e and 16 + 4 m + e side by side at 8 m + e, 8 m + 4 + e
-// of each 32-key group) and the 16-byte pieces of a row XOR'd with v % 16, so
-// that Y's B fragment is one 16-byte read and those reads are free of bank
-// conflicts.  c4 is a multiple of 4: the 4 keys c4 .. c4 + 3 stay together.
+// of each 32-key group) and the LD / 8 16-byte pieces of a row XOR'd with v modulo
+// their number, so that Y's B fragment is one 16-byte read and those reads are free
+// of bank conflicts.  c4 is a multiple of 4: the 4 keys c4 .. c4 + 3 stay together.
 template <int LD>
 __device__ __forceinline__ int map_s_ix(int v, int c4) {
   const int a = (c4 & 31) >> 2, pos = (c4 & ~31) + (a < 4 ? 8 * a : 8 * (a - 4) + 4);
-  return v * LD + ((((pos >> 3) ^ (v & 15)) << 3) | (pos & 7));
+  return v * LD + ((((pos >> 3) ^ (v & (LD / 8 - 1))) << 3) | (pos & 7));
 }
 // its B fragment for K-step p: keys 32 p + 4 g + (0..3) and 32 p + 16 + 4 g + (0..3)
 template <int LD>
 __device__ __forceinline__ int map_s_frag(int v, int p, int g) {
-  return v * LD + (((4 * p + g) ^ (v & 15)) << 3);
+  return v * LD + (((4 * p + g) ^ (v & (LD / 8 - 1))) << 3);
 }
 
 // B fragment of S for Y S in the permuted key order of Y's fragments:

@@ -66,16 +66,18 @@ def test_segmented_scans_match_oracle(Dk, Dv):
     _check(d, *_fwd_bwd(d))
 
 
-def test_segmented_saved_path_and_chunk_states():
+@pytest.mark.parametrize("D,shift", [(128, -3.0), (64, -3.0), (64, -6.0), (128, -6.0)])
+def test_segmented_saved_path_and_chunk_states(D, shift):
     """Saving forward + saved backward under segmentation: bit-identical to the
     recomputing backward, and the chunk-start states it leaves in the workspace
-    (the rescan's states across segment boundaries) match the oracle's."""
+    (the rescan's states across segment boundaries) match the oracle's; also with a
+    decay so slow (shift -6: e^-2 over a segment) that the maps carry over several of them."""
     import torch
     import paper_2605_22791_amd as g2
-    B, T, H, Dk, Dv = 1, 3200, 2, 128, 128
+    B, T, H, Dk, Dv = 1, 3200, 2, D, D
     nseg, seg_len = scan_segments(B, T, H, Dv)
     assert nseg == 4 and seg_len == 13
-    d = make_inputs(B, T, H, Dk, Dv, seed=95, dtype="bf16", decay_shift=-3.0, s0_std=0.05, with_dST=True)
+    d = make_inputs(B, T, H, Dk, Dv, seed=95, dtype="bf16", decay_shift=shift, s0_std=0.05, with_dST=True)
     x = dev_inputs(d)
     prob = g2._problem(x["q"], x["v"], d["scale"])
     lay, total, NC = ws_layout_bf16(B, T, H, Dk, Dv, bwd=True)
@@ -94,11 +96,15 @@ def test_segmented_saved_path_and_chunk_states():
     _, _, it = gdr2_chunk_fwd_ref(d["q"], d["k"], d["v"], d["log_alpha"], d["b"], d["w"], d["S0"],
                                   d["scale"], C=CH, keep=True)
     err_h = rel_l2(Hs, it["h"])
-    print("chunk states rel", f"{err_h:.2e}")
+    # (the worst value column of a segment's first state shows a map that is wrong in a few of them)
+    first = slice(seg_len, None, seg_len)
+    col = np.sqrt(((Hs - it["h"])[:, :, first] ** 2).sum(axis=(0, 1, 3)) / (it["h"][:, :, first] ** 2).sum(axis=(0, 1, 3)))
+    print("chunk states rel", f"{err_h:.2e}", "worst column of a segment's first", f"{col.max():.2e}")
     # the copies are fp16 with one power-of-two scale per 16 x 32 block that puts
     # the block's largest value in [2^14, 2^15): 11 significant bits each, about
     # 1.5e-4 rel-L2 over the states; a scale off by 2^k would show as 2^k times that
-    assert err_h < 4e-4
+    # (at shift -6 the states gather 50 chunks of Y S products, whose Y and S are bf16: the path's bound)
+    assert err_h < (4e-4 if shift == -3.0 else TOL) and col.max() < TOL
     o_r, S_r, g_r = _fwd_bwd(d)
     assert np.array_equal(o_s, o_r) and np.array_equal(S_s, S_r)
     for n in GRADS:
