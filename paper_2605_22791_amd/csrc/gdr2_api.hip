@@ -78,14 +78,6 @@ struct Layout {
   size_t total;
 };
 
-// Sequences of fewer chunks than this are scanned whole, in narrow slices
-// (narrow_scan): two passes over the segments and the chain between cost more than
-// one walk of 1.8 us a chunk.  One sequence, 16 heads, 128 x 128, whole / segmented:
-// 16 chunks 52 / 94 us forward, 156 / 230 training; 32 chunks 88 / 114, 263 / 276;
-// 64 chunks 188 / 194, 506 / 476 (with an intra-chunk kernel that took 4 us more at
-// 16 chunks than it does now, on either side).
-constexpr int kSegmentChunks = 48;
-
 constexpr int kParamSplits = 64;  // slot ranges of the first decay-parameter reduction pass
 
 // Sequence-parallel scans (bf16 path).  The state scans run one workgroup per
@@ -96,8 +88,8 @@ constexpr int kParamSplits = 64;  // slot ranges of the first decay-parameter re
 // are doubled while the scan grid stays within one workgroup per compute unit
 // and a segment keeps at least 8 chunks.  The rule depends on the problem's
 // shape alone, so a problem always runs the same schedule (and rounds the same
-// way).  The workspace has the segments' regions from 16 chunks on; kSegmentChunks
-// says from where they are used.
+// way).  The workspace has the segments' regions from 16 chunks on; segments_pay
+// says where they are used.
 void scan_segments(const gdr2_problem* p, int& nseg, int& seg_len) {
   const int NT = chunks_per_seq(p);
   const long long slices = (long long)p->B * p->H * (p->Dv / 64);
@@ -107,6 +99,26 @@ void scan_segments(const gdr2_problem* p, int& nseg, int& seg_len) {
   }
   seg_len = (NT + n - 1) / n;
   nseg = (NT + seg_len - 1) / seg_len;
+}
+
+// Whether sequences with room for nseg segments are scanned in them or whole, in
+// narrow slices (narrow_scan).  Segments walk every chunk twice, in wide slices, with
+// the chain between; whole, a scan is one walk of 1.8 to 3 us a chunk.  A forward and
+// the saving one take the same route, so one line serves both: forward + training in
+// us, whole / segmented (B x 16 heads),
+//   128 x 128  8 segments: 64 chunks 150 + 512 / 146 + 390, 120 chunks 347 + 975 / 248 + 660
+//              4 (B = 2):  32 chunks 105 + 357 / 136 + 371, 56 227 + 647 / 220 + 598
+//              4 (B = 1):  47 chunks 113 + 373 / 141 + 377, 56 135 + 457 / 165 + 431
+//              2 (B = 3):  64 chunks 303 + 889 / 387 + 1044, 200 906 + 2625 / 1144 + 3018
+//   64 x 64    4 (B = 1):  32 chunks 52 + 166 / 62 + 154, 47 74 + 240 / 86 + 214 (at so few
+//              pairs a forward alone, one user's prompt, is the more frequent call)
+//              4 (B = 3):  47 chunks 121 + 392 / 141 + 369, 56 170 + 474 / 168 + 428
+//              2 (B = 5):  64 chunks 256 + 702 / 321 + 799
+// With Dk != Dv the two maps of a segment take a launch each way and four do not pay:
+//   64 x 128   4 (B = 2): 56 chunks 130 + 430 / 161 + 441, 300 730 + 2103 / 783 + 2048; 8 (B = 1): 64 100 + 335 / 99 + 281
+//   128 x 64   4 (B = 3): 56 chunks 267 + 728 / 288 + 815, 200 855 + 2379 / 997 + 2630; 8 (B = 2): 64 250 + 665 / 229 + 622
+bool segments_pay(const gdr2_problem* p, int nseg) {
+  return nseg >= (p->Dk == p->Dv ? 4 : 8) && chunks_per_seq(p) >= 48;
 }
 
 // p: the value view (value_view); G > 1 adds the backward's group partials;
@@ -263,7 +275,7 @@ Geo make_geo(const gdr2_problem* p, bool bwd, int nseq, const int* cu, void* ws,
   Geo G{};
   G.G = grp;
   G.L = layout(p, bwd, nseq, grp, stage != nullptr);
-  if (nseq == 0 && chunks_per_seq(p) < kSegmentChunks) G.L.nseg = 1;
+  if (!segments_pay(p, G.L.nseg)) G.L.nseg = 1;
   if (stage != nullptr) {
     G.st.a_log = stage->a_log;
     G.st.delta = stage->delta;

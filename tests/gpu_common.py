@@ -234,10 +234,12 @@ def segment_room(B, T, H, Dv, dtype="bf16"):
     return -(-NT // seg_len), seg_len
 
 
-def scan_segments(B, T, H, Dv, dtype="bf16"):
-    """(nseg, seg_len) that the state scans run: below 48 chunks a sequence is scanned whole."""
+def scan_segments(B, T, H, Dv, dtype="bf16", Dk=128):
+    """(nseg, seg_len) that the state scans run: sequences of fewer than 48 chunks, or with room for
+    fewer segments than four (eight with Dk != Dv), are scanned whole."""
     NT = -(-T // CH)
-    return segment_room(B, T, H, Dv, dtype) if NT >= 48 else (1, NT)
+    nseg, seg_len = segment_room(B, T, H, Dv, dtype)
+    return (nseg, seg_len) if nseg >= (4 if Dk == Dv else 8) and NT >= 48 else (1, NT)
 
 
 def segments_ran(ws, B, H, T, Dk, Dv):

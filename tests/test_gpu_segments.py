@@ -17,7 +17,7 @@ from oracle import gdr2_recurrent_bwd, gdr2_recurrent_fwd
 from oracle.chunkwise import gdr2_chunk_fwd_ref
 from paper_2605_22791_amd.inputs import make_inputs
 from tests.helpers import rel_l2
-from tests.gpu_common import dev_inputs, host, scan_segments, seg_buffer_bytes, segments_ran, \
+from tests.gpu_common import dev_inputs, heads, host, pick, scan_segments, seg_buffer_bytes, segments_ran, \
     ws_layout_bf16, CH, decode_states_f16
 
 pytestmark = pytest.mark.gpu
@@ -53,12 +53,13 @@ def _check(d, o, ST, g):
         assert v < TOL, (k, v)
 
 
-@pytest.mark.parametrize("Dk,Dv", [(128, 128), (64, 128), (128, 64), (64, 64)])
-def test_segmented_scans_match_oracle(Dk, Dv):
-    # 50 chunks per head: 4 segments of 13, 13, 13 and 11 chunks
-    B, T, H = 1, 3200, 2
-    nseg, seg_len = scan_segments(B, T, H, Dv)
-    assert (nseg, seg_len) == (4, 13)
+@pytest.mark.parametrize("Dk,Dv,T", [(128, 128, 3200), (64, 128, 4150), (128, 64, 4150), (64, 64, 3100)])
+def test_segmented_scans_match_oracle(Dk, Dv, T):
+    # 50 chunks per head: 4 segments of 13, 13, 13 and 11 chunks; 65: 8 of 9, the last of 2;
+    # 49: 4 of 13, the last of 10
+    B, H = 1, 2
+    nseg, seg_len = scan_segments(B, T, H, Dv, Dk=Dk)
+    assert (nseg, seg_len) == {3200: (4, 13), 4150: (8, 9), 3100: (4, 13)}[T]
     with_state = Dk != 64 or Dv != 64   # the (64, 64) case starts and ends at zero
     d = make_inputs(B, T, H, Dk, Dv, seed=90 + Dk + Dv, dtype="bf16", decay_shift=-2.0,
                     s0_std=0.05 if with_state else 0.0, with_dST=with_state)
@@ -75,7 +76,7 @@ def test_segmented_saved_path_and_chunk_states(D, shift):
     import torch
     import paper_2605_22791_amd as g2
     B, T, H, Dk, Dv = 1, 3200, 2, D, D
-    nseg, seg_len = scan_segments(B, T, H, Dv)
+    nseg, seg_len = scan_segments(B, T, H, Dv, Dk=Dk)
     assert nseg == 4 and seg_len == 13
     d = make_inputs(B, T, H, Dk, Dv, seed=95, dtype="bf16", decay_shift=shift, s0_std=0.05, with_dST=True)
     x = dev_inputs(d)
@@ -112,21 +113,27 @@ def test_segmented_saved_path_and_chunk_states(D, shift):
     _check(d, o_s, S_s, g_s)
 
 
-@pytest.mark.parametrize("T,H,cut", [(47 * 64 + 1, 2, True), (56 * 64, 3, True), (3072 - 64, 1, False)])
-def test_segment_use_bound(T, H, cut):
-    """The shortest sequences that are cut into segments (48 chunks) and the longest that are not,
-    on the stored path, bit-identical to the recomputing one."""
+@pytest.mark.parametrize("T,H,Dk,Dv,cut", [
+    (47 * 64 + 1, 2, 128, 128, True), (56 * 64, 3, 128, 128, True), (3072 - 64, 1, 128, 128, False),
+    (47 * 64 + 1, 32, 64, 64, True), (47 * 64, 2, 64, 64, False),
+    (63 * 64, 2, 64, 128, False), (63 * 64 + 1, 2, 128, 64, True),
+    (48 * 64, 65, 64, 64, False)])   # (the last: room for two segments only)
+def test_segment_use_bound(T, H, Dk, Dv, cut):
+    """On both sides of the lines between segmented and whole scans, on the stored path, bit-identical to
+    the recomputing one; the first and the last head against the oracle."""
     import torch
     import paper_2605_22791_amd as g2
-    d = make_inputs(1, T, H, 128, 128, seed=96 + H, dtype="bf16", decay_shift=-3.0, s0_std=0.05, with_dST=True)
+    d = make_inputs(1, T, H, Dk, Dv, seed=96 + H, dtype="bf16", decay_shift=-3.0, s0_std=0.05, with_dST=True)
     x = dev_inputs(d)
     nbytes = g2.gdr2_chunk_workspace_bytes(g2._problem(x["q"], x["v"], d["scale"]), 1)
     ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
-    _case(f"segments at their bound T{T} H{H}")
+    _case(f"segments at their bounds T{T} H{H} Dk{Dk} Dv{Dv}")
     o, ST, g = _fwd_bwd(d, ws=ws, save=True)
-    assert (scan_segments(1, T, H, 128)[0] > 1) == cut == segments_ran(ws, 1, H, T, 128, 128)
+    assert (scan_segments(1, T, H, Dv, Dk=Dk)[0] > 1) == cut == segments_ran(ws, 1, H, T, Dk, Dv)
     o_r, S_r, g_r = _fwd_bwd(d)
     assert np.array_equal(o, o_r) and np.array_equal(ST, S_r)
     for n in GRADS:
         assert np.array_equal(g[n], g_r[n]), n
-    _check(d, o, ST, g)
+    pairs = [(0, 0), (0, H - 1)] if H > 1 else [(0, 0)]
+    _check(heads(d, pairs), pick(o, pairs), pick(ST, pairs, state=True),
+           {n: pick(t, pairs, state=n == "dS0") for n, t in g.items()})
