@@ -102,7 +102,7 @@ void scan_segments(const gdr2_problem* p, int& nseg, int& seg_len) {
 }
 
 // Whether sequences with room for nseg segments are scanned in them or whole, in
-// narrow slices (narrow_scan).  Segments walk every chunk twice, in wide slices, with
+// narrow slices (scan_slices).  Segments walk every chunk twice, in wide slices, with
 // the chain between; whole, a scan is one walk of 1.8 to 3 us a chunk.  A forward and
 // the saving one take the same route, so one line serves both: forward + training in
 // us, whole / segmented (B x 16 heads),
@@ -467,8 +467,7 @@ hipError_t scan_fwd_bf16(const ScanArgs& sa, const Layout& L, void* ws, Last&& l
 // forward phase of this backward (or the saving forward) left in sM: the map
 // pass of the reverse scan is then skipped.
 template <int DK, int DV>
-hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, bool narrow, hipStream_t st) {
-  if (L.nseg == 1) return launch_bscan_bf16<DK, DV>(ba, narrow, st);
+hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, hipStream_t st) {
   BScanArgs pn = ba;
   pn.dST = nullptr;
   pn.dS0 = nullptr;
@@ -499,20 +498,36 @@ hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, bool na
   return launch_bscan_bf16<DK, DV>(p3, false, st);
 }
 
-// Whether the state scans take 32-wide value slices (gdr2_nscan_bf16.hip, and the
-// reverse scan's narrow instance): when the 64-wide ones are at most half the
-// CUs.  4 x 16 (sequence, head) pairs of 2048 tokens, 128 wide scans: 207 us
-// forward narrow, 235 wide; 96 pairs, 192 wide scans: 363 and 288.  The sequences
-// of a packed batch differ in length, which the host does not know, and the
-// longest one's walk often sets the time (9 prompts of 37 to 3000 tokens x 16 heads:
-// 265 narrow, 317 wide; 4096 tokens and three of 64: 207 and 326): up to 512 wide
-// scans, as long as they are no more than 32 chunks for each CU (16 equal
-// sequences of 512, 16 chunks a CU: 228 and 202; the long packed training batch,
-// 64 a CU: 2065 and 1905).
-bool narrow_scan(const gdr2_problem* p, const Geo& G) {
-  if (G.L.nseg > 1) return false;
+// Slices of the state scans: 64 wide, or 32 wide (gdr2_nscan_bf16.hip, and the
+// reverse scan's narrow instance) when the 64-wide ones are at most half the CUs.  4 x 16
+// (sequence, head) pairs of 2048 tokens, 128 wide scans: 207 us forward narrow, 235
+// wide; 96 pairs, 192 wide scans: 363 and 288.  The sequences of a packed batch differ
+// in length, and the same line is where their total load is half the CUs' for as many
+// steps as the longest sequence has (packed_narrow).  The host knows where up to 128 wide
+// scans make it certain; else the table on the device does (kByTable: both kernels are
+// launched, the one not meant leaves at once, 4 us).  Whole calls of 16 heads, by table /
+// all narrow / all wide: training 6 sequences of 2048 808 / 901 / 807, 16 of 300 375 / 409 /
+// 367, two of 2048 and six of 100 443 / 439 / 516; forward 8 of 1024 184 / 203 / 180, 9 of
+// 37 to 3000 238 / 238 / 286.  A forward of up to 12 chunks for each CU gains less by it
+// than the launch takes (16 of 300: 130 / 135, two and six: 140 / 134) and is narrow; above
+// 512 wide scans, or 32 chunks for each CU, the wide ones are taken unasked (the long
+// packed training batch, 64 a CU: 2065 narrow and 1905 wide).
+enum Slices { kWide, kNarrow, kByTable };
+Slices scan_slices(const gdr2_problem* p, const Geo& G, bool reverse) {
+  if (G.L.nseg > 1) return kWide;
   const long long per_seq = (long long)p->H * (p->Dv / 64), wide = G.nscan * per_seq;
-  return wide <= 128 || (G.vl.cu != nullptr && wide <= 512 && G.NT * per_seq <= 32 * 256);
+  if (wide <= 128) return kNarrow;
+  if (G.vl.cu == nullptr || wide > 512 || G.NT * per_seq > 32 * 256) return kWide;
+  return reverse || G.NT * per_seq > 12 * 256 ? kByTable : kNarrow;
+}
+
+// Runs `launch(args, narrow)` for a scan's slices: one kernel, or both (kByTable).
+template <class Args, class F>
+hipError_t in_slices(Slices s, const gdr2_problem* p, Args x, F&& launch) {
+  if (s != kByTable) return launch(x, s == kNarrow);
+  x.pick = p->H * (p->Dv / 64);
+  const hipError_t e = launch(x, true);
+  return e == hipSuccess ? launch(x, false) : e;
 }
 
 // ---- dispatch over (Dk, Dv) ------------------------------------------------
@@ -554,10 +569,12 @@ struct FwdRun {
       sa.vl = G.vl;
       sa.G = G.G;
       return timed(GDR2_K_FWD_STATE, st, [&] {
-        return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& x) {
-          if (narrow_scan(p, G))
-            return save ? launch_nscan_bf16<DK, DV, true, true>(x, st) : launch_nscan_bf16<DK, DV, true, false>(x, st);
-          return save ? launch_scan_bf16<DK, DV, true, true>(x, st) : launch_scan_bf16<DK, DV, true, false>(x, st);
+        return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& y) {
+          return in_slices(scan_slices(p, G, false), p, y, [&](const ScanArgs& x, bool narrow) {
+            if (narrow)
+              return save ? launch_nscan_bf16<DK, DV, true, true>(x, st) : launch_nscan_bf16<DK, DV, true, false>(x, st);
+            return save ? launch_scan_bf16<DK, DV, true, true>(x, st) : launch_scan_bf16<DK, DV, true, false>(x, st);
+          });
         }, st);
       });
     } else {
@@ -615,9 +632,11 @@ struct BwdRun {
         sa.vl = G.vl;
         sa.G = G.G;
         e = timed(GDR2_K_BWD_RECOMPUTE_STATE, st, [&] {
-          return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& x) {
-            return narrow_scan(p, G) ? launch_nscan_bf16<DK, DV, false, true>(x, st)
-                                     : launch_scan_bf16<DK, DV, false, true>(x, st);
+          return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& y) {
+            return in_slices(scan_slices(p, G, false), p, y, [&](const ScanArgs& x, bool narrow) {
+              return narrow ? launch_nscan_bf16<DK, DV, false, true>(x, st)
+                            : launch_scan_bf16<DK, DV, false, true>(x, st);
+            });
           }, st);
         });
         if (e != hipSuccess) return e;
@@ -627,7 +646,12 @@ struct BwdRun {
       ba.DHsc = at<float>(ws, L.DHsc);
       ba.vl = G.vl;
       ba.G = G.G;
-      e = timed(GDR2_K_BWD_STATE, st, [&] { return scan_bwd_bf16<DK, DV>(ba, L, ws, narrow_scan(p, G), st); });
+      e = timed(GDR2_K_BWD_STATE, st, [&] {
+        if (L.nseg > 1) return scan_bwd_bf16<DK, DV>(ba, L, ws, st);
+        return in_slices(scan_slices(p, G, true), p, ba, [&](const BScanArgs& x, bool narrow) {
+          return launch_bscan_bf16<DK, DV>(x, narrow, st);
+        });
+      });
       if (e != hipSuccess) return e;
       // the WY VJP and the intra-chunk VJP in one chunk-parallel kernel
       BChunkBf16Args ca{static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k),

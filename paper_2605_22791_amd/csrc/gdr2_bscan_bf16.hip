@@ -21,7 +21,7 @@
 // and the dO rows come through a range-checked buffer load, so that every
 // path issues the same loads and stores.
 //
-// For few sequences (narrow_scan in gdr2_api.hip) the slices are 32 wide: half the
+// For few sequences (scan_slices in gdr2_api.hip) the slices are 32 wide: half the
 // products and fragments a step, and with LDS room for a second dO the operands are
 // copied there beside the products that do not read them, two barriers a step
 // instead of three.  4 x 16 pairs of 4000 tokens at 128 x 128: 215 us, 275 with
@@ -90,6 +90,7 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
   const int g = lane >> 4, r16 = lane & 15;
   const int qq = r16 & 3, ii = r16 >> 2;  // transpose-load role of this lane (4 ii + qq)
   const int T = a.T, H = a.H, NT = a.NT;
+  if (a.pick > 0 && packed_narrow(a.vl, a.pick) != NAR) return;  // the other instance's
 
   // independent scans: (sequence, segment) pairs, vs = seq * nseg + seg
   const int nseg = a.nseg, nvirt = a.B * H * nseg;

@@ -51,6 +51,16 @@ __device__ __forceinline__ void table_rows(const Varlen& vl, int c, int T, size_
   len = min(max(ld_table(vl.clen, c), 1), min(CH, T - t0));
 }
 
+// Whether a packed batch is scanned in 32-wide value slices, where the host cannot tell
+// (scan_slices in gdr2_api.hip): if the longest sequence is more than twice what a CU
+// has to walk on average, per_seq 64-wide scans a sequence.  The narrow and the wide
+// kernel both ask, with the same answer, and one of them leaves at once.
+__device__ __forceinline__ bool packed_narrow(const Varlen& vl, int per_seq) {
+  const int s = (int)min((unsigned)ld_table(vl.sorder, 0), (unsigned)vl.nseq - 1);
+  const int longest = ld_table(vl.coff, s + 1) - ld_table(vl.coff, s);
+  return (long long)ld_table(vl.coff, vl.nseq) * per_seq <= 128ll * longest;
+}
+
 struct ChunkPos {
   size_t row0;  // token row of the chunk's first row (row = b * T + t)
   int len;      // rows in use
@@ -353,6 +363,7 @@ struct ScanArgs {
   Varlen vl{};
   int G = 1;                     // value heads per key head: Y, Q_g, A_qk, K_tail, gamma_C per key head
   float* STseg_m = nullptr;      // the map pass (Dk = DV): M of every segment (B*H*nseg, Dk, Dk)
+  int pick = 0;                  // > 0: packed_narrow with so many wide scans a sequence says which kernel runs
 };
 
 struct BScanArgs {
@@ -375,6 +386,7 @@ struct BScanArgs {
   int flags = 0;                   // ScanFlags (kScanNoInput: dO = 0)
   Varlen vl{};
   int G = 1;                       // as in ScanArgs
+  int pick = 0;                    // as in ScanArgs
 };
 
 // Chaining of segment maps: X <- M_k X + N_k over the segments of each sequence
@@ -449,7 +461,7 @@ struct BChunkBf16Args {
 template <int DK, int DV>
 hipError_t launch_intra_bf16(const IntraBf16Args& a, hipStream_t st);
 template <int DK, int DV>
-hipError_t launch_bscan_bf16(const BScanArgs& a, bool narrow, hipStream_t st);
+hipError_t launch_bscan_bf16(const BScanArgs& a, bool narrow, hipStream_t st);  // narrow: 32-wide slices
 template <int DK, int DV, bool WITH_O, bool STORE_H>
 hipError_t launch_scan_bf16(const ScanArgs& a, hipStream_t st);
 // the same scan in 32-wide value slices, for few sequences (nseg = 1)

@@ -1,20 +1,21 @@
 // Inter-chunk state scan of the bf16 path for few sequences (gfx950): the
 // products of gdr2_scan_bf16.hip in the same order (the results are the same
-// bits), one 8-wave workgroup per (sequence, head) and 32-wide value slice.
+// bits), one workgroup of 8 to 16 waves per (sequence, head) and 32-wide value slice.
 //
 // With 64-wide slices a scan of few heads leaves half the chip or more idle and
 // is bound by the length of a step: 3.3 us, most of it LDS traffic (every
 // operand block staged there, the state's fragments read by all waves) and one
 // product after another in each wave.  Here a step's products have waves of their
-// own, four for R, four for Q_g S and A_qk R, one per key block for the state; every
+// own, four for R, four for Q_g S and A_qk R (with the output), one per key block for
+// the state: 16 or 12 waves with the output (Dk = 128, 64), 12 or 8 without.  Every
 // operand block goes from memory straight into the registers of the one wave
-// that multiplies it; and LDS holds S and R alone.  A step is 1.7 us on 64
-// workgroups (16 heads, 16 chunks, 128 x 128: 28 us, the wide scan 52); what is
-// left is LDS time of the products' S and R fragments and, with a workgroup on every CU, the memory's answer (3 us a step,
-// where the wide kernel takes 4).  With the loads of R's and Q_g's waves in front of
+// that multiplies it, and LDS holds S and R alone.  A step is 1.7 us on 64
+// workgroups (16 heads, 16 chunks, 128 x 128: 28 us, the wide scan 52); what is left is
+// LDS time of the products' S and R fragments and, with a workgroup on every CU, the
+// memory's answer (3 us a step, where the wide kernel takes 4).  With the loads of R's and Q_g's waves in front of
 // the barrier they wait at, a step was 2.1 us: the loads of all waves at once take
 // 700 cycles to issue.
-// narrow_scan in gdr2_api.hip says when it is taken.
+// scan_slices in gdr2_api.hip says when it is taken.
 //
 // Precision: as gdr2_scan_bf16.hip.
 
@@ -48,6 +49,7 @@ __global__ __launch_bounds__(nscan_threads(DK, WITH_O)) void nscan_bf16_kernel(S
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;
   const int H = a.H;
+  if (a.pick > 0 && !packed_narrow(a.vl, a.pick)) return;  // the wide kernel's
   // the slices of the G value heads that read one key head's tiles run on one XCD where the pairs divide
   int q, slice;
   {

@@ -116,6 +116,7 @@ __global__ __launch_bounds__(512) void scan_bf16_kernel(ScanArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, r16 = lane & 15;
   const int T = a.T, H = a.H, NT = a.NT;
+  if (a.pick > 0 && packed_narrow(a.vl, a.pick)) return;  // gdr2_nscan_bf16.hip's
 
   // independent scans: (sequence, segment) pairs, vs = seq * nseg + seg
   const int nseg = a.nseg, nvirt = a.B * H * nseg;

@@ -258,3 +258,50 @@ def test_saved_backward_on_a_foreign_workspace(dtype, entry):
     got = {n: host(t) for n, t in bwd().items()}
     got.update(o=host(o), S_T=host(ST))
     _compare(got, oracle_packed(d), TOL[dtype])
+
+
+@pytest.mark.parametrize("H,Dk,Dv,lengths", [
+    (16, 128, 128, [700] * 10),                             # alike: wide slices by the table
+    (16, 128, 128, [3000, 200, 64, 1, 0, 130, 77, 300]),    # one long sequence: narrow ones
+    (16, 64, 64, [1792] * 8 + [0]),                         # at the line: 8 x 28 chunks x 16 scans = 128 x 28
+    (16, 64, 64, [1792, 1] + [1792] * 7),                   # a chunk past it
+    (24, 64, 128, [100] * 9), (8, 128, 64, [0] * 40 + [70])])
+def test_packed_scan_slices(H, Dk, Dv, lengths):
+    """Batches whose scans run in wide or narrow slices by the table's lengths (both kernels are
+    launched): the bits of the sequences in batches so small that the host takes the narrow ones."""
+    import torch
+    import paper_2605_22791_amd as g2
+    T, N = sum(lengths), len(lengths)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(140 + N)
+    nrm = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    unit = lambda t: (t / t.norm(dim=-1, keepdim=True)).bfloat16()
+    x = {"q": unit(nrm(1, T, H, Dk)), "k": unit(nrm(1, T, H, Dk)), "v": nrm(1, T, H, Dv).bfloat16(),
+         "log_alpha": -torch.nn.functional.softplus(nrm(1, T, H, Dk) - 2.0),
+         "b": torch.sigmoid(nrm(1, T, H, Dk)).bfloat16(), "w": torch.sigmoid(nrm(1, T, H, Dv)).bfloat16(),
+         "do": nrm(1, T, H, Dv).bfloat16(), "S0": 0.05 * nrm(N, H, Dk, Dv), "dST": nrm(N, H, Dk, Dv)}
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    per_seq = H * Dv // 64
+    assert 128 < N * per_seq <= 512 and (T // 64 + N) * per_seq <= 32 * 256
+    _case(f"packed scan slices H{H} Dk{Dk} Dv{Dv} lengths {lengths}")
+
+    def run(t, cu, save):
+        args = [t[n] for n in ("q", "k", "v", "log_alpha", "b", "w")]
+        need = g2.gdr2_varlen_workspace_bytes(g2._problem(t["q"], t["v"], None), cu.numel() - 1, 1)
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+        o, ST = g2.gdr2_chunk_fwd_varlen(*args, cu, t["S0"], ws=ws, save=save)
+        g = g2.gdr2_chunk_bwd_varlen(*args, cu, t["S0"], t["do"], t["dST"], ws=ws, saved=save)
+        return {"o": o, "S_T": ST, **g}
+
+    cu = torch.from_numpy(off).cuda()
+    few = 128 // per_seq
+    for save in (True, False):
+        whole = run(x, cu, save)
+        for s0 in range(0, N, few):
+            s1 = min(N, s0 + few)
+            if off[s1] == off[s0]:
+                continue
+            part = lambda n, t: (t[s0:s1] if n in ("S0", "dST", "S_T", "dS0") else t[:, off[s0]:off[s1]]).contiguous()
+            sub = torch.from_numpy(off[s0:s1 + 1] - off[s0]).cuda()
+            for n, t in run({n: part(n, t) for n, t in x.items()}, sub, save).items():
+                assert torch.equal(t, part(n, whole[n])), (n, s0, save)
