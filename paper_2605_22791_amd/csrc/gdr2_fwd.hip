@@ -193,31 +193,38 @@ __global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
 // a workgroup, four waves, operands loaded where they are used: 160 and 110; the
 // two roles in one body, whose waits then counted the barer role: 95 and 45).
 // The slices of a sequence share their XCD (state_slot), hence its L2.
-template <int DK, int DV, bool WITH_O, bool STORE_H>
+//
+// Many pairs fill the chip whatever a slice's width, and then every slice's reading of
+// the key-side tiles counts: two slices a workgroup (NV = 2, the same sums).  Forward
+// calls, 128 x 128, NV = 1 / 2: 128 pairs of 256 tokens 136 / 118 us, 64 of 512 128 / 113,
+// 32 of 1000 (256 slices, one a CU) 126 / 150, 4 of 512 63 / 76.
+template <int DK, int DV, bool WITH_O, bool STORE_H, int NV>
 __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
   constexpr int NCB = DK / 16;      // key blocks: S tiles, one per wave
   constexpr int LT = DK + 4, LR = CH + 4;
   int q, vs;
-  if (!state_slot<DV / 16>(blockIdx.x, a.nq, q, vs)) return;
+  if (!state_slot<DV / (16 * NV)>(blockIdx.x, a.nq, q, vs)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 15, lg = lane >> 4, v0 = 16 * vs + lr;
+  const int lr = lane & 15, lg = lane >> 4, v0 = 16 * NV * vs + lr;
   const size_t seq = (size_t)scan_pair(a.vl, q, a.H);  // (sequence, head) pair
   const int h = (int)(seq % a.H);
   const ScanRange rng = scan_range(a.vl, (int)seq, a.H, a.NT);
   const bool low = wave < 4, own = NCB == 8 || low;
   const int i = wave & 3, cb = own ? wave : 0;  // row block of the products; key block of the S tile
 
-  __shared__ __align__(16) float sS[16 * LT];  // [v][c]
-  __shared__ __align__(16) float sR[16 * LR];  // [v][r]
+  __shared__ __align__(16) float sS[16 * NV * LT];  // [v][c]
+  __shared__ __align__(16) float sR[16 * NV * LR];  // [v][r]
 
-  f4 st = f4{0.f, 0.f, 0.f, 0.f};  // S[16 cb + 4 lg + u][v0]
+  f4 st[NV];  // S[16 cb + 4 lg + u][v0 + 16 t]
   const size_t so = (seq * DK + 16 * cb + 4 * lg) * DV + v0;
-  if (own) {
-    if (a.S0 != nullptr) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) st[u] = a.S0[so + (size_t)u * DV];
+  for (int t = 0; t < NV; ++t) {
+    st[t] = f4{0.f, 0.f, 0.f, 0.f};
+    if (own && a.S0 != nullptr) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) st[t][u] = a.S0[so + (size_t)u * DV + 16 * t];
     }
-    *reinterpret_cast<f4*>(sS + lr * LT + 16 * cb + 4 * lg) = st;
+    if (own) *reinterpret_cast<f4*>(sS + (16 * t + lr) * LT + 16 * cb + 4 * lg) = st[t];
   }
 
   // the two roles as code of their own: on each the same loads and stores go out
@@ -226,27 +233,33 @@ __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
     constexpr bool LOW = decltype(LOWC)::value, OWN = NCB == 8 || LOW;
     struct Ops {
       float4 p[DK / 16];  // row 16 i + lr of Y (waves 0-3) or Qg, channels 16 j + 4 lg ..
-      float4 x[4];        // waves 4-7: Aqk row 16 i + lr, keys 16 j + 4 lg ..; waves 0-3: x[0] = U's tile
+      float4 x[4];        // waves 4-7: Aqk row 16 i + lr, keys 16 j + 4 lg ..; waves 0-3: x[t] = U's tiles
       float k[4][4];      // Ktail[16 j + 4 lg + t][16 cb + lr]
       float4 g;           // gamma_C of channels 16 cb + 4 lg ..
     };
     const auto load = [&](Ops& o, int n) {
-      const size_t ch = rng.chs + min(n, rng.c1 - 1);  // past the end: the last chunk again, unused
-      const float* P = (LOW ? a.Y : a.Qg) + (ch * CH + 16 * i + lr) * DK + 4 * lg;
+      // past the end the last chunk again, unused, one cache line a load: with each
+      // lane's own line it was twice the traffic for a sequence of two chunks (512 pairs
+      // of 128 tokens 341 us, 312)
+      const size_t ch = rng.chs + min(n, rng.c1 - 1);
+      const int all = n < rng.c1 ? -1 : 0;
+      const float* P = (LOW ? a.Y : a.Qg) + ch * CH * DK + (((16 * i + lr) * DK + 4 * lg) & all);
       if (LOW || WITH_O) {
 #pragma unroll
         for (int j = 0; j < DK / 16; ++j) o.p[j] = ld4(P + 16 * j);
       }
       if (LOW) {
-        const float* U = a.U + (ch * CH + 16 * i + 4 * lg) * DV + v0;
-        o.x[0] = make_float4(U[0], U[DV], U[2 * DV], U[3 * DV]);
+        const float* U = a.U + ch * CH * DV + (((16 * i + 4 * lg) * DV + v0) & all);
+#pragma unroll
+        for (int t = 0; t < NV; ++t)
+          o.x[t] = make_float4(U[16 * t], U[DV + 16 * t], U[2 * DV + 16 * t], U[3 * DV + 16 * t]);
       } else if (WITH_O) {
-        const float* A = a.Aqk + (ch * CH + 16 * i + lr) * CH + 4 * lg;
+        const float* A = a.Aqk + ch * CH * CH + (((16 * i + lr) * CH + 4 * lg) & all);
 #pragma unroll
         for (int j = 0; j < 4; ++j) o.x[j] = ld4(A + 16 * min(j, i));
       }
       if (OWN) {
-        const float* K = a.Kt + (ch * CH + 4 * lg) * DK + 16 * cb + lr;
+        const float* K = a.Kt + ch * CH * DK + ((4 * lg * DK + 16 * cb + lr) & all);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -254,60 +267,85 @@ __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
         o.g = ld4(a.GC + ch * DK + 16 * cb + 4 * lg);
       }
     };
-    const auto step = [&](Ops& o, int n) {
+    const auto step = [&](Ops& o, int n, auto FETCH) {
       const size_t ch = rng.chs + n;
       if (STORE_H && OWN) {
         float* Hn = a.Hs + (ch * DK + 16 * cb + 4 * lg) * DV + v0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) Hn[u * DV] = st[u];
+        for (int t = 0; t < NV; ++t)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) Hn[u * DV + 16 * t] = st[t][u];
       }
       // Y S (waves 0-3), Qg S (waves 4-7): two accumulators, so that a product does not wait for the one before
-      f4 acc = f4{0.f, 0.f, 0.f, 0.f}, ac2 = acc;
+      f4 acc[NV], ac2[NV];
+#pragma unroll
+      for (int t = 0; t < NV; ++t) acc[t] = ac2[t] = f4{0.f, 0.f, 0.f, 0.f};
       if (LOW || WITH_O) {
 #pragma unroll
         for (int j = 0; j < DK / 16; ++j) {
-          const float4 y = o.p[j], s = ld4(sS + lr * LT + 16 * j + 4 * lg);
-          acc = mfma4(y.x, s.x, acc);
-          ac2 = mfma4(y.y, s.y, ac2);
-          acc = mfma4(y.z, s.z, acc);
-          ac2 = mfma4(y.w, s.w, ac2);
+          const float4 y = o.p[j];
+#pragma unroll
+          for (int t = 0; t < NV; ++t) {
+            const float4 s = ld4(sS + (16 * t + lr) * LT + 16 * j + 4 * lg);
+            acc[t] = mfma4(y.x, s.x, acc[t]);
+            ac2[t] = mfma4(y.y, s.y, ac2[t]);
+            acc[t] = mfma4(y.z, s.z, acc[t]);
+            ac2[t] = mfma4(y.w, s.w, ac2[t]);
+          }
         }
       }
-      acc += ac2;
-      if (LOW) {
-        const f4 R = f4{o.x[0].x, o.x[0].y, o.x[0].z, o.x[0].w} - acc;
-        *reinterpret_cast<f4*>(sR + lr * LR + 16 * i + 4 * lg) = R;
-        if (STORE_H) {
-          float* Rn = a.Rs + (ch * CH + 16 * i + 4 * lg) * DV + v0;
 #pragma unroll
-          for (int u = 0; u < 4; ++u) Rn[u * DV] = R[u];
+      for (int t = 0; t < NV; ++t) {
+        acc[t] += ac2[t];
+        if (LOW) {
+          const f4 R = f4{o.x[t].x, o.x[t].y, o.x[t].z, o.x[t].w} - acc[t];
+          *reinterpret_cast<f4*>(sR + (16 * t + lr) * LR + 16 * i + 4 * lg) = R;
+          if (STORE_H) {
+            float* Rn = a.Rs + (ch * CH + 16 * i + 4 * lg) * DV + v0 + 16 * t;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) Rn[u * DV] = R[u];
+          }
         }
       }
       __syncthreads();  // R is there, and nobody reads this chunk's S any more
-      float4 r[4];
+      float4 r[NV][4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) r[j] = ld4(sR + lr * LR + 16 * j + 4 * lg);
+      for (int t = 0; t < NV; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r[t][j] = ld4(sR + (16 * t + lr) * LR + 16 * j + 4 * lg);
       if (OWN) {
-        st = f4{o.g.x * st[0], o.g.y * st[1], o.g.z * st[2], o.g.w * st[3]};
-        f4 s2 = f4{0.f, 0.f, 0.f, 0.f};
+        f4 s2[NV];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          st = mfma4(o.k[j][0], r[j].x, st);
-          s2 = mfma4(o.k[j][1], r[j].y, s2);
-          st = mfma4(o.k[j][2], r[j].z, st);
-          s2 = mfma4(o.k[j][3], r[j].w, s2);
+        for (int t = 0; t < NV; ++t) {
+          st[t] = f4{o.g.x * st[t][0], o.g.y * st[t][1], o.g.z * st[t][2], o.g.w * st[t][3]};
+          s2[t] = f4{0.f, 0.f, 0.f, 0.f};
         }
-        st += s2;
-        *reinterpret_cast<f4*>(sS + lr * LT + 16 * cb + 4 * lg) = st;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int t = 0; t < NV; ++t) {
+            st[t] = mfma4(o.k[j][0], r[t][j].x, st[t]);
+            s2[t] = mfma4(o.k[j][1], r[t][j].y, s2[t]);
+            st[t] = mfma4(o.k[j][2], r[t][j].z, st[t]);
+            s2[t] = mfma4(o.k[j][3], r[t][j].w, s2[t]);
+          }
+#pragma unroll
+        for (int t = 0; t < NV; ++t) {
+          st[t] += s2[t];
+          *reinterpret_cast<f4*>(sS + (16 * t + lr) * LT + 16 * cb + 4 * lg) = st[t];
+        }
       }
       if (WITH_O && !LOW) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (j > i) break;
-          acc = mfma4(o.x[j].x, r[j].x, acc);
-          acc = mfma4(o.x[j].y, r[j].y, acc);
-          acc = mfma4(o.x[j].z, r[j].z, acc);
-          acc = mfma4(o.x[j].w, r[j].w, acc);
+#pragma unroll
+          for (int t = 0; t < NV; ++t) {
+            acc[t] = mfma4(o.x[j].x, r[t][j].x, acc[t]);
+            acc[t] = mfma4(o.x[j].y, r[t][j].y, acc[t]);
+            acc[t] = mfma4(o.x[j].z, r[t][j].z, acc[t]);
+            acc[t] = mfma4(o.x[j].w, r[t][j].w, acc[t]);
+          }
         }
         size_t row0;
         int len;
@@ -317,20 +355,27 @@ __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
         float* O = a.o + ((row0 + 16 * i + 4 * lg) * a.H + h) * DV + v0;
         float* X = const_cast<float*>(a.U) + (ch * CH + 16 * i + 4 * lg) * DV + v0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          *(16 * i + 4 * lg + u < len ? O + (size_t)u * a.H * DV : X + u * DV) = a.scale * acc[u];
+        for (int t = 0; t < NV; ++t)
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            *(16 * i + 4 * lg + u < len ? O + (size_t)u * a.H * DV + 16 * t : X + u * DV + 16 * t) = a.scale * acc[t][u];
       }
-      load(o, n + 2);
+      if constexpr (decltype(FETCH)::value) load(o, n + 2);
       __syncthreads();
     };
-    if (rng.c0 < rng.c1) {
+    if (NV == 2 && rng.c0 + 1 == rng.c1) {  // a single chunk: nothing else to fetch (256 pairs of 64 tokens 73 / 67 us)
+      Ops oa;
+      load(oa, rng.c0);
+      __syncthreads();
+      step(oa, rng.c0, std::false_type{});
+    } else if (rng.c0 < rng.c1) {
       Ops oa, ob;
       load(oa, rng.c0);
       load(ob, rng.c0 + 1);
       __syncthreads();
       for (int n = rng.c0; n < rng.c1; n += 2) {
-        step(oa, n);
-        if (n + 1 < rng.c1) step(ob, n + 1);
+        step(oa, n, std::true_type{});
+        if (n + 1 < rng.c1) step(ob, n + 1, std::true_type{});
       }
     }
   };
@@ -340,7 +385,9 @@ __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
     run(std::false_type{});
   if (a.ST != nullptr && own) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) a.ST[so + (size_t)u * DV] = st[u];
+    for (int t = 0; t < NV; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a.ST[so + (size_t)u * DV + 16 * t] = st[t][u];
   }
 }
 
@@ -361,7 +408,12 @@ hipError_t launch_fwd_intra(const IntraArgs<TIn>& a, int B, hipStream_t st) {
 
 template <int DK, int DV, bool WITH_O, bool STORE_H>
 hipError_t launch_fwd_state(const StateArgs<float>& a, hipStream_t st) {
-  hipLaunchKernelGGL((fwd_state_kernel<DK, DV, WITH_O, STORE_H>), dim3(state_slots<DV / 16>(a.nq)), dim3(512), 0, st, a);
+  if ((long long)a.nq * (DV / 16) <= 256)  // a CU for each narrow slice
+    hipLaunchKernelGGL((fwd_state_kernel<DK, DV, WITH_O, STORE_H, 1>), dim3(state_slots<DV / 16>(a.nq)), dim3(512),
+                       0, st, a);
+  else
+    hipLaunchKernelGGL((fwd_state_kernel<DK, DV, WITH_O, STORE_H, 2>), dim3(state_slots<DV / 32>(a.nq)), dim3(512),
+                       0, st, a);
   return hipGetLastError();
 }
 

@@ -568,3 +568,31 @@ def test_fp32_decayed_blocks_with_large_operands(per_token, large):
         err = rel_l2(one[n], ref[r])
         assert err < TOL["fp32"], (n, err)
     check_decay_grad(one["dlog_alpha"], ref["dg"], decay_terms(d, ref), np.arange(64) % 5 == 0, TOL["fp32"])
+
+
+@pytest.mark.parametrize("T", [40, 64, 128, 130, 200, 300])
+@pytest.mark.parametrize("H,Dk,Dv", [(33, 128, 128), (33, 64, 128), (65, 128, 64), (71, 64, 64)])
+def test_fp32_state_slices(H, Dk, Dv, T):
+    """More 16-column slices than CUs (two a workgroup, at one to five chunks, the first and last pair
+    of a count that eight does not divide): the bits of a head alone, one slice a workgroup."""
+    import torch
+    import paper_2605_22791_amd as g2
+    d = make_inputs(1, T, H, Dk, Dv, seed=420 + T, dtype="fp32", s0_std=0.1)
+    assert H * Dv // 16 > 256
+    _case(f"fp32 state slices H{H} T{T} Dk{Dk} Dv{Dv}")
+    x = {n: t for n, t in dev_inputs(d).items() if t is not None}
+
+    def run(t, save):
+        args = [t[n] for n in ("q", "k", "v", "log_alpha", "b", "w")]
+        need = g2.gdr2_chunk_workspace_bytes(g2._problem(t["q"], t["v"], d["scale"]), 1)
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+        o, ST = g2.gdr2_chunk_fwd(*args, t["S0"], scale=d["scale"], ws=ws, save=save)
+        return {"o": o, "S0": ST, **{"grad " + n: y for n, y in g2.gdr2_chunk_bwd(
+            *args, t["S0"], t["do"], None, scale=d["scale"], ws=ws, saved=save).items()}}
+
+    for save in (False, True):
+        all_heads = run(x, save)
+        for h in (0, H - 1):
+            head = lambda n, t: (t[:, h:h + 1] if n.endswith("S0") else t[:, :, h:h + 1]).contiguous()
+            for n, t in run({n: head(n, t) for n, t in x.items()}, save).items():
+                assert torch.equal(t, head(n, all_heads[n])), (n, h, save)
