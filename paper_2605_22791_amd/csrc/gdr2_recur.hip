@@ -8,9 +8,9 @@
 // One token (recurrent_one_kernel) is the state's way through memory and back.
 // A workgroup takes a (batch, head) and each of its four waves a quarter of the
 // rows, one contiguous run, a whole kilobyte an access; the rows' sums meet in
-// LDS behind the only barrier.  B = 256, 16 heads, 128 x 128 (545 MB): 104.4 us,
-// 5.2 TB/s (a large copy runs at 5.1); 108.2 with five barriers and a wave's
-// accesses in two runs 8 KB apart, 110.8 with a wave per 32 columns.  B = 64
+// LDS behind the only barrier (rows_tokens).  B = 256, 16 heads, 128 x 128 (545 MB):
+// 103 us, 5.2 TB/s (a large copy runs at 5.1); 108 with five barriers and a wave's
+// accesses in two runs 8 KB apart, 111 with a wave per 32 columns.  B = 64
 // (within the Infinity Cache): 22.2, 23.1 and 24.4 us.
 //
 // Several tokens (recurrent_kernel) are bound by a token's latency, or with many
@@ -22,7 +22,13 @@
 // on its way from memory: no barrier anywhere.  Two sequences x 16 heads x 128
 // x 128: 0.65 us a token, 1.48 with a workgroup per head and five barriers a
 // token; 64 sequences of 65 tokens 188 us, 295 before; a packed batch of 48
-// sequences of 1 to 16 tokens from raw projections 35.5 us, 49.9 before.
+// sequences of 1 to 16 tokens from raw projections 32.5 us a call, 48.5 before.
+//
+// A few tokens of many sequences are both: a sequence of up to kRowsTokens goes by
+// rows with a barrier a token, whatever its neighbours in a packed batch do (the
+// workgroup sees its count).  16 heads, 128 x 128, by columns / by rows: 256 sequences
+// of 2 tokens 94.2 / 87.4 us, of 4 107.8 / 100.6, of 8 143 / 138; 64 of 4 30.3 / 28.9, of 6
+// 33.2 / 33.6, of 8 37.3 / 38.7; a packed batch of 256 single tokens 89.3 / 81.1.
 //
 // Fused input stage (a.st.a_log set; App. C.1, App. D.2): q and k are the raw
 // projections, L2-normalised per token in fp32 and rounded to the operand
@@ -98,6 +104,20 @@ __device__ __forceinline__ float wave_sum(float x, int lane) {
   return x + row_partner32(x, lane >= 32);
 }
 
+// Tokens of sequence bb: its T, or cu[bb] .. cu[bb+1) of a packed batch (clamped into
+// [0, T]); the first one's row and their number, false if there is none.
+template <typename TIn>
+__device__ __forceinline__ bool tokens(const RecurArgs<TIn>& a, int bb, size_t& row, int& n) {
+  row = (size_t)bb * a.T;
+  n = a.T;
+  if (a.cu != nullptr) {
+    const int t0 = min(max(a.cu[bb], 0), a.T);
+    row = (size_t)t0;
+    n = min(max(a.cu[bb + 1], t0), a.T) - t0;
+  }
+  return n > 0;
+}
+
 // A wave's part of a token: NK = DK / 64 key-side rows and four value columns per lane
 template <int DK, typename TIn, bool FUSED>
 struct Token {
@@ -140,23 +160,31 @@ struct Token {
   }
 };
 
-// ---- T = 1 -----------------------------------------------------------------
-template <int DK, int DV, typename TIn, bool FUSED>
-__global__ __launch_bounds__(256) void recurrent_one_kernel(RecurArgs<TIn> a) {
-  constexpr int NW = 4, RW = DK / NW;       // waves, rows per wave
+constexpr int kRowsTokens = 4;
+
+// ---- a workgroup per (sequence, head): one token, or a few ------------------
+// n tokens from `row` on of pair seq; MULTI: n may be more than one.  smem: rows_lds bytes
+template <int DK, int DV, int NW, bool MULTI>
+constexpr int rows_lds() { return 4 * (NW * 4 * DK + (MULTI ? 2 : 1) * 2 * NW * DV); }
+template <int DK, int DV, typename TIn, bool FUSED, int NW, bool MULTI>
+__device__ __forceinline__ void rows_tokens(const RecurArgs<TIn>& a, int seq, size_t row, int n, unsigned char* smem) {
+  constexpr int RW = DK / NW;               // rows per wave
   constexpr int CG = DV / 4, RG = 64 / CG;  // the lanes' column and row groups
   constexpr int RPL = RW / RG;              // rows per lane: RW wave + RG i + rg
   static_assert(RG == 2 || RG == 4, "row groups are halves or quarters of a wave");
-  __shared__ __align__(16) float sF[NW][4 * DK];
-  __shared__ __align__(16) float sSum[2][NW][DV];
+  float(*sF)[4 * DK] = reinterpret_cast<float(*)[4 * DK]>(smem);
+  // the waves' sums, by token parity: one barrier a token
+  float(*sSum)[2][NW][DV] = reinterpret_cast<float(*)[2][NW][DV]>(smem + 4 * NW * 4 * DK);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int seq = blockIdx.x, bb = seq / a.H, h = seq % a.H;
+  const int h = seq % a.H;
   const int cg = lane % CG, rg = lane / CG;
   const int HK = a.H / a.G, hk = h / a.G;  // key side (q, k, g, b) on the H / G key heads
 
   using Tok = Token<DK, TIn, FUSED>;
+  const size_t ks = (size_t)HK * DK, vs = (size_t)a.H * DV;  // token strides
+  const size_t ok = row * ks + (size_t)hk * DK + Tok::NK * lane, ov = row * vs + (size_t)h * DV + 4 * cg;
   Tok x;
-  x.load(a, ((size_t)bb * HK + hk) * DK + Tok::NK * lane, (size_t)seq * DV + 4 * cg);
+  x.load(a, ok, ov);
   Raw<float, Tok::NK> dl{};
   float Adec = 0.f;
   if constexpr (FUSED) {
@@ -170,68 +198,94 @@ __global__ __launch_bounds__(256) void recurrent_one_kernel(RecurArgs<TIn> a) {
   for (int i = 0; i < RPL; ++i) S[i] = *reinterpret_cast<const f4*>(Sg + (ls + RG * i * DV));
 
   float* const F = sF[wave];
-  const float kq = x.factors(dl, Adec, a.st.eps, lane, [&](int row, float al, float e, float q, float k) {
-    *reinterpret_cast<float4*>(F + 4 * row) = make_float4(al, e, q, k);
-  });
-  __builtin_amdgcn_wave_barrier();
-  const float* Fl = F + 4 * (RW * wave + rg);
-  f4 pr = f4zero(), pp = f4zero();
+  for (int t = 0; t < (MULTI ? n : 1); ++t) {
+    const float kq = x.factors(dl, Adec, a.st.eps, lane, [&](int row, float al, float e, float q, float k) {
+      *reinterpret_cast<float4*>(F + 4 * row) = make_float4(al, e, q, k);
+    });
+    float z[4];
 #pragma unroll
-  for (int i = 0; i < RPL; ++i) {
-    const float4 f = *reinterpret_cast<const float4*>(Fl + 4 * RG * i);
+    for (int u = 0; u < 4; ++u) z[u] = x.v.at(u) * x.w.at(u);
+    if constexpr (MULTI) {  // the next token (past the last one the last again)
+      const size_t d = (size_t)min(t + 1, n - 1);
+      x.load(a, ok + d * ks, ov + d * vs);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const float* Fl = F + 4 * (RW * wave + rg);
+    f4 pr = f4zero(), pp = f4zero();
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+      const float4 f = *reinterpret_cast<const float4*>(Fl + 4 * RG * i);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        S[i][u] *= f.x;
+        pr[u] += S[i][u] * f.y;
+        pp[u] += S[i][u] * f.z;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      S[i][u] *= f.x;
-      pr[u] += S[i][u] * f.y;
-      pp[u] += S[i][u] * f.z;
+      if constexpr (RG == 4) {
+        pr[u] += row_partner16(pr[u], (lane & 16) != 0);
+        pp[u] += row_partner16(pp[u], (lane & 16) != 0);
+      }
+      pr[u] += row_partner32(pr[u], lane >= 32);
+      pp[u] += row_partner32(pp[u], lane >= 32);
     }
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    if constexpr (RG == 4) {
-      pr[u] += row_partner16(pr[u], (lane & 16) != 0);
-      pp[u] += row_partner16(pp[u], (lane & 16) != 0);
+    float(*sum)[NW][DV] = sSum[MULTI ? t & 1 : 0];
+    if (rg == 0) {
+      *reinterpret_cast<f4*>(&sum[0][wave][4 * cg]) = pr;
+      *reinterpret_cast<f4*>(&sum[1][wave][4 * cg]) = pp;
     }
-    pr[u] += row_partner32(pr[u], lane >= 32);
-    pp[u] += row_partner32(pp[u], lane >= 32);
-  }
-  if (rg == 0) {
-    *reinterpret_cast<f4*>(&sSum[0][wave][4 * cg]) = pr;
-    *reinterpret_cast<f4*>(&sSum[1][wave][4 * cg]) = pp;
-  }
-  __syncthreads();
-  float res[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    float r = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) r += sSum[0][w][4 * cg + u];
-    res[u] = x.v.at(u) * x.w.at(u) - r;
-  }
-#pragma unroll
-  for (int i = 0; i < RPL; ++i) {
-    const float k = Fl[4 * RG * i + 3];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) S[i][u] += k * res[u];
-  }
-  asm volatile("" : "+v"(ls));  // addresses anew: kept from the loads they would hold registers
-#pragma unroll
-  for (int i = 0; i < RPL; ++i) *reinterpret_cast<f4*>(Sg + (ls + RG * i * DV)) = S[i];
-  if (wave == 0 && rg == 0) {
-    float o4[4];
+    __syncthreads();
+    float res[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      float p = 0.f;
+      float r = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) p += sSum[1][w][4 * cg + u];
-      o4[u] = a.scale * (p + res[u] * kq);
+      for (int w = 0; w < NW; ++w) r += sum[0][w][4 * cg + u];
+      res[u] = z[u] - r;
     }
-    put4(a.o + (size_t)seq * DV + 4 * cg, o4);
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+      const float k = Fl[4 * RG * i + 3];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) S[i][u] += k * res[u];
+    }
+    if constexpr (!MULTI) {
+      asm volatile("" : "+v"(ls));  // addresses anew: kept from the loads they would hold registers
+#pragma unroll
+      for (int i = 0; i < RPL; ++i) *reinterpret_cast<f4*>(Sg + (ls + RG * i * DV)) = S[i];
+    }
+    if (wave == 0 && rg == 0) {
+      float o4[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float p = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) p += sum[1][w][4 * cg + u];
+        o4[u] = a.scale * (p + res[u] * kq);
+      }
+      put4(a.o + ov + (size_t)t * vs, o4);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  if constexpr (MULTI) {
+    asm volatile("" : "+v"(ls));
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) *reinterpret_cast<f4*>(Sg + (ls + RG * i * DV)) = S[i];
   }
 }
 
+template <int DK, int DV, typename TIn, bool FUSED>
+__global__ __launch_bounds__(256) void recurrent_one_kernel(RecurArgs<TIn> a) {
+  __shared__ __align__(16) unsigned char smem[rows_lds<DK, DV, 4, false>()];
+  rows_tokens<DK, DV, TIn, FUSED, 4, false>(a, blockIdx.x, blockIdx.x / a.H, 1, smem);
+}
+
 // ---- any number of tokens --------------------------------------------------
-template <int DK, int DV, typename TIn, bool FUSED, int CW, int NW>
+// ROWS > 0 (a head's waves in one workgroup): a sequence of at most so many tokens
+// goes by rows instead (see the top).
+template <int DK, int DV, typename TIn, bool FUSED, int CW, int NW, int ROWS = 0>
 __global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
   constexpr int NSL = DV / CW;              // column slices, one per wave
   constexpr int CG = CW / 4, RG = 64 / CG;  // the lanes' column and row groups
@@ -239,37 +293,37 @@ __global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
   static_assert(RG == 8 || RG == 16, "row sums within 8 or 16 lanes");
   // floats of one row group's factors: (exp g, b k, q, -) per row, then k of its rows; padded
   constexpr int RGS = 5 * RPL + 4;
-  __shared__ __align__(16) float sF[NW][2][RG * RGS];
+  constexpr int LDS_COLS = 4 * NW * 2 * RG * RGS, LDS_ROWS = ROWS > 0 ? rows_lds<DK, DV, NW, true>() : 0;
+  __shared__ __align__(16) unsigned char smem[LDS_COLS > LDS_ROWS ? LDS_COLS : LDS_ROWS];
+  float(*sF)[2][RG * RGS] = reinterpret_cast<float(*)[2][RG * RGS]>(smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = blockIdx.x * NW + wave;
   const int seq = unit / NSL, v0 = CW * (unit % NSL);
   const int bb = seq / a.H, h = seq % a.H;
   const int rg = lane % RG, cg = lane / RG;
-  const int T = a.T, H = a.H;
+  const int H = a.H;
 
-  // tokens of this sequence: bb's T tokens, or cu[bb] .. cu[bb+1) of a packed batch (clamped into [0, T])
-  int t0 = 0, t1 = T;
-  size_t rbase = (size_t)bb * T;
-  if (a.cu != nullptr) {
-    t0 = min(max(a.cu[bb], 0), T);
-    t1 = min(max(a.cu[bb + 1], t0), T);
-    rbase = 0;
+  int t1;
+  size_t row;
+  if (!tokens(a, bb, row, t1)) return;  // no token: the state stays as it is
+  if constexpr (ROWS > 0) {
+    static_assert(NW * CW == DV, "a workgroup has a whole head");
+    if (t1 <= ROWS) return rows_tokens<DK, DV, TIn, FUSED, NW, true>(a, seq, row, t1, smem);
   }
-  if (t0 >= t1) return;  // no token: the state stays as it is
   const int HK = H / a.G, hk = h / a.G;  // key side (q, k, g, b) on the H / G key heads
   const size_t ks = (size_t)HK * DK, vs = (size_t)H * DV;  // token strides
   using Tok = Token<DK, TIn, FUSED>;
-  const size_t ok = (rbase + t0) * ks + (size_t)hk * DK + Tok::NK * lane;
-  const size_t ov = (rbase + t0) * vs + (size_t)h * DV + v0 + 4 * cg;
+  const size_t ok = row * ks + (size_t)hk * DK + Tok::NK * lane;
+  const size_t ov = row * vs + (size_t)h * DV + v0 + 4 * cg;
 
   // Past the last token the last one is read again, so that every path issues
   // the same loads (waits count them in issue order).
   Tok x;
   const auto fetch = [&](int t) {
-    const size_t d = (size_t)(min(t, t1 - 1) - t0);
+    const size_t d = (size_t)min(t, t1 - 1);
     x.load(a, ok + d * ks, ov + d * vs);
   };
-  fetch(t0);
+  fetch(0);
   Raw<float, Tok::NK> dl{};
   float Adec = 0.f;
   if constexpr (FUSED) {
@@ -294,14 +348,14 @@ __global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
   };
   float kq, z[4];
   stage(sF[wave][0], kq, z);
-  fetch(t0 + 1);
+  fetch(1);
   // the state has arrived: later waits are for tokens' operands alone
 #pragma unroll
   for (int i = 0; i < RPL; ++i) asm volatile("" : "+v"(S[i]));
 
   // Token t computes from one half of sF while the next one's factors go into the
   // other and the one after that is on its way from memory.
-  for (int t = t0, p = 0; t < t1; ++t, p ^= 1) {
+  for (int t = 0, p = 0; t < t1; ++t, p ^= 1) {
     const float* F = sF[wave][p] + rg * RGS;
     float kqn, zn[4];
     __builtin_amdgcn_wave_barrier();
@@ -348,12 +402,12 @@ __global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
     for (int i = 0; i < RPL; ++i)
 #pragma unroll
       for (int u = 0; u < 4; ++u) S[i][u] += kr[i / 4][i % 4] * res[u];
-    if (rg == 0) put4(a.o + ov + (size_t)(t - t0) * vs, o4);
+    if (rg == 0) put4(a.o + ov + (size_t)t * vs, o4);
     kq = kqn;
 #pragma unroll
     for (int u = 0; u < 4; ++u) z[u] = zn[u];
   }
-  asm volatile("" : "+v"(ls));  // as in recurrent_one_kernel
+  asm volatile("" : "+v"(ls));  // as in rows_tokens
 #pragma unroll
   for (int i = 0; i < RPL; ++i) *reinterpret_cast<f4*>(Sg + (ls + RG * i * DV)) = S[i];
 }
@@ -376,7 +430,11 @@ hipError_t launch_recurrent_t(const RecurArgs<TIn>& a, int B, hipStream_t st) {
       hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, FUSED, 16, NW>), dim3(seqs), dim3(64 * NW), 0, st, a);
   } else {
     constexpr int NW = DV / 32;
-    hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, FUSED, 32, NW>), dim3(seqs), dim3(64 * NW), 0, st, a);
+    if (a.cu == nullptr && a.T > kRowsTokens)
+      hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, FUSED, 32, NW>), dim3(seqs), dim3(64 * NW), 0, st, a);
+    else
+      hipLaunchKernelGGL((recurrent_kernel<DK, DV, TIn, FUSED, 32, NW, kRowsTokens>), dim3(seqs), dim3(64 * NW), 0, st,
+                         a);
   }
   return hipGetLastError();
 }

@@ -100,11 +100,12 @@ def test_chunk_then_decode_handoff(dtype):
 
 
 # the sizes where the recurrent kernels change: one token or several, and 16 columns a wave
-# (apart, together) or 32 by the number of (sequence, head) pairs
+# (apart, together) or 32 by the number of (sequence, head) pairs, these up to four tokens by rows
 @pytest.mark.parametrize("B,T,H,Dk,Dv,dtype", [
     (1, 1, 1, 64, 64, "fp32"), (3, 1, 2, 128, 64, "bf16"), (2, 1, 3, 64, 128, "bf16"), (2, 1, 1, 128, 128, "fp32"),
     (32, 2, 4, 64, 128, "bf16"), (43, 3, 3, 128, 128, "bf16"), (64, 2, 4, 128, 128, "fp32"),
-    (257, 2, 1, 128, 128, "bf16"), (513, 3, 1, 128, 64, "fp32")])
+    (257, 2, 1, 128, 128, "bf16"), (513, 3, 1, 128, 64, "fp32"), (260, 4, 1, 64, 128, "fp32"),
+    (260, 5, 1, 64, 128, "bf16"), (520, 4, 1, 64, 64, "bf16")])
 @pytest.mark.parametrize("fused", [False, True])
 def test_recurrent_routes(B, T, H, Dk, Dv, dtype, fused):
     import torch
@@ -132,3 +133,34 @@ def test_recurrent_routes(B, T, H, Dk, Dv, dtype, fused):
     # fp32 state arithmetic; fused bf16 rounds the normalised k, where a value next to a tie can go
     # either way (2^-8 of that value)
     assert rel_l2(host(S), S_ref) < (1e-4 if fused and dtype == "bf16" else 1e-5)
+
+
+@pytest.mark.parametrize("Dk,Dv,H,Hv,dtype", [(128, 128, 1, 1, "bf16"), (64, 128, 1, 2, "fp32"), (128, 64, 2, 2, "bf16"),
+                                              (64, 64, 2, 4, "bf16")])
+def test_recurrent_packed_mixed_counts(Dk, Dv, H, Hv, dtype):
+    """A packed batch past the line of 1024 32-column waves whose sequences take 0 to 9 tokens: those of
+    up to four go by rows, the others by columns, side by side in one launch."""
+    import torch
+    import paper_2605_22791_amd as g2
+    from oracle import gdr2_packed_fwd
+    rng = np.random.default_rng(77)
+    N = 1024 // (Hv * Dv // 32) + 3
+    lengths = rng.choice([0, 1, 1, 2, 3, 4, 5, 9], size=N)
+    lengths[:3], lengths[-2:] = (4, 5, 0), (9, 1)
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    T = int(cu[-1])
+    d = make_inputs(1, T, Hv, Dk, Dv, seed=97, dtype=dtype)
+    for n in ("q", "k", "log_alpha", "b"):
+        d[n] = np.ascontiguousarray(d[n][:, :, :H])
+    S0 = (0.1 * rng.standard_normal((N, Hv, Dk, Dv))).astype(np.float32)
+    _case(f"recurrent packed {N} sequences, T = {T}, H{H} Hv{Hv} Dk{Dk} Dv{Dv} {dtype}")
+    x = dev_inputs(dict(d, S0=S0))
+    S = x["S0"].clone()
+    o = g2.gdr2_recurrent_varlen(x["q"], x["k"], x["v"], x["log_alpha"], x["b"], x["w"], torch.from_numpy(cu).cuda(), S,
+                                 scale=d["scale"])
+    rep = {n: np.repeat(d[n].astype(np.float64), Hv // H, axis=2) for n in ("q", "k", "log_alpha", "b")}
+    o_ref, S_ref = gdr2_packed_fwd(rep["q"], rep["k"], d["v"], rep["log_alpha"], rep["b"], d["w"], cu, S0, d["scale"])
+    assert rel_l2(host(o), o_ref) < TOL[dtype]
+    assert rel_l2(host(S), S_ref) < 1e-5
+    none = torch.from_numpy(np.flatnonzero(lengths == 0)).cuda()
+    assert torch.equal(S[none], x["S0"][none])
