@@ -42,7 +42,7 @@ __global__ __launch_bounds__(4 * DK) void segcombine_kernel(SegCombineArgs a) {
     f4 n;           // N's tile
   };
   const auto load = [&](Ops& x, int step) {
-    const size_t sk = seg(min(step, nseg - 1));  // past the end: unused
+    const size_t sk = seg(min(step, nseg - 1));  // past the last link: unused
     const float *M = a.M + sk * DK * DK, *N = a.N + sk * DK * DV + o;
     if (a.transpose_m) {
 #pragma unroll
@@ -62,11 +62,13 @@ __global__ __launch_bounds__(4 * DK) void segcombine_kernel(SegCombineArgs a) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) x[u] = a.X0[(size_t)seq * DK * DV + o + (size_t)u * DV];
   }
-  // the value entering segment `step`, then X <- M X + N
-  const auto link = [&](Ops& w, int step) {
+  const auto enter = [&](int step) {  // the value entering segment `step`
     float* xs = a.Xs + seg(step) * DK * DV + o;
 #pragma unroll
     for (int u = 0; u < 4; ++u) xs[(size_t)u * DV] = x[u];
+  };
+  const auto link = [&](Ops& w, int step) {  // then X <- M X + N
+    enter(step);
     float* X = sX[step & 1] + lr * LX;
     *reinterpret_cast<f4*>(X + 16 * cb + 4 * lg) = x;
     __syncthreads();  // (the readers of the link before last are done, or they had not met the last link's)
@@ -88,11 +90,12 @@ __global__ __launch_bounds__(4 * DK) void segcombine_kernel(SegCombineArgs a) {
   load(ob, 1);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the loop's waits then count its own loads and stores alone
   int step = 0;
-  for (; step + 1 < nseg; step += 2) {
+  for (; step + 2 < nseg; step += 2) {
     link(oa, step);
     link(ob, step + 1);
   }
-  if (step < nseg) link(oa, step);
+  if (step + 1 < nseg) link(oa, step++);
+  enter(step);  // nothing follows the last segment
 }
 
 template <int DK, int DV>
