@@ -373,18 +373,17 @@ hipError_t timed(int id, hipStream_t st, F&& launch) {
 
 // ---- grouped value heads of fp32 problems: sum each key head's G partials into
 // dq, dk, db, dlog_alpha (p: the value view, so the key heads are p->H / G)
-template <typename TIn>
 hipError_t group_reduce(const gdr2_problem* p, const Geo& G, const Layout& L, void* ws, void* dq, void* dk,
                         void* db, float* dg, hipStream_t st) {
   const size_t rows = (size_t)p->B * p->T;
   const int Hk = p->H / G.G;
   hipError_t e = hipSuccess;
   if (dq != nullptr)
-    e = launch_group_reduce<TIn>(at<float>(ws, L.pQ), static_cast<TIn*>(dq), rows, Hk, G.G, p->Dk, st);
+    e = launch_group_reduce(at<float>(ws, L.pQ), static_cast<float*>(dq), rows, Hk, G.G, p->Dk, st);
   if (e == hipSuccess && dk != nullptr)
-    e = launch_group_reduce<TIn>(at<float>(ws, L.pK), static_cast<TIn*>(dk), rows, Hk, G.G, p->Dk, st);
-  if (e == hipSuccess) e = launch_group_reduce<TIn>(at<float>(ws, L.pB), static_cast<TIn*>(db), rows, Hk, G.G, p->Dk, st);
-  if (e == hipSuccess) e = launch_group_reduce<float>(at<float>(ws, L.pG), dg, rows, Hk, G.G, p->Dk, st);
+    e = launch_group_reduce(at<float>(ws, L.pK), static_cast<float*>(dk), rows, Hk, G.G, p->Dk, st);
+  if (e == hipSuccess) e = launch_group_reduce(at<float>(ws, L.pB), static_cast<float*>(db), rows, Hk, G.G, p->Dk, st);
+  if (e == hipSuccess) e = launch_group_reduce(at<float>(ws, L.pG), dg, rows, Hk, G.G, p->Dk, st);
   return e;
 }
 
@@ -578,18 +577,18 @@ struct FwdRun {
         }, st);
       });
     } else {
-      IntraArgs<TIn> ia{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
-                        static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
-                        static_cast<const TIn*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
-                        at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
-                        at<float>(ws, L.GC), p->T, p->H, NT};
+      IntraArgs ia{static_cast<const float*>(q), static_cast<const float*>(k),
+                   static_cast<const float*>(v), g, static_cast<const float*>(b),
+                   static_cast<const float*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
+                   at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
+                   at<float>(ws, L.GC), p->T, p->H, NT};
       ia.vl = G.vl;
       ia.G = G.G;
-      hipError_t e = timed(GDR2_K_FWD_INTRA, st, [&] { return launch_fwd_intra<DK, DV, TIn>(ia, p->B, st); });
+      hipError_t e = timed(GDR2_K_FWD_INTRA, st, [&] { return launch_fwd_intra<DK, DV>(ia, p->B, st); });
       if (e != hipSuccess) return e;
-      StateArgs<TIn> sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, ST, static_cast<TIn*>(o),
-                        save ? at<float>(ws, L.Hs) : nullptr, save ? at<float>(ws, L.Rs) : nullptr,
-                        p->T, p->H, NT, p->scale, G.nscan * p->H};
+      StateArgs sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, ST, static_cast<float*>(o),
+                   save ? at<float>(ws, L.Hs) : nullptr, save ? at<float>(ws, L.Rs) : nullptr,
+                   p->T, p->H, NT, p->scale, G.nscan * p->H};
       sa.vl = G.vl;
       return timed(GDR2_K_FWD_STATE, st, [&] {
         return save ? launch_fwd_state<DK, DV, true, true>(sa, st) : launch_fwd_state<DK, DV, true, false>(sa, st);
@@ -693,50 +692,50 @@ struct BwdRun {
       if (e != hipSuccess || !fused) return e;
       return timed(GDR2_K_STAGE_BWD, st, [&] { return stage_bwd<DK>(p, G, ws, q, k, dq, dk, da, ddelta, st); });
     } else {
-      IntraArgs<TIn> ia{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
-                        static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
-                        static_cast<const TIn*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
-                        at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
-                        at<float>(ws, L.GC), p->T, p->H, NT};
+      IntraArgs ia{static_cast<const float*>(q), static_cast<const float*>(k),
+                   static_cast<const float*>(v), g, static_cast<const float*>(b),
+                   static_cast<const float*>(w), at<float>(ws, L.Y), at<float>(ws, L.U),
+                   at<float>(ws, L.Kt), at<float>(ws, L.Qg), at<float>(ws, L.Aqk),
+                   at<float>(ws, L.GC), p->T, p->H, NT};
       ia.vl = G.vl;
       ia.G = G.G;
-      StateArgs<TIn> sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, nullptr, nullptr,
-                        at<float>(ws, L.Hs), at<float>(ws, L.Rs), p->T, p->H, NT, p->scale,
-                        G.nscan * p->H};
+      StateArgs sa{ia.Y, ia.U, ia.Kt, ia.Qg, ia.Aqk, ia.GC, S0, nullptr, nullptr,
+                   at<float>(ws, L.Hs), at<float>(ws, L.Rs), p->T, p->H, NT, p->scale,
+                   G.nscan * p->H};
       sa.vl = G.vl;
       if (!saved) {
-        e = timed(GDR2_K_BWD_RECOMPUTE_INTRA, st, [&] { return launch_fwd_intra<DK, DV, TIn>(ia, p->B, st); });
+        e = timed(GDR2_K_BWD_RECOMPUTE_INTRA, st, [&] { return launch_fwd_intra<DK, DV>(ia, p->B, st); });
         if (e != hipSuccess) return e;
         e = timed(GDR2_K_BWD_RECOMPUTE_STATE, st,
                   [&] { return launch_fwd_state<DK, DV, false, true>(sa, st); });
         if (e != hipSuccess) return e;
       }
-      BwdStateArgs<TIn> ba{ia.Qg, ia.Kt, ia.Y, ia.Aqk, ia.GC, static_cast<const TIn*>(dout), dST,
-                           dS0, at<float>(ws, L.DH), at<float>(ws, L.DR), p->T, p->H, NT, p->scale,
-                           G.nscan * p->H};
+      BwdStateArgs ba{ia.Qg, ia.Kt, ia.Y, ia.Aqk, ia.GC, static_cast<const float*>(dout), dST,
+                      dS0, at<float>(ws, L.DH), at<float>(ws, L.DR), p->T, p->H, NT, p->scale,
+                      G.nscan * p->H};
       ba.vl = G.vl;
       e = timed(GDR2_K_BWD_STATE, st, [&] { return launch_bwd_state<DK, DV>(ba, st); });
       if (e != hipSuccess) return e;
-      BwdChunkArgs<TIn> ca{static_cast<const TIn*>(q), static_cast<const TIn*>(k),
-                           static_cast<const TIn*>(v), g, static_cast<const TIn*>(b),
-                           static_cast<const TIn*>(w), static_cast<const TIn*>(dout),
-                           sa.Hs, ba.DH, sa.Rs, ba.DR, at<float>(ws, L.DAqk), at<float>(ws, L.DT),
-                           at<float>(ws, L.DEg), static_cast<TIn*>(dq), static_cast<TIn*>(dk),
-                           static_cast<TIn*>(dv), static_cast<TIn*>(db), static_cast<TIn*>(dw), dg,
-                           p->T, p->H, NT, p->scale};
+      BwdChunkArgs ca{static_cast<const float*>(q), static_cast<const float*>(k),
+                      static_cast<const float*>(v), g, static_cast<const float*>(b),
+                      static_cast<const float*>(w), static_cast<const float*>(dout),
+                      sa.Hs, ba.DH, sa.Rs, ba.DR, at<float>(ws, L.DAqk), at<float>(ws, L.DT),
+                      at<float>(ws, L.DEg), static_cast<float*>(dq), static_cast<float*>(dk),
+                      static_cast<float*>(dv), static_cast<float*>(db), static_cast<float*>(dw), dg,
+                      p->T, p->H, NT, p->scale};
       ca.vl = G.vl;
       ca.G = G.G;
-      e = timed(GDR2_K_BWD_WY, st, [&] { return launch_bwd_wy<DK, DV, TIn>(ca, p->B, st); });
+      e = timed(GDR2_K_BWD_WY, st, [&] { return launch_bwd_wy<DK, DV>(ca, p->B, st); });
       if (e != hipSuccess) return e;
       if (G.G > 1) {  // the key-side gradients of each value head go to the fp32 partials
-        ca.dq = reinterpret_cast<TIn*>(at<float>(ws, L.pQ));
-        ca.dk = reinterpret_cast<TIn*>(at<float>(ws, L.pK));
-        ca.db = reinterpret_cast<TIn*>(at<float>(ws, L.pB));
+        ca.dq = at<float>(ws, L.pQ);
+        ca.dk = at<float>(ws, L.pK);
+        ca.db = at<float>(ws, L.pB);
         ca.dg = at<float>(ws, L.pG);
       }
       return timed(GDR2_K_BWD_INTRA, st, [&] {
-        hipError_t r = launch_bwd_intra<DK, DV, TIn>(ca, p->B, st);
-        if (r == hipSuccess && G.G > 1) r = group_reduce<TIn>(p, G, L, ws, dq, dk, db, dg, st);
+        hipError_t r = launch_bwd_intra<DK, DV>(ca, p->B, st);
+        if (r == hipSuccess && G.G > 1) r = group_reduce(p, G, L, ws, dq, dk, db, dg, st);
         return r;
       });
     }

@@ -33,7 +33,7 @@ namespace gdr2 {
 // and for that of wave - 4.  8 sequences x 16 chunks at 128 x 128: 65 us (385
 // with 32 columns, four waves and operands loaded where they are used).
 template <int DK, int DV>
-__global__ __launch_bounds__(512) void bwd_state_kernel(BwdStateArgs<float> a) {
+__global__ __launch_bounds__(512) void bwd_state_kernel(BwdStateArgs a) {
   constexpr int NCB = DK / 16;
   constexpr int LT = DK + 4, LR = CH + 4;
   int q, vs;
@@ -210,8 +210,8 @@ __global__ __launch_bounds__(512) void bwd_state_kernel(BwdStateArgs<float> a) {
 // Gate-aware WY VJP.  Writes dv, dw (final), and per chunk-head workspace:
 //   DAqk (64x64) = tril(scale dO R^T),  DT (64x64) strict lower,
 //   DEg (64xDK)  = (A^T dY) * gamma  with dY = -dR S0^T.
-template <int DK, int DV, typename TIn>
-__global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
+template <int DK, int DV>
+__global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs a) {
   constexpr int NTHR = 512, NW = 8;
   constexpr int LS = DK + 4;
   ChunkPos cp;
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
       int i, j;
       pair_of(it, i, j);
       const f4 acc = (i == j && split[i] == kSplitNone)
-                         ? diag_tile_direct<DK, TIn>(a.b + kbase, a.k + kbase, a.k + kbase,
+                         ? diag_tile_direct<DK>(a.b + kbase, a.k + kbase, a.k + kbase,
                                                      a.g + kbase, rs, i, lane, true, len)
                          : gram_tile<DK>(sLe, sRk, brg, split, i, j, lane);
       const int s = 16 * j + lr;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
       const int i = (it - 10) >> 2, j = (it - 10) & 3;
       f4 acc = {0.f, 0.f, 0.f, 0.f};
       if (j <= i) {
-        const TIn* pd = a.dout + vbase + (16 * i + lr) * rsv + 4 * lg;
+        const float* pd = a.dout + vbase + (16 * i + lr) * rsv + 4 * lg;
         const bool pdin = 16 * i + lr < len;
         const float* pr = Rn + (16 * j + lr) * DV + 4 * lg;
         for (int kk = 0; kk < DV; kk += 16) {
@@ -346,8 +346,8 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
       if (isZ) {
         const size_t off = vbase + s * rsv + col;
         if (s < len) {
-          put(a.dw + off, acc[u] * to_f(a.v[off]));
-          put(a.dv + off, acc[u] * to_f(a.w[off]));
+          a.dw[off] = acc[u] * a.v[off];
+          a.dv[off] = acc[u] * a.w[off];
         }
       } else {
         DEg[s * DK + col] = acc[u] * expf(sG[s * LS + col]);
@@ -362,8 +362,8 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
     f4 acc = {0.f, 0.f, 0.f, 0.f};
     if (j <= i) {
       const float* pa = DRn + (16 * i + lr) * DV + 4 * lg;
-      const TIn* pw = a.w + vbase + (16 * j + lr) * rsv + 4 * lg;
-      const TIn* pv = a.v + vbase + (16 * j + lr) * rsv + 4 * lg;
+      const float* pw = a.w + vbase + (16 * j + lr) * rsv + 4 * lg;
+      const float* pv = a.v + vbase + (16 * j + lr) * rsv + 4 * lg;
       const bool jin = 16 * j + lr < len;
       for (int kk = 0; kk < DV; kk += 16) {
         const float4 x = ld4(pa + kk), w4 = ld4z(pw + kk, jin), v4 = ld4z(pv + kk, jin);
@@ -431,8 +431,8 @@ __global__ __launch_bounds__(512) void bwd_wy_kernel(BwdChunkArgs<TIn> a) {
 
 // ---------------------------------------------------------------------------
 // Intra-chunk VJP and decay chain: dq, dk, db, dlog_alpha.
-template <int DK, int DV, typename TIn>
-__global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
+template <int DK, int DV>
+__global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs a) {
   constexpr int NTHR = 512, NW = 8;
   constexpr int LS = DK + 4;
   constexpr int NCB = DK / 16;
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
     }
     // dQs = dO S0^T and dKt = R dS_C^T
     {
-      const TIn* pd = a.dout + vbase + (16 * i + lr) * rsv + 4 * lg;
+      const float* pd = a.dout + vbase + (16 * i + lr) * rsv + 4 * lg;
       const bool pdin = 16 * i + lr < len;
       const float* pr = Rn + (16 * i + lr) * DV + 4 * lg;
       const float* ph = Hn + (16 * cb + lr) * DV + 4 * lg;
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
       const float tail = expf(sG[(CH - 1) * LS + c] - G);
       const size_t off = kbase + r * rs + c, offo = kobase + r * rso + c;
       const bool rin = r < len;
-      const float kv = to_fz(a.k + off, rin), bv = to_fz(a.b + off, rin), qv = to_fz(a.q + off, rin);
+      const float kv = ldz(a.k + off, rin), bv = ldz(a.b + off, rin), qv = ldz(a.q + off, rin);
       float dEg = DEg[r * DK + c] + lf * P1[u];
       float dq = a.scale * gam * dQs[u] + lf * P2[u];
       float dKg = rf * P3[u] + tail * dKt[u];
@@ -583,21 +583,21 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
           const float Gs = sG[s * LS + c];
           if (s <= r) {
             const float e = expf(G - Gs);   // r >= s: <= 1
-            const float ks = to_fz(a.k + so, s < len);
+            const float ks = ldz(a.k + so, s < len);
             if (s < r) dEg += DT[r * CH + s] * ks * e;
             dq += DAqk[r * CH + s] * ks * e;
           }
           if (s >= r) {
             const float e = expf(Gs - G);   // s >= r: <= 1
-            if (s > r) dKg += DT[s * CH + r] * to_fz(a.b + so, s < len) * to_fz(a.k + so, s < len) * e;
-            dKg += DAqk[s * CH + r] * to_fz(a.q + so, s < len) * e;
+            if (s > r) dKg += DT[s * CH + r] * ldz(a.b + so, s < len) * ldz(a.k + so, s < len) * e;
+            dKg += DAqk[s * CH + r] * ldz(a.q + so, s < len) * e;
           }
         }
       }
       if (rin) {
-        put(a.db + offo, dEg * kv);
-        put(a.dk + offo, dEg * bv + dKg);
-        put(a.dq + offo, dq);
+        a.db[offo] = dEg * kv;
+        a.dk[offo] = dEg * bv + dKg;
+        a.dq[offo] = dq;
       }
       keep[q][u] = dq * qv - dKg * kv + dEg * bv * kv;
       tailpart += dKt[u] * kv * tail;
@@ -644,38 +644,38 @@ __global__ __launch_bounds__(512) void bwd_intra_kernel(BwdChunkArgs<TIn> a) {
 
 // ---------------------------------------------------------------------------
 template <int DK, int DV>
-hipError_t launch_bwd_state(const BwdStateArgs<float>& a, hipStream_t st) {
+hipError_t launch_bwd_state(const BwdStateArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((bwd_state_kernel<DK, DV>), dim3(state_slots<DV / 16>(a.nq)), dim3(512), 0, st, a);
   return hipGetLastError();
 }
 
-template <int DK, int DV, typename TIn>
-hipError_t launch_bwd_wy(const BwdChunkArgs<TIn>& a, int B, hipStream_t st) {
+template <int DK, int DV>
+hipError_t launch_bwd_wy(const BwdChunkArgs& a, int B, hipStream_t st) {
   constexpr size_t lds = sizeof(float) * (3 * CH * (DK + 4) + 2 * CH * LD64 + 15 * DK) + 4 * sizeof(int);
-  hipError_t e = hipFuncSetAttribute((const void*)bwd_wy_kernel<DK, DV, TIn>,
+  hipError_t e = hipFuncSetAttribute((const void*)bwd_wy_kernel<DK, DV>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   dim3 grid(a.vl.ct0 ? a.vl.ncmax : a.NT, a.H, a.vl.ct0 ? 1 : B);
-  hipLaunchKernelGGL((bwd_wy_kernel<DK, DV, TIn>), grid, dim3(512), lds, st, a);
+  hipLaunchKernelGGL((bwd_wy_kernel<DK, DV>), grid, dim3(512), lds, st, a);
   return hipGetLastError();
 }
 
-template <int DK, int DV, typename TIn>
-hipError_t launch_bwd_intra(const BwdChunkArgs<TIn>& a, int B, hipStream_t st) {
+template <int DK, int DV>
+hipError_t launch_bwd_intra(const BwdChunkArgs& a, int B, hipStream_t st) {
   constexpr int NSPLIT = 512 / DK;
   constexpr size_t lds = sizeof(float) * (4 * CH * (DK + 4) + 15 * DK + 16 * DK + DK * NSPLIT) + 4 * sizeof(int);
-  hipError_t e = hipFuncSetAttribute((const void*)bwd_intra_kernel<DK, DV, TIn>,
+  hipError_t e = hipFuncSetAttribute((const void*)bwd_intra_kernel<DK, DV>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   dim3 grid(a.vl.ct0 ? a.vl.ncmax : a.NT, a.H, a.vl.ct0 ? 1 : B);
-  hipLaunchKernelGGL((bwd_intra_kernel<DK, DV, TIn>), grid, dim3(512), lds, st, a);
+  hipLaunchKernelGGL((bwd_intra_kernel<DK, DV>), grid, dim3(512), lds, st, a);
   return hipGetLastError();
 }
 
-#define GDR2_INST_BWD(DK, DV)                                                                     \
-  template hipError_t launch_bwd_state<DK, DV>(const BwdStateArgs<float>&, hipStream_t);          \
-  template hipError_t launch_bwd_wy<DK, DV, float>(const BwdChunkArgs<float>&, int, hipStream_t); \
-  template hipError_t launch_bwd_intra<DK, DV, float>(const BwdChunkArgs<float>&, int, hipStream_t);
+#define GDR2_INST_BWD(DK, DV)                                                          \
+  template hipError_t launch_bwd_state<DK, DV>(const BwdStateArgs&, hipStream_t);      \
+  template hipError_t launch_bwd_wy<DK, DV>(const BwdChunkArgs&, int, hipStream_t);    \
+  template hipError_t launch_bwd_intra<DK, DV>(const BwdChunkArgs&, int, hipStream_t);
 
 GDR2_INST_BWD(64, 64)
 GDR2_INST_BWD(64, 128)

@@ -55,37 +55,12 @@ __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ float to_f(float x) { return x; }
-__device__ __forceinline__ float to_f(bf16_t x) { return __uint_as_float(((uint32_t)x.x) << 16); }
-
-__device__ __forceinline__ void put(float* p, float x) { *p = x; }
-__device__ __forceinline__ void put(bf16_t* p, float x) {
-  uint32_t u = __float_as_uint(x);
-  uint16_t r;
-  if ((u & 0x7fffffffu) > 0x7f800000u) {
-    r = 0x7fc0;  // quiet NaN
-  } else {
-    u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
-    r = (uint16_t)(u >> 16);
-  }
-  p->x = r;
-}
-
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ float4 ld4(const bf16_t* p) {
-  uint2 u = *reinterpret_cast<const uint2*>(p);
-  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
-}
-// ld4 / to_f of a token row that may lie past a partial chunk's end (then 0)
-template <typename T>
-__device__ __forceinline__ float4 ld4z(const T* p, bool ok) {
+// a token row's values where it may lie past a partial chunk's end (then 0)
+__device__ __forceinline__ float4 ld4z(const float* p, bool ok) {
   return ok ? ld4(p) : make_float4(0.f, 0.f, 0.f, 0.f);
 }
-template <typename T>
-__device__ __forceinline__ float to_fz(const T* p, bool ok) {
-  return ok ? to_f(*p) : 0.f;
-}
+__device__ __forceinline__ float ldz(const float* p, bool ok) { return ok ? *p : 0.f; }
 __device__ __forceinline__ float f4at(const float4& v, int u) {
   return u == 0 ? v.x : (u == 1 ? v.y : (u == 2 ? v.z : v.w));
 }
@@ -235,9 +210,9 @@ __device__ __forceinline__ f4 gram_tile(const float* L, const float* R, const fl
 // s = 16i+n, for r >= s (strict when `strict`), else 0.  X = b*k (Gram T) or
 // q (scores).  Reads the raw inputs; G differences are accumulated locally
 // from g so they never leave the block.  Rows >= len read as zero.
-template <int DK, typename TIn>
-__device__ f4 diag_tile_direct(const TIn* __restrict__ x1, const TIn* __restrict__ x2,
-                               const TIn* __restrict__ k, const float* __restrict__ g,
+template <int DK>
+__device__ f4 diag_tile_direct(const float* __restrict__ x1, const float* __restrict__ x2,
+                               const float* __restrict__ k, const float* __restrict__ g,
                                size_t rs, int i, int lane, bool strict, int len) {
   f4 acc = {0.f, 0.f, 0.f, 0.f};
   const int n = lane & 15, mb = 4 * (lane >> 4);
@@ -245,20 +220,20 @@ __device__ f4 diag_tile_direct(const TIn* __restrict__ x1, const TIn* __restrict
   for (int c = 0; c < DK; ++c) {
     float run = 0.f, Gs = 0.f, Gr[4] = {0.f, 0.f, 0.f, 0.f};
     for (int t = 0; t < 16; ++t) {
-      run += to_fz(g + (16 * i + t) * rs + c, 16 * i + t < len);
+      run += ldz(g + (16 * i + t) * rs + c, 16 * i + t < len);
       if (t == n) Gs = run;
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         if (t == mb + u) Gr[u] = run;
     }
-    const float ks = to_fz(k + s * rs + c, s < len);
+    const float ks = ldz(k + s * rs + c, s < len);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int m = mb + u;
       if (m > n || (!strict && m == n)) {
         const int r = 16 * i + m;
-        float xv = to_fz(x1 + r * rs + c, r < len);
-        if (x2) xv *= to_fz(x2 + r * rs + c, r < len);
+        float xv = ldz(x1 + r * rs + c, r < len);
+        if (x2) xv *= ldz(x2 + r * rs + c, r < len);
         acc[u] += xv * ks * expf(Gr[u] - Gs);
       }
     }

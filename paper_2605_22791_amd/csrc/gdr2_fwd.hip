@@ -25,8 +25,8 @@ namespace gdr2 {
 //   Qg[ch]  (64 x DK)  gamma_r * q_r
 //   Aqk[ch] (64 x 64)  causal scores, zero above the diagonal
 //   GC[ch]  (DK)       gamma_C
-template <int DK, int DV, typename TIn>
-__global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
+template <int DK, int DV>
+__global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs a) {
   constexpr int NTHR = 512;
   constexpr int LS = DK + 4;
   ChunkPos cp;
@@ -97,8 +97,8 @@ __global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
     pair_of(isT ? it : it - 10, i, j);
     f4 acc;
     if (i == j && split[i] == kSplitNone) {
-      acc = isT ? diag_tile_direct<DK, TIn>(a.b + kbase, a.k + kbase, a.k + kbase, a.g + kbase, rs, i, lane, true, len)
-                : diag_tile_direct<DK, TIn>(a.q + kbase, nullptr, a.k + kbase, a.g + kbase, rs, i, lane, false, len);
+      acc = isT ? diag_tile_direct<DK>(a.b + kbase, a.k + kbase, a.k + kbase, a.g + kbase, rs, i, lane, true, len)
+                : diag_tile_direct<DK>(a.q + kbase, nullptr, a.k + kbase, a.g + kbase, rs, i, lane, false, len);
     } else {
       acc = gram_tile<DK>(isT ? sLe : sLq, sRk, brg, split, i, j, lane);
     }
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(512) void fwd_intra_kernel(IntraArgs<TIn> a) {
 // calls, 128 x 128, NV = 1 / 2: 128 pairs of 256 tokens 136 / 118 us, 64 of 512 128 / 113,
 // 32 of 1000 (256 slices, one a CU) 126 / 150, 4 of 512 63 / 76.
 template <int DK, int DV, bool WITH_O, bool STORE_H, int NV>
-__global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
+__global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs a) {
   constexpr int NCB = DK / 16;      // key blocks: S tiles, one per wave
   constexpr int LT = DK + 4, LR = CH + 4;
   int q, vs;
@@ -392,22 +392,22 @@ __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs<float> a) {
 }
 
 // ---------------------------------------------------------------------------
-template <int DK, int DV, typename TIn>
-hipError_t launch_fwd_intra(const IntraArgs<TIn>& a, int B, hipStream_t st) {
+template <int DK, int DV>
+hipError_t launch_fwd_intra(const IntraArgs& a, int B, hipStream_t st) {
   constexpr size_t lds = sizeof(float) * (4 * CH * (DK + 4) + CH * LD64 + 15 * DK) + 4 * sizeof(int);
   // Z (row stride DV+4) reuses the dead sLq + sRk regions
   static_assert(CH * (DV + 4) <= 2 * CH * (DK + 4), "Z tile fits the freed regions");
   static_assert(CH * LD64 <= CH * (DK + 4), "T tile fits the G region");
-  hipError_t e = hipFuncSetAttribute((const void*)fwd_intra_kernel<DK, DV, TIn>,
+  hipError_t e = hipFuncSetAttribute((const void*)fwd_intra_kernel<DK, DV>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   dim3 grid(a.vl.ct0 ? a.vl.ncmax : a.NT, a.H, a.vl.ct0 ? 1 : B);
-  hipLaunchKernelGGL((fwd_intra_kernel<DK, DV, TIn>), grid, dim3(512), lds, st, a);
+  hipLaunchKernelGGL((fwd_intra_kernel<DK, DV>), grid, dim3(512), lds, st, a);
   return hipGetLastError();
 }
 
 template <int DK, int DV, bool WITH_O, bool STORE_H>
-hipError_t launch_fwd_state(const StateArgs<float>& a, hipStream_t st) {
+hipError_t launch_fwd_state(const StateArgs& a, hipStream_t st) {
   if ((long long)a.nq * (DV / 16) <= 256)  // a CU for each narrow slice
     hipLaunchKernelGGL((fwd_state_kernel<DK, DV, WITH_O, STORE_H, 1>), dim3(state_slots<DV / 16>(a.nq)), dim3(512),
                        0, st, a);
@@ -417,11 +417,11 @@ hipError_t launch_fwd_state(const StateArgs<float>& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-#define GDR2_INST_FWD(DK, DV)                                                                \
-  template hipError_t launch_fwd_intra<DK, DV, float>(const IntraArgs<float>&, int, hipStream_t); \
-  template hipError_t launch_fwd_state<DK, DV, true, false>(const StateArgs<float>&, hipStream_t); \
-  template hipError_t launch_fwd_state<DK, DV, false, true>(const StateArgs<float>&, hipStream_t); \
-  template hipError_t launch_fwd_state<DK, DV, true, true>(const StateArgs<float>&, hipStream_t);
+#define GDR2_INST_FWD(DK, DV)                                                               \
+  template hipError_t launch_fwd_intra<DK, DV>(const IntraArgs&, int, hipStream_t);         \
+  template hipError_t launch_fwd_state<DK, DV, true, false>(const StateArgs&, hipStream_t); \
+  template hipError_t launch_fwd_state<DK, DV, false, true>(const StateArgs&, hipStream_t); \
+  template hipError_t launch_fwd_state<DK, DV, true, true>(const StateArgs&, hipStream_t);
 
 GDR2_INST_FWD(64, 64)
 GDR2_INST_FWD(64, 128)

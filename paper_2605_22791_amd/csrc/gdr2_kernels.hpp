@@ -155,14 +155,13 @@ struct Stage {
 // Arguments of the intra-chunk forward kernel.  Inputs use the operator's
 // token-major layouts; outputs are per-chunk-head workspace tiles, chunk-head
 // index ch = (b * H + h) * NT + n.
-template <typename TIn>
 struct IntraArgs {
-  const TIn* q;
-  const TIn* k;
-  const TIn* v;
+  const float* q;
+  const float* k;
+  const float* v;
   const float* g;
-  const TIn* b;
-  const TIn* w;
+  const float* b;
+  const float* w;
   float* Y;
   float* U;
   float* Kt;
@@ -175,7 +174,6 @@ struct IntraArgs {
 };
 
 // Arguments of the sequential forward state kernel.
-template <typename TIn>
 struct StateArgs {
   const float* Y;
   const float* U;
@@ -185,7 +183,7 @@ struct StateArgs {
   const float* GC;
   const float* S0;  // nullable
   float* ST;        // nullable
-  TIn* o;           // written when the output is fused in
+  float* o;         // written when the output is fused in
   float* Hs;        // chunk-start states (backward recompute)
   float* Rs;        // R per chunk (backward recompute)
   int T, H, NT;
@@ -195,14 +193,13 @@ struct StateArgs {
 };
 
 // Reverse state scan of the backward (App. B.1).
-template <typename TIn>
 struct BwdStateArgs {
   const float* Qg;
   const float* Kt;
   const float* Y;
   const float* Aqk;
   const float* GC;
-  const TIn* dout;
+  const float* dout;
   const float* dST;  // nullable
   float* dS0;        // nullable
   float* DH;         // gradient of each chunk's end state
@@ -214,15 +211,14 @@ struct BwdStateArgs {
 };
 
 // Chunk-parallel backward kernels (App. B.2 - B.5).
-template <typename TIn>
 struct BwdChunkArgs {
-  const TIn* q;
-  const TIn* k;
-  const TIn* v;
+  const float* q;
+  const float* k;
+  const float* v;
   const float* g;
-  const TIn* b;
-  const TIn* w;
-  const TIn* dout;
+  const float* b;
+  const float* w;
+  const float* dout;
   const float* Hs;
   const float* DH;
   const float* Rs;
@@ -230,11 +226,11 @@ struct BwdChunkArgs {
   float* DAqk;
   float* DT;
   float* DEg;
-  TIn* dq;
-  TIn* dk;
-  TIn* dv;
-  TIn* db;
-  TIn* dw;
+  float* dq;
+  float* dk;
+  float* dv;
+  float* db;
+  float* dw;
   float* dg;
   int T, H, NT;
   float scale;
@@ -476,23 +472,22 @@ hipError_t launch_bchunk_bf16(const BChunkBf16Args& a, hipStream_t st);
 template <int DK, int DV>
 hipError_t launch_segcombine(const SegCombineArgs& a, hipStream_t st);
 
-template <int DK, int DV, typename TIn>
-hipError_t launch_fwd_intra(const IntraArgs<TIn>& a, int B, hipStream_t st);
-template <int DK, int DV, bool WITH_O, bool STORE_H>
-hipError_t launch_fwd_state(const StateArgs<float>& a, hipStream_t st);
 template <int DK, int DV>
-hipError_t launch_bwd_state(const BwdStateArgs<float>& a, hipStream_t st);
-template <int DK, int DV, typename TIn>
-hipError_t launch_bwd_wy(const BwdChunkArgs<TIn>& a, int B, hipStream_t st);
-template <int DK, int DV, typename TIn>
-hipError_t launch_bwd_intra(const BwdChunkArgs<TIn>& a, int B, hipStream_t st);
+hipError_t launch_fwd_intra(const IntraArgs& a, int B, hipStream_t st);
+template <int DK, int DV, bool WITH_O, bool STORE_H>
+hipError_t launch_fwd_state(const StateArgs& a, hipStream_t st);
+template <int DK, int DV>
+hipError_t launch_bwd_state(const BwdStateArgs& a, hipStream_t st);
+template <int DK, int DV>
+hipError_t launch_bwd_wy(const BwdChunkArgs& a, int B, hipStream_t st);
+template <int DK, int DV>
+hipError_t launch_bwd_intra(const BwdChunkArgs& a, int B, hipStream_t st);
 template <int DK, int DV, typename TIn>
 hipError_t launch_recurrent(const RecurArgs<TIn>& a, int B, hipStream_t st);
 
 // Grouped value heads: out[r, h, c] = sum_{j < G} P[r, h * G + j, c] for rows
-// r < rows, key heads h < Hk, channels c < D (P fp32 on the value-head axis).
-template <typename TOut>
-hipError_t launch_group_reduce(const float* P, TOut* out, size_t rows, int Hk, int G, int D, hipStream_t st);
+// r < rows, key heads h < Hk, channels c < D (P on the value-head axis).
+hipError_t launch_group_reduce(const float* P, float* out, size_t rows, int Hk, int G, int D, hipStream_t st);
 
 // Normalisation VJP of the fused stage (App. D.2): for rows r < rows, key
 // heads hk < Hk, dx = rinv (dy - y <y, dy>), y = rinv x, with x the raw q or
