@@ -104,20 +104,6 @@ __device__ __forceinline__ float wave_sum(float x, int lane) {
   return x + row_partner32(x, lane >= 32);
 }
 
-// Tokens of sequence bb: its T, or cu[bb] .. cu[bb+1) of a packed batch (clamped into
-// [0, T]); the first one's row and their number, false if there is none.
-template <typename TIn>
-__device__ __forceinline__ bool tokens(const RecurArgs<TIn>& a, int bb, size_t& row, int& n) {
-  row = (size_t)bb * a.T;
-  n = a.T;
-  if (a.cu != nullptr) {
-    const int t0 = min(max(a.cu[bb], 0), a.T);
-    row = (size_t)t0;
-    n = min(max(a.cu[bb + 1], t0), a.T) - t0;
-  }
-  return n > 0;
-}
-
 // A wave's part of a token: NK = DK / 64 key-side rows and four value columns per lane
 template <int DK, typename TIn, bool FUSED>
 struct Token {
@@ -301,29 +287,35 @@ __global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
   const int seq = unit / NSL, v0 = CW * (unit % NSL);
   const int bb = seq / a.H, h = seq % a.H;
   const int rg = lane % RG, cg = lane / RG;
-  const int H = a.H;
+  const int T = a.T, H = a.H;
 
-  int t1;
-  size_t row;
-  if (!tokens(a, bb, row, t1)) return;  // no token: the state stays as it is
+  // tokens of this sequence: bb's T tokens, or cu[bb] .. cu[bb+1) of a packed batch (clamped into [0, T])
+  int t0 = 0, t1 = T;
+  size_t rbase = (size_t)bb * T;
+  if (a.cu != nullptr) {
+    t0 = min(max(a.cu[bb], 0), T);
+    t1 = min(max(a.cu[bb + 1], t0), T);
+    rbase = 0;
+  }
+  if (t0 >= t1) return;  // no token: the state stays as it is
   if constexpr (ROWS > 0) {
     static_assert(NW * CW == DV, "a workgroup has a whole head");
-    if (t1 <= ROWS) return rows_tokens<DK, DV, TIn, FUSED, NW, true>(a, seq, row, t1, smem);
+    if (t1 - t0 <= ROWS) return rows_tokens<DK, DV, TIn, FUSED, NW, true>(a, seq, rbase + t0, t1 - t0, smem);
   }
   const int HK = H / a.G, hk = h / a.G;  // key side (q, k, g, b) on the H / G key heads
   const size_t ks = (size_t)HK * DK, vs = (size_t)H * DV;  // token strides
   using Tok = Token<DK, TIn, FUSED>;
-  const size_t ok = row * ks + (size_t)hk * DK + Tok::NK * lane;
-  const size_t ov = row * vs + (size_t)h * DV + v0 + 4 * cg;
+  const size_t ok = (rbase + t0) * ks + (size_t)hk * DK + Tok::NK * lane;
+  const size_t ov = (rbase + t0) * vs + (size_t)h * DV + v0 + 4 * cg;
 
   // Past the last token the last one is read again, so that every path issues
   // the same loads (waits count them in issue order).
   Tok x;
   const auto fetch = [&](int t) {
-    const size_t d = (size_t)min(t, t1 - 1);
+    const size_t d = (size_t)(min(t, t1 - 1) - t0);
     x.load(a, ok + d * ks, ov + d * vs);
   };
-  fetch(0);
+  fetch(t0);
   Raw<float, Tok::NK> dl{};
   float Adec = 0.f;
   if constexpr (FUSED) {
@@ -348,14 +340,14 @@ __global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
   };
   float kq, z[4];
   stage(sF[wave][0], kq, z);
-  fetch(1);
+  fetch(t0 + 1);
   // the state has arrived: later waits are for tokens' operands alone
 #pragma unroll
   for (int i = 0; i < RPL; ++i) asm volatile("" : "+v"(S[i]));
 
   // Token t computes from one half of sF while the next one's factors go into the
   // other and the one after that is on its way from memory.
-  for (int t = 0, p = 0; t < t1; ++t, p ^= 1) {
+  for (int t = t0, p = 0; t < t1; ++t, p ^= 1) {
     const float* F = sF[wave][p] + rg * RGS;
     float kqn, zn[4];
     __builtin_amdgcn_wave_barrier();
@@ -402,7 +394,7 @@ __global__ __launch_bounds__(64 * NW) void recurrent_kernel(RecurArgs<TIn> a) {
     for (int i = 0; i < RPL; ++i)
 #pragma unroll
       for (int u = 0; u < 4; ++u) S[i][u] += kr[i / 4][i % 4] * res[u];
-    if (rg == 0) put4(a.o + ov + (size_t)t * vs, o4);
+    if (rg == 0) put4(a.o + ov + (size_t)(t - t0) * vs, o4);
     kq = kqn;
 #pragma unroll
     for (int u = 0; u < 4; ++u) z[u] = zn[u];
