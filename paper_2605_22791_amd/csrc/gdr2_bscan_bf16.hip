@@ -108,7 +108,7 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
     slice = blockIdx.x % NS;
   }
   const int seq = scan_pair(a.vl, vs / nseg, H), seg = vs % nseg;  // (sequence, head) pair
-  const ScanRange rng = scan_range(a.vl, seq, H, NT);
+  const ScanRange rng = scan_range(a.vl, seq, H, T, NT);
   const int seg_len = a.seg_len > 0 ? a.seg_len : rng.c1 - rng.c0;
   const int n0 = rng.c0 + seg * seg_len, n1 = min(rng.c1, n0 + seg_len);
   const bool no_input = (a.flags & kScanNoInput) != 0;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(512) void bscan_bf16_kernel(BScanArgs a) {
     const int r_ = tid / (DVS / 8), c8_ = (tid % (DVS / 8)) * 8;                                       \
     size_t orow_;                                                                                      \
     int olen_;                                                                                         \
-    scan_rows(a.vl, seq, H, T, (N_), orow_, olen_);                                                    \
+    scan_rows(rng, (N_), orow_, olen_);                                                                \
     /* through a buffer whose range ends with the chunk's last row (empty       */                  \
     /* without dO): rows past it read as zero, with no branch around the load  */                  \
     const unsigned pitch_ = (unsigned)(H * DV) * 2u;                                                   \

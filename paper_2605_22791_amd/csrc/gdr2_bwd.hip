@@ -42,7 +42,7 @@ __global__ __launch_bounds__(512) void bwd_state_kernel(BwdStateArgs a) {
   const int lr = lane & 15, lg = lane >> 4, v0 = 16 * vs + lr;
   const size_t seq = (size_t)scan_pair(a.vl, q, a.H);  // (sequence, head) pair
   const int h = (int)(seq % a.H);
-  const ScanRange rng = scan_range(a.vl, (int)seq, a.H, a.NT);
+  const ScanRange rng = scan_range(a.vl, (int)seq, a.H, a.T, a.NT);
   const bool low = wave < 4, own = NCB == 8 || low;
   const int i = wave & 3, cb = own ? wave : 0;
 
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(512) void bwd_state_kernel(BwdStateArgs a) {
       const size_t ch = rng.chs + n;
       size_t row0;
       int len;
-      scan_rows(a.vl, (int)seq, a.H, a.T, n, row0, len);
+      scan_rows(rng, n, row0, len);
       // rows past the chunk's end read its last row; put_dO makes them zero
       const int r = tid >> 3;
       o.in = r < len;

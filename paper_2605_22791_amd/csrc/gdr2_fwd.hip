@@ -208,7 +208,7 @@ __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs a) {
   const int lr = lane & 15, lg = lane >> 4, v0 = 16 * NV * vs + lr;
   const size_t seq = (size_t)scan_pair(a.vl, q, a.H);  // (sequence, head) pair
   const int h = (int)(seq % a.H);
-  const ScanRange rng = scan_range(a.vl, (int)seq, a.H, a.NT);
+  const ScanRange rng = scan_range(a.vl, (int)seq, a.H, a.T, a.NT);
   const bool low = wave < 4, own = NCB == 8 || low;
   const int i = wave & 3, cb = own ? wave : 0;  // row block of the products; key block of the S tile
 
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(512) void fwd_state_kernel(StateArgs a) {
         }
         size_t row0;
         int len;
-        scan_rows(a.vl, (int)seq, a.H, a.T, n, row0, len);
+        scan_rows(rng, n, row0, len);
         // rows past the chunk's end go over U's, which nobody reads any more: a
         // store on every path (waits count stores too)
         float* O = a.o + ((row0 + 16 * i + 4 * lg) * a.H + h) * DV + v0;

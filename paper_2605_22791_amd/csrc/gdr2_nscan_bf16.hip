@@ -68,7 +68,7 @@ __global__ __launch_bounds__(nscan_threads(DK, WITH_O)) void nscan_bf16_kernel(S
     slice = rem % NS;
   }
   const int seq = scan_pair(a.vl, q, H), h = seq % H;  // (sequence, head) pair
-  const ScanRange rng = scan_range(a.vl, seq, H, a.NT);
+  const ScanRange rng = scan_range(a.vl, seq, H, a.T, a.NT);
   const size_t chs = rng.chs;                          // value-head chunks: U, h, R
   const size_t chk = key_ch(a.vl, chs, H, a.G, a.NT);  // key-head chunks: Y, Q_g, A_qk, K_tail, gamma_C
   const int v0 = slice * DVS;
@@ -158,6 +158,8 @@ __global__ __launch_bounds__(nscan_threads(DK, WITH_O)) void nscan_bf16_kernel(S
     };
     u4v x[4];  // A_qk's blocks, one chunk ahead (registers for two chunks are not there)
     f4 acc[2];
+    __bf16* const oseq = reinterpret_cast<__bf16*>(a.o) + (rng.row0 + 16 * i + r16) * ((size_t)H * DV) +
+                         (size_t)h * DV + v0 + 4 * g;
     const auto load_A = [&](int n) {
       // keys 32.. of query rows 0..31 are zero and not stored: the first block again, unused
       const unsigned char* A = a.Aqk + (chk + n) * WsBf16::aqk() + i * 4096 + 16 * lane;
@@ -203,16 +205,13 @@ __global__ __launch_bounds__(nscan_threads(DK, WITH_O)) void nscan_bf16_kernel(S
           asm volatile("" ::: "memory");
           load_A(min(n + 1, rng.c1 - 1));
           asm volatile("" ::: "memory");
-          size_t row0;
-          int len;
-          scan_rows(a.vl, seq, H, a.T, n, row0, len);
+          const int t0 = (n - rng.c0) * CH;  // the chunk's first token
           // rows past the chunk's end go over the slice's U tiles of this chunk,
           // which nobody reads any more: a store on every path
-          __bf16* orow = reinterpret_cast<__bf16*>(a.o) + (row0 + 16 * i + r16) * ((size_t)H * DV) + (size_t)h * DV +
-                         v0 + 4 * g;
+          __bf16* orow = oseq + t0 * (size_t)(H * DV);
           __bf16* urow = reinterpret_cast<__bf16*>(const_cast<float*>(a.U) + (chs + n) * (WsBf16::u(DV) / 4) +
                                                    ((size_t)(v0 / 16 * 4 + i) * 64 + lane) * 4);
-          const bool in = 16 * i + r16 < len;
+          const bool in = t0 + 16 * i + r16 < rng.rows;
 #pragma unroll
           for (int t = 0; t < 2; ++t)
             st4(in ? orow + 16 * t : urow + 4 * t, a.scale * acc[t][0], a.scale * acc[t][1], a.scale * acc[t][2],

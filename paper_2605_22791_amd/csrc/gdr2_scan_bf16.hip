@@ -134,7 +134,7 @@ __global__ __launch_bounds__(512) void scan_bf16_kernel(ScanArgs a) {
     slice = blockIdx.x % NS;
   }
   const int seq = scan_pair(a.vl, vs / nseg, H), seg = vs % nseg;  // (sequence, head) pair
-  const ScanRange rng = scan_range(a.vl, seq, H, NT);
+  const ScanRange rng = scan_range(a.vl, seq, H, T, NT);
   const int seg_len = a.seg_len > 0 ? a.seg_len : rng.c1 - rng.c0;
   const int n0 = rng.c0 + seg * seg_len, n1 = min(rng.c1, n0 + seg_len);
   // MAP: slice 0 is the N map (input U, zero start), slice 1 the M map
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(512) void scan_bf16_kernel(ScanArgs a) {
       const float sc = a.scale;
       size_t orow;
       int olen;
-      scan_rows(a.vl, seq, H, T, n, orow, olen);
+      scan_rows(rng, n, orow, olen);
       if (16 * iO + r16 < olen) {
         __bf16* orp = O + (orow + 16 * iO + r16) * ((size_t)H * DV) + (size_t)h * DV + v0;
 #pragma unroll
