@@ -25,8 +25,8 @@
 // = 1.1e26 before its other factor, or e^-60: finite, and nothing lost, for operands
 // of 1e-12 to 1e12.  The limit is that of the operands; a split at the block's ends up
 // to e^78 left 4.5e4.  The element-by-element tile is slow enough to set a kernel's time,
-// and the layer's own decay (exp(a) up to 16) passes e^60 in some 3 of 10^3 (block, head)
-// pairs, e^60 in a half in none of 3 10^4 drawn: 1000 tokens x 16 heads from raw
+// and the layer's own decay (exp(a) up to 16) passes e^60 in 1 (Dk = 64) to 2 of 10^3
+// (block, head) pairs, e^60 in a half in 1 of 10^5: 1000 tokens x 16 heads from raw
 // projections, training, 891 us with it past e^60, 438 with the middle.  The paper
 // does not prescribe a stabilisation; this one is this library's.
 

@@ -5,11 +5,11 @@
 //              fp32 WY solve and the auxiliaries Y = A Ebar, U = A (W*V)
 //              (Sec. 3.3; App. A; App. C.2: the intra-chunk products, the WY
 //              solve and the construction of the auxiliaries).
-//   fwd_state  one workgroup per (value slice, head, batch): the sequential
-//              inter-chunk recurrence (eq. eq_gdn2_chunk_state) with the fp32
-//              state slice resident in LDS, fused with the chunk output
-//              (eq. eq_gdn2_chunk_output).  Columns of S evolve independently,
-//              so the value axis is split across workgroups.
+//   fwd_state  one workgroup per (sequence, head) and one or two 16-column value
+//              slices: the sequential inter-chunk recurrence (eq.
+//              eq_gdn2_chunk_state) with the fp32 state in registers, fused with
+//              the chunk output (eq. eq_gdn2_chunk_output).  Columns of S evolve
+//              independently, so the value axis is split across workgroups.
 
 #include "gdr2_kernels.hpp"
 

@@ -22,14 +22,15 @@
 // block: 2^(G2_r - G2_p) * 2^(G2_p - G2_s).  p is the middle row (8 of 16): in the
 // diagonal block each factor is bounded by half a block's decay (entries above
 // the diagonal may overflow and are masked), and left of it the first factor is
-// and the second is <= 1.  In a block with a half whose decay exceeds e^60 p is the
-// first row, both factors <= 1 left of the diagonal, and the diagonal block takes
-// four 4-row sub-blocks: products split at each sub-block's first row (both
-// factors <= 1) and its own 4 x 4 pairs element by element.  Split at the block's
-// first row and beyond that element by element (16 x 16 x Dk serial steps, some
-// 90 us), the 3 to 6 in 10^4 (block, head) pairs over the bound at the layer's own
-// decay distribution (exp(a) up to 16) set the kernel's time: 8192 tokens x 16
-// heads from raw projections took 212 us, 146 then.
+// and the second is <= 1.  (So q, k and b k meet at most e^60 before their other
+// factor: finite up to 1e12, as in gdr2_device.hpp.)  In a block with a half whose
+// decay exceeds e^60 p is the first row, both factors <= 1 left of the diagonal, and
+// the diagonal block takes four 4-row sub-blocks: products split at each sub-block's
+// first row (both factors <= 1) and its own 4 x 4 pairs element by element.  Split at
+// the block's first row and beyond that element by element (16 x 16 x Dk serial steps,
+// some 90 us), the 1 (Dk = 64) to 2 in 10^3 (block, head) pairs over the bound at the
+// layer's own decay distribution (exp(a) up to 16) set the kernel's time: 8192 tokens x
+// 16 heads from raw projections took 212 us, 146 then.
 //
 // A row block's tiles share p, so a wave takes a row block's tiles side by side
 // and forms their query side (decay factor, b * k, splits) once a K-step.  Dealt
