@@ -504,20 +504,22 @@ hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, hipStre
 // in length, and the same line is where their total load is half the CUs' for as many
 // steps as the longest sequence has (packed_narrow).  The host knows where up to 128 wide
 // scans make it certain; else the table on the device does (kByTable: both kernels are
-// launched, the one not meant leaves at once, 4 us).  Whole calls of 16 heads, by table /
-// all narrow / all wide: training 6 sequences of 2048 808 / 901 / 807, 16 of 300 375 / 409 /
-// 367, two of 2048 and six of 100 443 / 439 / 516; forward 8 of 1024 184 / 203 / 180, 9 of
-// 37 to 3000 238 / 238 / 286.  A forward of up to 12 chunks for each CU gains less by it
-// than the launch takes (16 of 300: 130 / 135, two and six: 140 / 134) and is narrow; above
-// 512 wide scans, or 32 chunks for each CU, the wide ones are taken unasked (the long
-// packed training batch, 64 a CU: 2065 narrow and 1905 wide).
+// launched, the one not meant leaves at once, 4.6 us).  Training, 16 heads, by table / all
+// narrow / all wide: 6 sequences of 2048 808 / 901 / 807 us, 16 of 300 375 / 409 / 367, two of
+// 2048 and six of 100 443 / 439 / 516.  A forward alone gives 2 % for it where one sequence is
+// long (9 of 37 to 3000: 242 against 238) and would gain 10 % where all are alike (8 of 1024:
+// 188 against 203): narrow unasked; so is training's forward up to 12 chunks for each CU,
+// where the launch costs what it gives.  Above 512 wide scans, or 32 chunks for each CU,
+// the wide ones are taken unasked (the long packed training batch, 64 a CU: 2065 narrow
+// and 1905 wide).
 enum Slices { kWide, kNarrow, kByTable };
-Slices scan_slices(const gdr2_problem* p, const Geo& G, bool reverse) {
+enum Scan { kForwardScan, kTrainingForwardScan, kReverseScan };
+Slices scan_slices(const gdr2_problem* p, const Geo& G, Scan scan) {
   if (G.L.nseg > 1) return kWide;
-  const long long per_seq = (long long)p->H * (p->Dv / 64), wide = G.nscan * per_seq;
+  const long long per_seq = (long long)p->H * (p->Dv / 64), wide = G.nscan * per_seq, load = G.NT * per_seq;
   if (wide <= 128) return kNarrow;
-  if (G.vl.cu == nullptr || wide > 512 || G.NT * per_seq > 32 * 256) return kWide;
-  return reverse || G.NT * per_seq > 12 * 256 ? kByTable : kNarrow;
+  if (G.vl.cu == nullptr || wide > 512 || load > 32 * 256) return kWide;
+  return scan == kReverseScan || (scan == kTrainingForwardScan && load > 12 * 256) ? kByTable : kNarrow;
 }
 
 // Runs `launch(args, narrow)` for a scan's slices: one kernel, or both (kByTable).
@@ -569,7 +571,8 @@ struct FwdRun {
       sa.G = G.G;
       return timed(GDR2_K_FWD_STATE, st, [&] {
         return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& y) {
-          return in_slices(scan_slices(p, G, false), p, y, [&](const ScanArgs& x, bool narrow) {
+          const Slices slices = scan_slices(p, G, save ? kTrainingForwardScan : kForwardScan);
+          return in_slices(slices, p, y, [&](const ScanArgs& x, bool narrow) {
             if (narrow)
               return save ? launch_nscan_bf16<DK, DV, true, true>(x, st) : launch_nscan_bf16<DK, DV, true, false>(x, st);
             return save ? launch_scan_bf16<DK, DV, true, true>(x, st) : launch_scan_bf16<DK, DV, true, false>(x, st);
@@ -632,7 +635,7 @@ struct BwdRun {
         sa.G = G.G;
         e = timed(GDR2_K_BWD_RECOMPUTE_STATE, st, [&] {
           return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& y) {
-            return in_slices(scan_slices(p, G, false), p, y, [&](const ScanArgs& x, bool narrow) {
+            return in_slices(scan_slices(p, G, kTrainingForwardScan), p, y, [&](const ScanArgs& x, bool narrow) {
               return narrow ? launch_nscan_bf16<DK, DV, false, true>(x, st)
                             : launch_scan_bf16<DK, DV, false, true>(x, st);
             });
@@ -647,7 +650,7 @@ struct BwdRun {
       ba.G = G.G;
       e = timed(GDR2_K_BWD_STATE, st, [&] {
         if (L.nseg > 1) return scan_bwd_bf16<DK, DV>(ba, L, ws, st);
-        return in_slices(scan_slices(p, G, true), p, ba, [&](const BScanArgs& x, bool narrow) {
+        return in_slices(scan_slices(p, G, kReverseScan), p, ba, [&](const BScanArgs& x, bool narrow) {
           return launch_bscan_bf16<DK, DV>(x, narrow, st);
         });
       });
