@@ -168,7 +168,8 @@ __device__ __forceinline__ void rows_tokens(const RecurArgs<TIn>& a, int seq, si
 
   using Tok = Token<DK, TIn, FUSED>;
   const size_t ks = (size_t)HK * DK, vs = (size_t)a.H * DV;  // token strides
-  const size_t ok = row * ks + (size_t)hk * DK + Tok::NK * lane, ov = row * vs + (size_t)h * DV + 4 * cg;
+  const size_t ok = (row * HK + hk) * DK + Tok::NK * lane;
+  const size_t ov = (MULTI ? row * a.H + h : (size_t)seq) * DV + 4 * cg;
   Tok x;
   x.load(a, ok, ov);
   Raw<float, Tok::NK> dl{};
@@ -189,9 +190,10 @@ __device__ __forceinline__ void rows_tokens(const RecurArgs<TIn>& a, int seq, si
       *reinterpret_cast<float4*>(F + 4 * row) = make_float4(al, e, q, k);
     });
     float z[4];
+    if constexpr (MULTI) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) z[u] = x.v.at(u) * x.w.at(u);
-    if constexpr (MULTI) {  // the next token (past the last one the last again)
+      for (int u = 0; u < 4; ++u) z[u] = x.v.at(u) * x.w.at(u);
+      // the next token (past the last one the last again)
       const size_t d = (size_t)min(t + 1, n - 1);
       x.load(a, ok + d * ks, ov + d * vs);
     }
@@ -229,7 +231,7 @@ __device__ __forceinline__ void rows_tokens(const RecurArgs<TIn>& a, int seq, si
       float r = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) r += sum[0][w][4 * cg + u];
-      res[u] = z[u] - r;
+      res[u] = (MULTI ? z[u] : x.v.at(u) * x.w.at(u)) - r;
     }
 #pragma unroll
     for (int i = 0; i < RPL; ++i) {
@@ -265,7 +267,8 @@ __device__ __forceinline__ void rows_tokens(const RecurArgs<TIn>& a, int seq, si
 template <int DK, int DV, typename TIn, bool FUSED>
 __global__ __launch_bounds__(256) void recurrent_one_kernel(RecurArgs<TIn> a) {
   __shared__ __align__(16) unsigned char smem[rows_lds<DK, DV, 4, false>()];
-  rows_tokens<DK, DV, TIn, FUSED, 4, false>(a, blockIdx.x, blockIdx.x / a.H, 1, smem);
+  const int seq = blockIdx.x;  // signed, as the remainder in rows_tokens: one division for both
+  rows_tokens<DK, DV, TIn, FUSED, 4, false>(a, seq, seq / a.H, 1, smem);
 }
 
 // ---- any number of tokens --------------------------------------------------
