@@ -505,21 +505,20 @@ hipError_t scan_bwd_bf16(const BScanArgs& ba, const Layout& L, void* ws, hipStre
 // steps as the longest sequence has (packed_narrow).  The host knows where up to 128 wide
 // scans make it certain; else the table on the device does (kByTable: both kernels are
 // launched, the one not meant leaves at once, 4.6 us).  Training, 16 heads, by table / all
-// narrow / all wide: 6 sequences of 2048 808 / 901 / 807 us, 16 of 300 375 / 409 / 367, two of
-// 2048 and six of 100 443 / 439 / 516.  A forward alone gives 2 % for it where one sequence is
-// long (9 of 37 to 3000: 242 against 238) and would gain 10 % where all are alike (8 of 1024:
-// 188 against 203): narrow unasked; so is training's forward up to 12 chunks for each CU,
-// where the launch costs what it gives.  Above 512 wide scans, or 32 chunks for each CU,
-// the wide ones are taken unasked (the long packed training batch, 64 a CU: 2065 narrow
-// and 1905 wide).
+// narrow: 6 sequences of 2048 802 / 895 us, 16 of 512 548 / 598; 9 of 37 to 3000 679 / 675.
+// Up to 12 chunks for each CU the launches cost what they give (38 sequences of 21 to
+// 2197, 2 heads: 317 against 312): narrow unasked; so is a forward alone, which gives 2 % for
+// them where one sequence is long (9 of 37 to 3000: 242 against 238) and would gain 10 %
+// where all are alike (8 of 1024: 188 against 203).  Above 512 wide scans, or 32 chunks for
+// each CU, the wide ones are taken unasked (the long packed training batch, 64 a CU: 2065
+// narrow and 1905 wide).
 enum Slices { kWide, kNarrow, kByTable };
-enum Scan { kForwardScan, kTrainingForwardScan, kReverseScan };
-Slices scan_slices(const gdr2_problem* p, const Geo& G, Scan scan) {
+Slices scan_slices(const gdr2_problem* p, const Geo& G, bool training) {
   if (G.L.nseg > 1) return kWide;
   const long long per_seq = (long long)p->H * (p->Dv / 64), wide = G.nscan * per_seq, load = G.NT * per_seq;
   if (wide <= 128) return kNarrow;
   if (G.vl.cu == nullptr || wide > 512 || load > 32 * 256) return kWide;
-  return scan == kReverseScan || (scan == kTrainingForwardScan && load > 12 * 256) ? kByTable : kNarrow;
+  return training && load > 12 * 256 ? kByTable : kNarrow;
 }
 
 // Runs `launch(args, narrow)` for a scan's slices: one kernel, or both (kByTable).
@@ -571,8 +570,7 @@ struct FwdRun {
       sa.G = G.G;
       return timed(GDR2_K_FWD_STATE, st, [&] {
         return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& y) {
-          const Slices slices = scan_slices(p, G, save ? kTrainingForwardScan : kForwardScan);
-          return in_slices(slices, p, y, [&](const ScanArgs& x, bool narrow) {
+          return in_slices(scan_slices(p, G, save), p, y, [&](const ScanArgs& x, bool narrow) {
             if (narrow)
               return save ? launch_nscan_bf16<DK, DV, true, true>(x, st) : launch_nscan_bf16<DK, DV, true, false>(x, st);
             return save ? launch_scan_bf16<DK, DV, true, true>(x, st) : launch_scan_bf16<DK, DV, true, false>(x, st);
@@ -635,7 +633,7 @@ struct BwdRun {
         sa.G = G.G;
         e = timed(GDR2_K_BWD_RECOMPUTE_STATE, st, [&] {
           return scan_fwd_bf16<DK, DV>(sa, L, ws, [&](const ScanArgs& y) {
-            return in_slices(scan_slices(p, G, kTrainingForwardScan), p, y, [&](const ScanArgs& x, bool narrow) {
+            return in_slices(scan_slices(p, G, true), p, y, [&](const ScanArgs& x, bool narrow) {
               return narrow ? launch_nscan_bf16<DK, DV, false, true>(x, st)
                             : launch_scan_bf16<DK, DV, false, true>(x, st);
             });
@@ -650,7 +648,7 @@ struct BwdRun {
       ba.G = G.G;
       e = timed(GDR2_K_BWD_STATE, st, [&] {
         if (L.nseg > 1) return scan_bwd_bf16<DK, DV>(ba, L, ws, st);
-        return in_slices(scan_slices(p, G, kReverseScan), p, ba, [&](const BScanArgs& x, bool narrow) {
+        return in_slices(scan_slices(p, G, true), p, ba, [&](const BScanArgs& x, bool narrow) {
           return launch_bscan_bf16<DK, DV>(x, narrow, st);
         });
       });
