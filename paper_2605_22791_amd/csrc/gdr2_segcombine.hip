@@ -19,7 +19,7 @@
 // of M_k and N_k loaded straight into its registers two links ahead, fp32 MFMA
 // (no splitting; 32 products deep at Dk = 128), X handed round through LDS with
 // one barrier a link.  The slices of a sequence share their XCD (state_slot).
-// 16 sequences x 8 segments at 128 x 128: 23 us (39 with split-bf16 products on
+// 16 sequences x 8 segments at 128 x 128: 21 us (39 with split-bf16 products on
 // 64-wide slices and M_k loaded where it is used, 4.7 us a link).
 
 #include "gdr2_kernels.hpp"
